@@ -89,25 +89,43 @@ __device__ __forceinline__ Nb nbrs(int i, int j, int k, int nx, int ny, int nz) 
 // reductions (deterministic)
 // ---------------------------------------------------------------------------
 
-__device__ __forceinline__ double wave_sum(double v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+// v of the lane that a DPP row operation names, 0 where there is none
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp_get(double v) {
+  const long long b = __double_as_longlong(v);
+  const int lo = __builtin_amdgcn_update_dpp(0, (int)b, CTRL, ROWS, 0xf, true);
+  const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, ROWS, 0xf, true);
+  return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
+}
+
+__device__ __forceinline__ double lane_get(double v, int lane) {
+  const long long b = __double_as_longlong(v);
+  const int lo = __builtin_amdgcn_readlane((int)b, lane);
+  const int hi = __builtin_amdgcn_readlane((int)(b >> 32), lane);
+  return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
+}
+
+// running sums within each row of 16 lanes: lane 15 holds the row's total
+__device__ __forceinline__ double row_scan(double v) {
+  v += dpp_get<0x111, 0xf>(v);  // row_shr:1
+  v += dpp_get<0x112, 0xf>(v);
+  v += dpp_get<0x114, 0xf>(v);
+  v += dpp_get<0x118, 0xf>(v);
   return v;
 }
 
-// Sum over the block; the result is valid in every thread.
-template <int NW>
-__device__ __forceinline__ double block_sum(double v, double *sh) {
-  v = wave_sum(v);
-  const int w = threadIdx.x >> 6;
-  __syncthreads();
-  if ((threadIdx.x & 63) == 0) sh[w] = v;
-  __syncthreads();
-  double s = 0.0;
-#pragma unroll
-  for (int i = 0; i < NW; ++i) s += sh[i];
-  return s;
+// Sum over the wave, in every lane, by DPP moves (registers only: a
+// butterfly of cross-lane LDS operations takes about four times as long).
+// Every lane must be active.
+__device__ __forceinline__ double wave_total(double v) {
+  v = row_scan(v);
+  v += dpp_get<0x142, 0xa>(v);  // row_bcast:15 into rows 1 and 3
+  v += dpp_get<0x143, 0xc>(v);  // row_bcast:31 into rows 2 and 3
+  return lane_get(v, 63);
 }
+
+// Sum of lanes 0 .. 15, in every lane.
+__device__ __forceinline__ double row_total(double v) { return lane_get(row_scan(v), 15); }
 
 // N sums of a tile into out[N * tile + i] (one LDS round for all of them)
 template <int N>
@@ -116,7 +134,7 @@ __device__ __forceinline__ void write_sums(double *out, int tile, const double (
   __shared__ double sh[N][NW];
   double w[N];
 #pragma unroll
-  for (int i = 0; i < N; ++i) w[i] = wave_sum(v[i]);
+  for (int i = 0; i < N; ++i) w[i] = wave_total(v[i]);
   if ((threadIdx.x & 63) == 0) {
 #pragma unroll
     for (int i = 0; i < N; ++i) sh[i][threadIdx.x >> 6] = w[i];
@@ -132,13 +150,8 @@ __device__ __forceinline__ void write_sums(double *out, int tile, const double (
 
 __device__ __forceinline__ void write_partials(const Tables &T, int tile,
                                                double a0, double a1) {
-  __shared__ double sh[kBlock / 64];
-  const double s0 = block_sum<kBlock / 64>(a0, sh);
-  const double s1 = block_sum<kBlock / 64>(a1, sh);
-  if (threadIdx.x == 0) {
-    T.part[2 * tile] = s0;
-    T.part[2 * tile + 1] = s1;
-  }
+  const double v[2] = {a0, a1};
+  write_sums(T.part, tile, v);
 }
 
 // ---------------------------------------------------------------------------

@@ -320,9 +320,11 @@ int Engine::setup(const fld_params &p, hipStream_t s,
   hier.resize(np);
   mem.resize(np);
   Lmax = 0;
+  tail_big = 0;
   for (int i = 0; i < np; ++i) {
     hier[i] = make_hier(g[i], p);
     Lmax = std::max(Lmax, hier[i].levels);
+    if (hier[i].cells(hier[i].levels - 1) > 2 * kTailBlock) tail_big = 1;
   }
   tables_layout(tbl, hier, this);
   for (int i = 0; i < np; ++i) {
@@ -605,7 +607,7 @@ void Engine::enqueue_fused_rest(const ListSet &ls) {
     launch_pre0(T, ls.gsm[l], l, prec, stream);
     if (l + 1 < Lmax) launch_resid_restrict(T, ls.gdn[l + 1], l + 1, prec, stream);
   }
-  if (Lmax > 1) launch_vtail(T, prec, 1, 1, tri, stream);
+  if (Lmax > 1) launch_vtail(T, prec, 1, 1, tri, tail_big, stream);
   for (int l = Lmax - 1; l >= 1; --l) {
     launch_vup(T, ls.fsm[l], l, prec, 0, tri, stream);
     launch_prolong_black(T, ls.gsm[l], l, prec, tri, stream);
@@ -648,7 +650,7 @@ void Engine::enqueue_vcycle(const ListSet &ls) {
       }
       if (l + 1 < Lmax) launch_resid_restrict(T, down[l + 1], l + 1, prec, stream);
     }
-    if (Lmax > 1) launch_vtail(T, prec, np, nq, tri, stream);
+    if (Lmax > 1) launch_vtail(T, prec, np, nq, tri, tail_big, stream);
     for (int l = Lmax - 1; l >= 0; --l) {
       if (smooth[l].nblocks == 0) continue;
       int in2 = nq & 1;  // buffer the correction lands in
@@ -670,7 +672,7 @@ void Engine::enqueue_vcycle(const ListSet &ls) {
     }
     if (l + 1 < Lmax) launch_resid_restrict(T, down[l + 1], l + 1, prec, stream);
   }
-  if (Lmax > 1) launch_vtail(T, prec, prm.nu_pre, prm.nu_post, tri, stream);
+  if (Lmax > 1) launch_vtail(T, prec, prm.nu_pre, prm.nu_post, tri, tail_big, stream);
   for (int l = Lmax - 1; l >= 0; --l) {
     if (smooth[l].nblocks == 0) continue;
     launch_prolong_black(T, smooth[l], l, prec, tri, stream);

@@ -97,6 +97,7 @@ class Engine {
   std::vector<Hier> hier;
   std::vector<ProbMem> mem;
   int Lmax = 0;
+  int tail_big = 0;        // a coarsest level of more than 2 kTailBlock cells
 
   // host mirrors of the device tables
   std::vector<LevelDev> h_lv;

@@ -220,8 +220,9 @@ void launch_resid_restrict(const Tables &T, TileList coarse, int lc, int prec,
                            hipStream_t s);
 void launch_prolong_black(const Tables &T, TileList L, int l, int prec,
                           int trilinear, hipStream_t s);
+// big: some problem's coarsest level has more than 2048 cells
 void launch_vtail(const Tables &T, int prec, int nu_pre, int nu_post,
-                  int trilinear, hipStream_t s);
+                  int trilinear, int big, hipStream_t s);
 // weighted Jacobi smoother: mode 0 = first sweep from x = 0, 1 = sweep,
 // 2 = last finest-level sweep writing z and the r.z partials (in = x2);
 // in_x2 selects the input buffer, the output is the other one

@@ -555,215 +555,6 @@ __global__ __launch_bounds__(kBlock) void k_prolong_add(Tables T, TileList TL,
 }
 
 // ---------------------------------------------------------------------------
-// Tail of the V-cycle, one workgroup per problem: the coarsest level's
-// Jacobi-CG solve and, above it, the levels from P.tail down (each small):
-// pre-smoothing and restriction down to the coarsest level, the solve, then
-// prolongation and post-smoothing back up to P.tail, in the order of the
-// per-level path (red/black, red = even i+j+k), separated by workgroup
-// barriers on data that stays in the L2.  (By default P.tail is the
-// coarsest level: on gfx950 one workgroup sweeping 16^3 or 32^3 levels is
-// no faster than the per-level launches it replaces.)
-// ---------------------------------------------------------------------------
-
-template <typename R>
-struct LvlView {
-  int nx, ny, nz, n;
-  Coef<R> C;
-  R *x, *f;
-  __device__ __forceinline__ void ijk(int c, int &i, int &j, int &k) const {
-    i = c % nx;
-    j = (c / nx) % ny;
-    k = c / (nx * ny);
-  }
-};
-
-template <typename R>
-__device__ __forceinline__ LvlView<R> lvl_view(const Tables &T, int l, int p) {
-  const LevelDev L = T.lv[l * T.nprob + p];
-  LvlView<R> v;
-  v.nx = L.nx;
-  v.ny = L.ny;
-  v.nz = L.nz;
-  v.n = L.n;
-  v.C = coefs<R>(L);
-  v.x = (R *)L.x;
-  v.f = (R *)L.f;
-  return v;
-}
-
-// first pre-sweep from x = 0 (red x = f/d, black from those red values)
-template <typename R>
-__device__ void tail_pre0(const LvlView<R> &V) {
-  for (int c = threadIdx.x; c < V.n; c += kTailBlock) {
-    int i, j, k;
-    V.ijk(c, i, j, k);
-    const Nb n = nbrs(i, j, k, V.nx, V.ny, V.nz);
-    R v;
-    if (((i + j + k) & 1) == 0) {
-      v = V.f[c] * recip(V.C.d[c]);
-    } else {
-      auto red = [&](int q) { return V.f[q] * recip(V.C.d[q]); };
-      v = (V.f[c] + offsum(V.C, n, red)) * recip(V.C.d[c]);
-    }
-    V.x[c] = v;
-  }
-}
-
-template <typename R>
-__device__ void tail_half(const LvlView<R> &V, int colour) {
-  auto xv = [&](int q) { return V.x[q]; };
-  for (int c = threadIdx.x; c < V.n; c += kTailBlock) {
-    int i, j, k;
-    V.ijk(c, i, j, k);
-    if (((i + j + k) & 1) != colour) continue;
-    const Nb n = nbrs(i, j, k, V.nx, V.ny, V.nz);
-    V.x[c] = (V.f[c] + offsum(V.C, n, xv)) * recip(V.C.d[c]);
-  }
-}
-
-// coarse right-hand side: fine residual summed over the 8 children
-template <typename R>
-__device__ void tail_restrict(const LvlView<R> &F, const LvlView<R> &Cv) {
-  auto xv = [&](int q) { return F.x[q]; };
-  for (int c = threadIdx.x; c < Cv.n; c += kTailBlock) {
-    int I, J, K;
-    Cv.ijk(c, I, J, K);
-    R acc = 0;
-    for (int cz = 0; cz < 2; ++cz)
-      for (int cy = 0; cy < 2; ++cy)
-        for (int cx = 0; cx < 2; ++cx) {
-          const Nb n = nbrs(2 * I + cx, 2 * J + cy, 2 * K + cz, F.nx, F.ny, F.nz);
-          acc += F.f[n.c] - (F.C.d[n.c] * F.x[n.c] - offsum(F.C, n, xv));
-        }
-    Cv.f[c] = acc;
-  }
-}
-
-// black half-sweep with the coarse-grid correction folded in (red
-// neighbours read as x + e(parent))
-template <typename R>
-__device__ void tail_prolong_black(const LvlView<R> &V, const LvlView<R> &Cv,
-                                   bool tri) {
-  for (int c = threadIdx.x; c < V.n; c += kTailBlock) {
-    int i, j, k;
-    V.ijk(c, i, j, k);
-    if (((i + j + k) & 1) != 1) continue;
-    const Nb n = nbrs(i, j, k, V.nx, V.ny, V.nz);
-    const int im = i == 0 ? V.nx - 1 : i - 1, ip = i == V.nx - 1 ? 0 : i + 1;
-    const int jm = j == 0 ? V.ny - 1 : j - 1, jp = j == V.ny - 1 ? 0 : j + 1;
-    const int km = k == 0 ? V.nz - 1 : k - 1, kp = k == V.nz - 1 ? 0 : k + 1;
-    auto par = [&](int a, int b2, int c2) {
-      return coarse_corr(Cv.x, a, b2, c2, Cv.nx, Cv.ny, Cv.nz, tri);
-    };
-    const R s = V.C.tx[c] * (V.x[n.xp] + par(ip, j, k)) +
-                V.C.tx[n.xm] * (V.x[n.xm] + par(im, j, k)) +
-                V.C.ty[c] * (V.x[n.yp] + par(i, jp, k)) +
-                V.C.ty[n.ym] * (V.x[n.ym] + par(i, jm, k)) +
-                V.C.tz[c] * (V.x[n.zp] + par(i, j, kp)) +
-                V.C.tz[n.zm] * (V.x[n.zm] + par(i, j, km));
-    V.x[c] = (V.f[c] + s) * recip(V.C.d[c]);
-  }
-}
-
-// coarsest level: Jacobi-preconditioned CG in FP64 to a relative residual of
-// 1e-12 (an effectively exact solve), scratch in P.cs
-template <typename R>
-__device__ void tail_coarse_solve(const Tables &T, const ProbDev &P, int p,
-                                  double *sh) {
-  const int lc = P.levels - 1;
-  const LevelDev L = T.lv[lc * T.nprob + p];
-  const int n = L.n, nx = L.nx, ny = L.ny, nz = L.nz;
-  double *xs = P.cs, *rs = P.cs + n, *ps = P.cs + 2 * n, *qs = P.cs + 3 * n;
-  const R *f = (const R *)L.f;
-  R *xo = (R *)L.x;
-  double acc = 0.0;
-  for (int c = threadIdx.x; c < n; c += kTailBlock) {
-    const double v = (double)f[c];
-    rs[c] = v;
-    xs[c] = 0.0;
-    acc += v * v;
-  }
-  const double bb = block_sum<kTailBlock / 64>(acc, sh);
-  double rz_old = 1.0;
-  if (bb > 0.0) {
-    for (int it = 0; it < 1000; ++it) {
-      acc = 0.0;
-      for (int c = threadIdx.x; c < n; c += kTailBlock) acc += rs[c] * rs[c] / L.diag[c];
-      const double rz = block_sum<kTailBlock / 64>(acc, sh);
-      const double beta = it == 0 ? 0.0 : rz / rz_old;
-      rz_old = rz;
-      for (int c = threadIdx.x; c < n; c += kTailBlock)
-        ps[c] = rs[c] / L.diag[c] + (it == 0 ? 0.0 : beta * ps[c]);
-      __syncthreads();
-      acc = 0.0;
-      for (int c = threadIdx.x; c < n; c += kTailBlock) {
-        const int i = c % nx, j = (c / nx) % ny, k = c / (nx * ny);
-        const Nb nb = nbrs(i, j, k, nx, ny, nz);
-        const double q = L.diag[c] * ps[c] -
-                         (L.Tx[c] * ps[nb.xp] + L.Tx[nb.xm] * ps[nb.xm] +
-                          L.Ty[c] * ps[nb.yp] + L.Ty[nb.ym] * ps[nb.ym] +
-                          L.Tz[c] * ps[nb.zp] + L.Tz[nb.zm] * ps[nb.zm]);
-        qs[c] = q;
-        acc += ps[c] * q;
-      }
-      const double pq = block_sum<kTailBlock / 64>(acc, sh);
-      const double alpha = rz / pq;
-      acc = 0.0;
-      for (int c = threadIdx.x; c < n; c += kTailBlock) {
-        xs[c] += alpha * ps[c];
-        const double r = rs[c] - alpha * qs[c];
-        rs[c] = r;
-        acc += r * r;
-      }
-      const double rr = block_sum<kTailBlock / 64>(acc, sh);
-      if (!(rr > 1e-24 * bb)) break;  // converged (or NaN: stop)
-    }
-  }
-  __syncthreads();
-  for (int c = threadIdx.x; c < n; c += kTailBlock) xo[c] = (R)xs[c];
-}
-
-template <typename R>
-__global__ __launch_bounds__(kTailBlock) void k_vtail(Tables T, int nu_pre,
-                                                     int nu_post, int trilinear) {
-  const int p = blockIdx.x;
-  const Scal &sc = T.sc[p];
-  const ProbDev P = T.pd[p];
-  if (!sc.active || P.levels < 2) return;
-  __shared__ double sh[kTailBlock / 64];
-  const int lt = P.tail, lc = P.levels - 1;
-  const bool tri = trilinear != 0;
-  for (int l = lt; l < lc; ++l) {
-    const LvlView<R> V = lvl_view<R>(T, l, p);
-    tail_pre0(V);
-    __syncthreads();
-    for (int s2 = 1; s2 < nu_pre; ++s2) {
-      tail_half(V, 0);
-      __syncthreads();
-      tail_half(V, 1);
-      __syncthreads();
-    }
-    tail_restrict(V, lvl_view<R>(T, l + 1, p));
-    __syncthreads();
-  }
-  tail_coarse_solve<R>(T, P, p, sh);
-  __syncthreads();
-  for (int l = lc - 1; l >= lt; --l) {
-    const LvlView<R> V = lvl_view<R>(T, l, p);
-    tail_prolong_black(V, lvl_view<R>(T, l + 1, p), tri);
-    __syncthreads();
-    tail_half(V, 0);
-    __syncthreads();
-    for (int s2 = 1; s2 < nu_post; ++s2) {
-      tail_half(V, 1);
-      __syncthreads();
-      tail_half(V, 0);
-      __syncthreads();
-    }
-  }
-}
-
-// ---------------------------------------------------------------------------
 // Krylov kernels (FP64, finest level; two x-consecutive cells per thread)
 // ---------------------------------------------------------------------------
 
@@ -1308,8 +1099,15 @@ __global__ __launch_bounds__(kBlock) void k_local(Tables T, TileList TL, int col
     dz += r[n.c] * (s * ((double)xn - (double)xo));
   }
   __shared__ double sh[kBlock / 64];
-  const double v = block_sum<kBlock / 64>(dz, sh);
-  if (threadIdx.x == 0) T.lpart[2 * tid + colour] = v;
+  const double w = wave_total(dz);
+  if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = w;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    double v = 0.0;
+#pragma unroll
+    for (int i = 0; i < kBlock / 64; ++i) v += sh[i];
+    T.lpart[2 * tid + colour] = v;
+  }
 }
 
 // Warm-started problems whose guess was dropped (by FIN_BB or FIN_WARM: it
@@ -1463,16 +1261,14 @@ __global__ __launch_bounds__(kFinBlock) void k_fin_bb(Tables T, int mixed) {
   __shared__ double sh[kAsmSums][NW];
 #pragma unroll
   for (int i = 0; i < kAsmSums; ++i) {
-    const double w = wave_sum(a[i]);
+    const double w = wave_total(a[i]);
     if ((threadIdx.x & 63) == 0) sh[i][threadIdx.x >> 6] = w;
   }
   __syncthreads();
+  if (threadIdx.x >= 64) return;
+#pragma unroll
+  for (int i = 0; i < kAsmSums; ++i) a[i] = row_total(sh[i][threadIdx.x & (NW - 1)]);
   if (threadIdx.x != 0) return;
-  for (int i = 0; i < kAsmSums; ++i) {
-    double v = 0.0;
-    for (int k = 0; k < NW; ++k) v += sh[i][k];
-    a[i] = v;
-  }
   const double bb = a[AS_BB];
   sc.bb = bb;
   sc.rr = bb;
@@ -1578,9 +1374,19 @@ __global__ __launch_bounds__(kFinBlock) void k_fin(Tables T, int which, int mixe
     a0 += T.part[2 * t];
     a1 += T.part[2 * t + 1];
   }
-  __shared__ double sh[kFinBlock / 64];
-  a0 = block_sum<kFinBlock / 64>(a0, sh);
-  a1 = block_sum<kFinBlock / 64>(a1, sh);
+  constexpr int NW = kFinBlock / 64;
+  __shared__ double sh[2][NW];
+  a0 = wave_total(a0);
+  a1 = wave_total(a1);
+  const int lane = threadIdx.x & 63;
+  if (lane == 0) {
+    sh[0][threadIdx.x >> 6] = a0;
+    sh[1][threadIdx.x >> 6] = a1;
+  }
+  __syncthreads();
+  if (threadIdx.x >= 64) return;
+  a0 = row_total(sh[0][lane & (NW - 1)]);
+  a1 = row_total(sh[1][lane & (NW - 1)]);
   if (threadIdx.x != 0) return;
   switch (which) {
     case FIN_RZ: {
@@ -1837,16 +1643,6 @@ void launch_prolong_black(const Tables &T, TileList L, int l, int prec,
     else LAUNCH(id, (k_prolong_black<double, false>), L.nblocks, kBlock, s, T, L, l, trilinear);
   }
 }
-
-void launch_vtail(const Tables &T, int prec, int nu_pre, int nu_post,
-                  int trilinear, hipStream_t s) {
-  if (!T.nprob) return;
-  if (prec)
-    LAUNCH(K_COARSE_SOLVE, (k_vtail<float>), T.nprob, kTailBlock, s, T, nu_pre, nu_post, trilinear);
-  else
-    LAUNCH(K_COARSE_SOLVE, (k_vtail<double>), T.nprob, kTailBlock, s, T, nu_pre, nu_post, trilinear);
-}
-
 
 void launch_spmv_f(const Tables &T, TileList F0, int km, hipStream_t s) {
   if (!F0.nblocks) return;

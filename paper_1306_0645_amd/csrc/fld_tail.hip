@@ -1,0 +1,622 @@
+// Tail of the V-cycle, one workgroup per problem: the coarsest level's
+// Jacobi-CG solve and, above it, the levels from P.tail down (each small):
+// pre-smoothing and restriction down to the coarsest level, the solve, then
+// prolongation and post-smoothing back up to P.tail, in the order of the
+// per-level path (red/black, red = even i+j+k).
+//
+// One workgroup on one CU is bound by latency: of a memory access, of a
+// barrier and of a reduction, each paid once per phase.  So everything a
+// thread needs is loaded at the start in one round of independent loads (its
+// cell's coefficients on every level, one cell per thread), the values that
+// cross threads live in LDS, reductions take one barrier (wave sums by DPP
+// row operations, then every wave sums the 16 wave results), and a coarsest
+// level of at most 64 cells is solved by one wave without any barrier.  The
+// CG carries r.z and ||r||^2 through one reduction and scales by the
+// approximate reciprocal of the diagonal (any fixed positive scaling leads to
+// the same solution; an exact division costs 16 times the instructions).
+// A coarsest level of up to 16 x 1024 cells (extents that stop halving early,
+// such as 25^3 under 200^3) keeps r, x and q in registers and p in LDS, and
+// streams the operator from the L2 in each iteration.  Measured per cycle
+// (before: every phase through memory, three reductions of two barriers each
+// per CG iteration, exact divisions): 8^3 and 4^3 levels of 64^3 and 256^3
+// 21.3 -> 8.0 us, of 256^3 in FP64 24.8 -> 10.0 us; one 4^3 level 8.1 ->
+// 2.8 us; 20^3 under 640^3 98 -> 48 us; 25^3 under 200^3 292 -> 146 us.
+#include "fld_device.h"
+
+namespace fld {
+
+constexpr int kTW = kTailBlock / 64;  // waves of the tail block
+
+// ---- one-barrier sums over the block ---------------------------------------
+
+// red: [2][N][kTW] doubles; slot alternates from call to call, so that a
+// call's writes never meet the reads of the call before
+template <int N>
+__device__ __forceinline__ void tail_sums(double (&v)[N], double *red, int &slot) {
+  double *s = red + slot * 2 * kTW;
+  slot ^= 1;
+  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+#pragma unroll
+  for (int i = 0; i < N; ++i) v[i] = wave_total(v[i]);
+  if (lane == 0) {
+#pragma unroll
+    for (int i = 0; i < N; ++i) s[i * kTW + w] = v[i];
+  }
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < N; ++i) v[i] = row_total(s[i * kTW + (lane & (kTW - 1))]);
+}
+
+// ---- coarsest solve ----------------------------------------------------------
+
+// operator of one cell: its six faces and diagonal, and the neighbours'
+// indices
+struct CgCell {
+  double xp, xm, yp, ym, zp, zm, d;
+  Nb n;
+};
+
+__device__ __forceinline__ void cg_load(CgCell &a, const LevelDev &L, int i, int j, int k) {
+  a.n = nbrs(i, j, k, L.nx, L.ny, L.nz);
+  a.xp = L.Tx[a.n.c];
+  a.xm = L.Tx[a.n.xm];
+  a.yp = L.Ty[a.n.c];
+  a.ym = L.Ty[a.n.ym];
+  a.zp = L.Tz[a.n.c];
+  a.zm = L.Tz[a.n.zm];
+  a.d = L.diag[a.n.c];
+}
+
+__device__ __forceinline__ void cg_load(CgCell &a, const LevelDev &L, int c) {
+  cg_load(a, L, c % L.nx, (c / L.nx) % L.ny, c / (L.nx * L.ny));
+}
+
+__device__ __forceinline__ double cg_row(const CgCell &a, const double *p) {
+  return a.d * p[a.n.c] - (a.xp * p[a.n.xp] + a.xm * p[a.n.xm] + a.yp * p[a.n.yp] +
+                           a.ym * p[a.n.ym] + a.zp * p[a.n.zp] + a.zm * p[a.n.zm]);
+}
+
+// Jacobi-preconditioned CG in FP64 to a relative residual of 1e-12 (an
+// effectively exact solve) on n cells, cell c = tid + u kTailBlock in slot u
+// of the thread; f: right-hand side, x: solution.  Every thread of the block
+// calls it.  WAVE: n <= 64, only wave 0 works and no barrier is taken.
+// HOLD: the operator (cell[u], loaded by the caller) and x stay in registers;
+// otherwise the operator is read in each iteration, two cells' loads at a
+// time (all 16 at once would spill), and x accumulates in xm (memory).
+template <int CPT, bool WAVE, bool HOLD>
+__device__ __forceinline__ void coarse_cg(const LevelDev &L, CgCell (&cell)[HOLD ? CPT : 1],
+                                          const double (&f)[CPT], double (&x)[HOLD ? CPT : 1],
+                                          double *xm, double *sp, double *red) {
+  const int n = L.n;
+  int slot = 0;
+  auto sums = [&](double (&v)[2]) {
+    if constexpr (WAVE) {
+      v[0] = wave_total(v[0]);
+      v[1] = wave_total(v[1]);
+    } else {
+      tail_sums<2>(v, red, slot);
+    }
+  };
+  // !HOLD: the thread's first cell, and the step of kTailBlock cells, in
+  // (x, y, z)
+  const int i0 = HOLD ? 0 : (int)threadIdx.x % L.nx, j0 = HOLD ? 0 : (int)threadIdx.x / L.nx % L.ny,
+            k0 = HOLD ? 0 : (int)threadIdx.x / (L.nx * L.ny);
+  const int di = HOLD ? 0 : kTailBlock % L.nx, dj = HOLD ? 0 : kTailBlock / L.nx % L.ny,
+            dk = HOLD ? 0 : kTailBlock / (L.nx * L.ny);
+  double r[CPT];
+  double a2[2] = {0.0, 0.0};  // ||r||^2, r.z
+#pragma unroll
+  for (int u = 0; u < CPT; ++u) {
+    const int c = threadIdx.x + u * kTailBlock;
+    if constexpr (HOLD) x[u] = 0.0;
+    r[u] = 0.0;
+    if (c < n) {
+      r[u] = f[u];
+      if constexpr (!HOLD) xm[c] = 0.0;
+      const double t = r[u] * __builtin_amdgcn_rcp(HOLD ? cell[HOLD ? u : 0].d : L.diag[c]);
+      sp[c] = t;
+      a2[0] += r[u] * r[u];
+      a2[1] += r[u] * t;
+    }
+    if constexpr (!HOLD) {
+      if ((u & 3) == 3) asm volatile("" ::: "memory");
+    }
+  }
+  sums(a2);
+  const double bb = a2[0];
+  double rz = a2[1];
+  if (!(bb > 0.0)) return;
+  for (int it = 0; it < 1000; ++it) {
+    // (the sums above or below ended with a barrier: p is complete)
+    double q[CPT];
+    double a1[2] = {0.0, 0.0};
+    int i = i0, j = j0, k = k0;
+    // (the coordinates are opaque to the compiler: it would otherwise keep
+    // every cell's addresses across the iterations, and spill them)
+    if constexpr (!HOLD) asm volatile("" : "+v"(i), "+v"(j), "+v"(k));
+#pragma unroll
+    for (int u = 0; u < CPT; ++u) {
+      const int c = threadIdx.x + u * kTailBlock;
+      q[u] = 0.0;
+      if (c < n) {
+        if constexpr (HOLD) {
+          q[u] = cg_row(cell[u], sp);
+        } else {
+          CgCell a;
+          cg_load(a, L, i, j, k);
+          q[u] = cg_row(a, sp);
+        }
+        a1[0] += sp[c] * q[u];
+      }
+      if constexpr (!HOLD) {
+        if (u & 1) asm volatile("" ::: "memory");
+        i += di;
+        j += dj;
+        k += dk;
+        if (i >= L.nx) {
+          i -= L.nx;
+          ++j;
+        }
+        if (j >= L.ny) {
+          j -= L.ny;
+          ++k;
+        }
+      }
+    }
+    if constexpr (WAVE) {
+      a1[0] = wave_total(a1[0]);
+    } else {
+      double b1[1] = {a1[0]};
+      tail_sums<1>(b1, red, slot);
+      a1[0] = b1[0];
+    }
+    const double alpha = rz / a1[0];
+    double rd[CPT];
+    a2[0] = a2[1] = 0.0;
+    int c0 = threadIdx.x;
+    if constexpr (!HOLD) asm volatile("" : "+v"(c0));
+#pragma unroll
+    for (int u = 0; u < CPT; ++u) {
+      const int c = c0 + u * kTailBlock;
+      rd[u] = 0.0;
+      if (c < n) {
+        if constexpr (HOLD) x[u] += alpha * sp[c];
+        else xm[c] += alpha * sp[c];
+        r[u] -= alpha * q[u];
+        rd[u] = r[u] * __builtin_amdgcn_rcp(HOLD ? cell[HOLD ? u : 0].d : L.diag[c]);
+        a2[0] += r[u] * r[u];
+        a2[1] += r[u] * rd[u];
+      }
+      if constexpr (!HOLD) {
+        if ((u & 3) == 3) asm volatile("" ::: "memory");
+      }
+    }
+    sums(a2);
+    if (!(a2[0] > 1e-24 * bb)) break;  // converged (or NaN: stop)
+    const double beta = a2[1] / rz;
+    rz = a2[1];
+#pragma unroll
+    for (int u = 0; u < CPT; ++u) {
+      const int c = threadIdx.x + u * kTailBlock;
+      if (c < n) sp[c] = rd[u] + beta * sp[c];
+    }
+    if constexpr (!WAVE) __syncthreads();
+  }
+}
+
+// ---- smoothing levels, one cell per thread, in LDS ---------------------------
+
+template <typename R>
+struct TailCell {
+  R xp, xm, yp, ym, zp, zm, id;  // faces; 1 / diagonal
+  R d;
+  Nb n;
+  int i, j, k;
+  bool on, red;
+};
+
+template <typename R>
+__device__ __forceinline__ void tail_load(TailCell<R> &a, const LevelDev &L) {
+  const Coef<R> C = coefs<R>(L);
+  const int c = threadIdx.x;
+  a.on = c < L.n;
+  a.red = false;
+  if (!a.on) return;
+  a.i = c % L.nx;
+  a.j = (c / L.nx) % L.ny;
+  a.k = c / (L.nx * L.ny);
+  a.n = nbrs(a.i, a.j, a.k, L.nx, L.ny, L.nz);
+  a.red = ((a.i + a.j + a.k) & 1) == 0;
+  a.xp = C.tx[a.n.c];
+  a.xm = C.tx[a.n.xm];
+  a.yp = C.ty[a.n.c];
+  a.ym = C.ty[a.n.ym];
+  a.zp = C.tz[a.n.c];
+  a.zm = C.tz[a.n.zm];
+  a.d = C.d[a.n.c];
+}
+
+template <typename R, typename U>
+__device__ __forceinline__ R tail_off(const TailCell<R> &a, const U &u) {
+  return a.xp * u(a.n.xp) + a.xm * u(a.n.xm) + a.yp * u(a.n.yp) + a.ym * u(a.n.ym) +
+         a.zp * u(a.n.zp) + a.zm * u(a.n.zm);
+}
+
+template <typename R>
+__device__ __forceinline__ void tail_half(const TailCell<R> &a, R f, R *x, bool red) {
+  auto xv = [&](int q) { return x[q]; };
+  if (a.on && a.red == red) x[a.n.c] = (f + tail_off(a, xv)) * a.id;
+  __syncthreads();
+}
+
+// nu sweeps from x = 0 (the first red half is f / d), then the residual into
+// rs, and the coarse right-hand side of coarse cell tid (of LC): the 8
+// children's residuals
+template <typename R>
+__device__ __forceinline__ R tail_down(TailCell<R> &a, R f, int nu, R *x, R *rs,
+                                       const LevelDev &LF, const LevelDev &LC) {
+  if (a.on) {
+    a.id = recip(a.d);
+    if (a.red) x[a.n.c] = f * a.id;
+  }
+  __syncthreads();
+  tail_half(a, f, x, false);
+  for (int s = 1; s < nu; ++s) {
+    tail_half(a, f, x, true);
+    tail_half(a, f, x, false);
+  }
+  auto xv = [&](int q) { return x[q]; };
+  if (a.on) rs[a.n.c] = f - (a.d * x[a.n.c] - tail_off(a, xv));
+  __syncthreads();
+  R acc = 0;
+  const int c = threadIdx.x;
+  if (c < LC.n) {
+    const int I = c % LC.nx, J = (c / LC.nx) % LC.ny, K = c / (LC.nx * LC.ny);
+#pragma unroll
+    for (int cz = 0; cz < 2; ++cz)
+#pragma unroll
+      for (int cy = 0; cy < 2; ++cy)
+#pragma unroll
+        for (int cx = 0; cx < 2; ++cx)
+          acc += rs[((2 * K + cz) * LF.ny + 2 * J + cy) * LF.nx + 2 * I + cx];
+  }
+  __syncthreads();
+  return acc;
+}
+
+// the correction e of the coarse level, folded into the first black half;
+// then the rest of nu sweeps (black, red)
+template <typename R>
+__device__ __forceinline__ void tail_up(const TailCell<R> &a, R f, int nu, R *x, const R *e,
+                                        const LevelDev &LF, const LevelDev &LC, bool tri) {
+  if (a.on && !a.red) {
+    const int nx = LF.nx, ny = LF.ny, nz = LF.nz, i = a.i, j = a.j, k = a.k;
+    auto par = [&](int g, int b2, int c2) {
+      return coarse_corr(e, g, b2, c2, LC.nx, LC.ny, LC.nz, tri);
+    };
+    const int im = i == 0 ? nx - 1 : i - 1, ip = i == nx - 1 ? 0 : i + 1;
+    const int jm = j == 0 ? ny - 1 : j - 1, jp = j == ny - 1 ? 0 : j + 1;
+    const int km = k == 0 ? nz - 1 : k - 1, kp = k == nz - 1 ? 0 : k + 1;
+    const R s = a.xp * (x[a.n.xp] + par(ip, j, k)) + a.xm * (x[a.n.xm] + par(im, j, k)) +
+                a.yp * (x[a.n.yp] + par(i, jp, k)) + a.ym * (x[a.n.ym] + par(i, jm, k)) +
+                a.zp * (x[a.n.zp] + par(i, j, kp)) + a.zm * (x[a.n.zm] + par(i, j, km));
+    x[a.n.c] = (f + s) * a.id;
+  }
+  __syncthreads();
+  tail_half(a, f, x, true);
+  for (int s = 1; s < nu; ++s) {
+    tail_half(a, f, x, false);
+    tail_half(a, f, x, true);
+  }
+}
+
+// ---- smoothing levels through memory (more than kTailBlock cells) ------------
+
+template <typename R>
+struct LvlView {
+  int nx, ny, nz, n;
+  Coef<R> C;
+  R *x, *f;
+  __device__ __forceinline__ void ijk(int c, int &i, int &j, int &k) const {
+    i = c % nx;
+    j = (c / nx) % ny;
+    k = c / (nx * ny);
+  }
+};
+
+template <typename R>
+__device__ __forceinline__ LvlView<R> lvl_view(const Tables &T, int l, int p) {
+  const LevelDev L = T.lv[l * T.nprob + p];
+  LvlView<R> v;
+  v.nx = L.nx;
+  v.ny = L.ny;
+  v.nz = L.nz;
+  v.n = L.n;
+  v.C = coefs<R>(L);
+  v.x = (R *)L.x;
+  v.f = (R *)L.f;
+  return v;
+}
+
+// first pre-sweep from x = 0 (red x = f/d, black from those red values)
+template <typename R>
+__device__ void mem_pre0(const LvlView<R> &V) {
+  for (int c = threadIdx.x; c < V.n; c += kTailBlock) {
+    int i, j, k;
+    V.ijk(c, i, j, k);
+    const Nb n = nbrs(i, j, k, V.nx, V.ny, V.nz);
+    R v;
+    if (((i + j + k) & 1) == 0) {
+      v = V.f[c] * recip(V.C.d[c]);
+    } else {
+      auto red = [&](int q) { return V.f[q] * recip(V.C.d[q]); };
+      v = (V.f[c] + offsum(V.C, n, red)) * recip(V.C.d[c]);
+    }
+    V.x[c] = v;
+  }
+}
+
+template <typename R>
+__device__ void mem_half(const LvlView<R> &V, int colour) {
+  auto xv = [&](int q) { return V.x[q]; };
+  for (int c = threadIdx.x; c < V.n; c += kTailBlock) {
+    int i, j, k;
+    V.ijk(c, i, j, k);
+    if (((i + j + k) & 1) != colour) continue;
+    const Nb n = nbrs(i, j, k, V.nx, V.ny, V.nz);
+    V.x[c] = (V.f[c] + offsum(V.C, n, xv)) * recip(V.C.d[c]);
+  }
+}
+
+// coarse right-hand side: fine residual summed over the 8 children
+template <typename R>
+__device__ void mem_restrict(const LvlView<R> &F, const LvlView<R> &Cv) {
+  auto xv = [&](int q) { return F.x[q]; };
+  for (int c = threadIdx.x; c < Cv.n; c += kTailBlock) {
+    int I, J, K;
+    Cv.ijk(c, I, J, K);
+    R acc = 0;
+    for (int cz = 0; cz < 2; ++cz)
+      for (int cy = 0; cy < 2; ++cy)
+        for (int cx = 0; cx < 2; ++cx) {
+          const Nb n = nbrs(2 * I + cx, 2 * J + cy, 2 * K + cz, F.nx, F.ny, F.nz);
+          acc += F.f[n.c] - (F.C.d[n.c] * F.x[n.c] - offsum(F.C, n, xv));
+        }
+    Cv.f[c] = acc;
+  }
+}
+
+// black half-sweep with the coarse-grid correction folded in (red
+// neighbours read as x + e(parent))
+template <typename R>
+__device__ void mem_prolong_black(const LvlView<R> &V, const LvlView<R> &Cv, bool tri) {
+  for (int c = threadIdx.x; c < V.n; c += kTailBlock) {
+    int i, j, k;
+    V.ijk(c, i, j, k);
+    if (((i + j + k) & 1) != 1) continue;
+    const Nb n = nbrs(i, j, k, V.nx, V.ny, V.nz);
+    const int im = i == 0 ? V.nx - 1 : i - 1, ip = i == V.nx - 1 ? 0 : i + 1;
+    const int jm = j == 0 ? V.ny - 1 : j - 1, jp = j == V.ny - 1 ? 0 : j + 1;
+    const int km = k == 0 ? V.nz - 1 : k - 1, kp = k == V.nz - 1 ? 0 : k + 1;
+    auto par = [&](int a, int b2, int c2) {
+      return coarse_corr(Cv.x, a, b2, c2, Cv.nx, Cv.ny, Cv.nz, tri);
+    };
+    const R s = V.C.tx[c] * (V.x[n.xp] + par(ip, j, k)) +
+                V.C.tx[n.xm] * (V.x[n.xm] + par(im, j, k)) +
+                V.C.ty[c] * (V.x[n.yp] + par(i, jp, k)) +
+                V.C.ty[n.ym] * (V.x[n.ym] + par(i, jm, k)) +
+                V.C.tz[c] * (V.x[n.zp] + par(i, j, kp)) +
+                V.C.tz[n.zm] * (V.x[n.zm] + par(i, j, km));
+    V.x[c] = (V.f[c] + s) * recip(V.C.d[c]);
+  }
+}
+
+// the same CG for a coarsest level beyond the register path, its vectors in
+// P.cs
+template <typename R>
+__device__ void mem_coarse_solve(const LevelDev &L, const ProbDev &P, double *red) {
+  const int n = L.n, nx = L.nx, ny = L.ny, nz = L.nz;
+  double *xs = P.cs, *rs = P.cs + n, *ps = P.cs + 2 * n, *qs = P.cs + 3 * n;
+  const R *f = (const R *)L.f;
+  R *xo = (R *)L.x;
+  int slot = 0;
+  double a2[2] = {0.0, 0.0};
+  for (int c = threadIdx.x; c < n; c += kTailBlock) {
+    const double v = (double)f[c], t = v * __builtin_amdgcn_rcp(L.diag[c]);
+    rs[c] = v;
+    xs[c] = 0.0;
+    ps[c] = t;
+    a2[0] += v * v;
+    a2[1] += v * t;
+  }
+  tail_sums<2>(a2, red, slot);
+  const double bb = a2[0];
+  double rz = a2[1];
+  if (bb > 0.0) {
+    for (int it = 0; it < 1000; ++it) {
+      __syncthreads();
+      double a1[1] = {0.0};
+      for (int c = threadIdx.x; c < n; c += kTailBlock) {
+        const int i = c % nx, j = (c / nx) % ny, k = c / (nx * ny);
+        const Nb nb = nbrs(i, j, k, nx, ny, nz);
+        const double q = L.diag[c] * ps[c] -
+                         (L.Tx[c] * ps[nb.xp] + L.Tx[nb.xm] * ps[nb.xm] +
+                          L.Ty[c] * ps[nb.yp] + L.Ty[nb.ym] * ps[nb.ym] +
+                          L.Tz[c] * ps[nb.zp] + L.Tz[nb.zm] * ps[nb.zm]);
+        qs[c] = q;
+        a1[0] += ps[c] * q;
+      }
+      tail_sums<1>(a1, red, slot);
+      const double alpha = rz / a1[0];
+      a2[0] = a2[1] = 0.0;
+      for (int c = threadIdx.x; c < n; c += kTailBlock) {
+        xs[c] += alpha * ps[c];
+        const double r = rs[c] - alpha * qs[c];
+        rs[c] = r;
+        a2[0] += r * r;
+        a2[1] += r * (r * __builtin_amdgcn_rcp(L.diag[c]));
+      }
+      tail_sums<2>(a2, red, slot);
+      if (!(a2[0] > 1e-24 * bb)) break;  // converged (or NaN: stop)
+      const double beta = a2[1] / rz;
+      rz = a2[1];
+      for (int c = threadIdx.x; c < n; c += kTailBlock)
+        ps[c] = rs[c] * __builtin_amdgcn_rcp(L.diag[c]) + beta * ps[c];
+    }
+  }
+  for (int c = threadIdx.x; c < n; c += kTailBlock) xo[c] = (R)xs[c];
+}
+
+// CG over CPT cells per thread, right-hand side and solution in memory
+template <typename R, int CPT, bool HOLD>
+__device__ __forceinline__ void level_cg(const LevelDev &L, double *xm, double *sp,
+                                         double *red) {
+  CgCell cell[HOLD ? CPT : 1];
+  double f[CPT], x[HOLD ? CPT : 1];
+#pragma unroll
+  for (int u = 0; u < CPT; ++u) {
+    const int c = threadIdx.x + u * kTailBlock;
+    f[u] = 0.0;
+    if (c < L.n) {
+      f[u] = (double)((const R *)L.f)[c];
+      if constexpr (HOLD) cg_load(cell[u], L, c);
+    }
+  }
+  coarse_cg<CPT, false, HOLD>(L, cell, f, x, xm, sp, red);
+#pragma unroll
+  for (int u = 0; u < CPT; ++u) {
+    const int c = threadIdx.x + u * kTailBlock;
+    if (c < L.n) ((R *)L.x)[c] = (R)(HOLD ? x[HOLD ? u : 0] : xm[c]);
+  }
+}
+
+// cells of a coarsest level solved from registers and LDS, by LDS size
+constexpr int kTailSmall = 2 * kTailBlock, kTailBig = 16 * kTailBlock;
+
+template <typename R, int CAP>
+__global__ __launch_bounds__(kTailBlock) void k_vtail(Tables T, int nu_pre,
+                                                     int nu_post, int trilinear) {
+  const int p = blockIdx.x;
+  const Scal &sc = T.sc[p];
+  const ProbDev &P = T.pd[p];
+  const int levels = P.levels, lt = P.tail, lc = levels - 1;
+  if (!sc.active || levels < 2) return;
+  __shared__ double sp[CAP];
+  __shared__ double red[2 * 2 * kTW];
+  // (each level has an eighth of the cells of the one above)
+  __shared__ R xa[kTailBlock], xb[kTailBlock / 8], xc[kTailBlock / 64], rs[kTailBlock];
+  const bool tri = trilinear != 0;
+  const int ns = lc - lt;  // smoothing levels of the tail
+  const LevelDev L0 = T.lv[lt * T.nprob + p];
+  if (ns >= 1 && ns <= 2 && L0.n <= kTailBlock) {
+    // one cell per thread on every level, values in LDS.  Every load of the
+    // pass is issued here
+    const LevelDev L1 = T.lv[(lt + 1) * T.nprob + p];
+    const LevelDev L2 = T.lv[lc * T.nprob + p];
+    const int c = threadIdx.x;
+    TailCell<R> a, b;
+    CgCell cell[1];
+    tail_load(a, L0);
+    b.on = b.red = false;
+    if (ns == 2) tail_load(b, L1);
+    if (c < L2.n) cg_load(cell[0], L2, c);
+    R fa = 0, fb = 0, fcg;
+    if (a.on) fa = ((const R *)L0.f)[c];
+    fcg = tail_down(a, fa, nu_pre, xa, rs, L0, L1);
+    if (ns == 2) {
+      fb = fcg;
+      fcg = tail_down(b, fb, nu_pre, xb, rs, L1, L2);
+    }
+    const double f[1] = {c < L2.n ? (double)fcg : 0.0};
+    double x[1] = {0.0};
+    if (L2.n <= 64) {
+      if (c < 64) coarse_cg<1, true, true>(L2, cell, f, x, nullptr, sp, red);
+    } else {
+      coarse_cg<1, false, true>(L2, cell, f, x, nullptr, sp, red);
+    }
+    R *xl = ns == 2 ? xc : xb;
+    if (c < L2.n) xl[c] = (R)x[0];
+    __syncthreads();
+    if (ns == 2) tail_up(b, fb, nu_post, xb, xc, L1, L2, tri);
+    tail_up(a, fa, nu_post, xa, xb, L0, L1, tri);
+    if (a.on) ((R *)L0.x)[c] = xa[c];
+    return;
+  }
+  for (int l = lt; l < lc; ++l) {
+    const LvlView<R> V = lvl_view<R>(T, l, p);
+    mem_pre0(V);
+    __syncthreads();
+    for (int s2 = 1; s2 < nu_pre; ++s2) {
+      mem_half(V, 0);
+      __syncthreads();
+      mem_half(V, 1);
+      __syncthreads();
+    }
+    mem_restrict(V, lvl_view<R>(T, l + 1, p));
+    __syncthreads();
+  }
+  const LevelDev LC = T.lv[lc * T.nprob + p];
+  if (LC.n <= kTailBlock) {
+    if (LC.n <= 64) {
+      if (threadIdx.x < 64) {
+        CgCell cell[1];
+        const int c = threadIdx.x;
+        double f[1] = {0.0}, x[1];
+        if (c < LC.n) {
+          f[0] = (double)((const R *)LC.f)[c];
+          cg_load(cell[0], LC, c);
+        }
+        coarse_cg<1, true, true>(LC, cell, f, x, nullptr, sp, red);
+        if (c < LC.n) ((R *)LC.x)[c] = (R)x[0];
+      }
+    } else {
+      level_cg<R, 1, true>(LC, P.cs, sp, red);
+    }
+  } else if (LC.n <= 2 * kTailBlock) {
+    level_cg<R, 2, true>(LC, P.cs, sp, red);
+  } else if (CAP >= kTailBig && LC.n <= 4 * kTailBlock) {
+    if constexpr (CAP >= kTailBig) level_cg<R, 4, false>(LC, P.cs, sp, red);
+  } else if (CAP >= kTailBig && LC.n <= 8 * kTailBlock) {
+    if constexpr (CAP >= kTailBig) level_cg<R, 8, false>(LC, P.cs, sp, red);
+  } else if (CAP >= kTailBig && LC.n <= kTailBig) {
+    if constexpr (CAP >= kTailBig) level_cg<R, 16, false>(LC, P.cs, sp, red);
+  } else {
+    mem_coarse_solve<R>(LC, P, red);
+  }
+  __syncthreads();
+  for (int l = lc - 1; l >= lt; --l) {
+    const LvlView<R> V = lvl_view<R>(T, l, p);
+    mem_prolong_black(V, lvl_view<R>(T, l + 1, p), tri);
+    __syncthreads();
+    mem_half(V, 0);
+    __syncthreads();
+    for (int s2 = 1; s2 < nu_post; ++s2) {
+      mem_half(V, 1);
+      __syncthreads();
+      mem_half(V, 0);
+      __syncthreads();
+    }
+  }
+}
+
+void launch_vtail(const Tables &T, int prec, int nu_pre, int nu_post, int trilinear,
+                  int big, hipStream_t s) {
+  if (!T.nprob) return;
+  if (prec) {
+    if (big)
+      FLD_LAUNCH(K_COARSE_SOLVE, (k_vtail<float, kTailBig>), T.nprob, kTailBlock, s, T,
+                 nu_pre, nu_post, trilinear);
+    else
+      FLD_LAUNCH(K_COARSE_SOLVE, (k_vtail<float, kTailSmall>), T.nprob, kTailBlock, s, T,
+                 nu_pre, nu_post, trilinear);
+  } else {
+    if (big)
+      FLD_LAUNCH(K_COARSE_SOLVE, (k_vtail<double, kTailBig>), T.nprob, kTailBlock, s, T,
+                 nu_pre, nu_post, trilinear);
+    else
+      FLD_LAUNCH(K_COARSE_SOLVE, (k_vtail<double, kTailSmall>), T.nprob, kTailBlock, s, T,
+                 nu_pre, nu_post, trilinear);
+  }
+}
+
+}  // namespace fld
