@@ -157,12 +157,14 @@ typedef struct fld_params {
                           level: measured at 256^3, 2680 against 2652
                           Mcell-updates/s with 0 and 2658 with 4096) */
   int32_t smoother;    /* fld_smoother; default FLD_SMOOTH_RBGS */
-  int32_t fused_levels;/* under V(1,1) red/black: the finest fused_levels
-                          levels run the two fused passes (coarse ones with
-                          4-plane tiles); 0 = automatic (the finest level, and
-                          each coarser one that still holds at least 2^20
-                          cells; decided per problem, so that a problem's
-                          result does not depend on its batch) */
+  int32_t fused_levels;/* under V(1,1) red/black every level above the tail runs
+                          two fused passes: the finest fused_levels levels on
+                          tiles marched through their planes, the others box
+                          by box; 0 = automatic (marching tiles on a level of
+                          at least 1.5 x 2^20 cells; decided per problem, so
+                          that a problem's result does not depend on its
+                          batch).  fused_tile_z > 0 keeps the finest level on
+                          marching tiles */
   int32_t coarse_op;   /* coarse face coefficients: 0 = coarse_scale times the
                           sum of the 4 fine faces the coarse face covers; 1 =
                           2 coarse_scale times the sum over the 4 fine rows

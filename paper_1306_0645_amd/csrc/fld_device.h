@@ -6,6 +6,8 @@
 
 #include <math.h>
 
+#include <type_traits>
+
 #include "fld_internal.h"
 
 namespace fld {
@@ -50,7 +52,7 @@ __device__ __forceinline__ int get_tile_index(const TileList &L) {
 }
 
 // Thread -> cells: a thread owns the column (i, j) of the tile and walks its
-// planes (the tables give every tile cpt = 1 cell per thread along x).
+// planes.
 struct Col {
   int i, j;
   bool on;
@@ -58,9 +60,8 @@ struct Col {
 
 __device__ __forceinline__ Col tile_col(const Tile &t) {
   Col c;
-  const int tpr = t.tx / t.cpt;
-  const int lx = threadIdx.x % tpr, ly = threadIdx.x / tpr;
-  c.i = t.x0 + lx * t.cpt;
+  const int lx = threadIdx.x % t.tx, ly = threadIdx.x / t.tx;
+  c.i = t.x0 + lx;
   c.j = t.y0 + ly;
   c.on = ly < t.ty;
   return c;
@@ -195,9 +196,19 @@ __device__ __forceinline__ float recip(float d) {
 
 template <typename R, bool L0>
 struct FSrc {
+  using FT = std::conditional_t<L0, double, R>;
   const R *f;
   const double *r;
   double inv_s;
+  // the value as stored, and scaled to the cycle's units
+  __device__ __forceinline__ FT raw(int c) const {
+    if constexpr (L0) return r[c];
+    else return f[c];
+  }
+  __device__ __forceinline__ R scaled(FT v, double is) const {
+    if constexpr (L0) return (R)(v * is);
+    else return v;
+  }
   __device__ __forceinline__ R operator()(int c) const {
     if constexpr (L0) return (R)(r[c] * inv_s);
     else return f[c];

@@ -17,6 +17,7 @@ int hip_ok(hipError_t e) { return e == hipSuccess ? ST_OK : ST_EDEVICE; }
     if ((expr) != hipSuccess) return ST_EDEVICE; \
   } while (0)
 
+
 static bool finite_pos(double v) { return std::isfinite(v) && v > 0.0; }
 
 bool grid_ok(const fld_grid &g) {
@@ -53,11 +54,43 @@ bool params_ok(const fld_params &p) {
   return true;
 }
 
+// Whether the one-sweep cycle runs level l (cells cells) box by box instead of
+// marching through planes: a level that does not fill the GPU with marching
+// tiles.  A property of the problem alone, so that its result does not depend
+// on the company it is solved in.  The line lies at 1.5 x 2^20 cells: measured
+// (us for three steps, boxes / marching tiles on the finest level), mixed 64^3
+// 3640 / 4160 (four steps with chemistry), 96^3 1688 / 1726, 112^3 2409 / 2525,
+// 128^3 2908 / 2655; FP64 96^3 1597 / 1808, 128^3 2813 / 2692.  An explicit
+// fused_levels or (finest level) fused_tile_z asks for marching tiles.
+constexpr long long kBoxCells = 3LL << 19;
+static bool box_level(const fld_params &p, int l, long long cells) {
+  if (p.fused_levels > 0) return l >= p.fused_levels;
+  if (l == 0) return p.fused_tile_z == 0 && cells < kBoxCells;
+  return cells < kBoxCells;
+}
+
+// Box of a box pass: up to 16 x 8 x 4 cells, halved while that leaves fewer
+// than 256 boxes (one per CU), down to 8 x 4 x 4.
+void box_shape(int nx, int ny, int nz, int &tx, int &ty, int &tz) {
+  tx = kBoxX;
+  ty = kBoxY;
+  tz = kBoxZ;
+  auto count = [&] {
+    return (long long)((nx + tx - 1) / tx) * ((ny + ty - 1) / ty) * ((nz + tz - 1) / tz);
+  };
+  if (count() < 256) tx = 8;
+  if (count() < 256) ty = 4;
+  tx = std::min(tx, nx);
+  ty = std::min(ty, ny);
+  tz = std::min(tz, nz);
+}
+
 // Full 2x coarsening while every extent stays even.  Automatic depth stops
 // once an extent would drop below 4; an explicit depth allows extents >= 2.
 Hier make_hier(const fld_grid &g, const fld_params &p) {
   Hier h;
   h.levels = 1;
+  h.local = p.precision == FLD_PREC_MIXED && p.local_sweeps > 0;
   h.n[0][0] = g.nx;
   h.n[0][1] = g.ny;
   h.n[0][2] = g.nz;
@@ -70,10 +103,6 @@ Hier make_hier(const fld_grid &g, const fld_params &p) {
     for (int d = 0; d < 3; ++d) h.n[h.levels][d] = c[d] / 2;
     ++h.levels;
   }
-  for (int l = 0; l < h.levels; ++l) {
-    h.tiles[l] = count_tiles(p, h.n[l][0], h.n[l][1], h.n[l][2]);
-    h.ftiles[l] = count_fused_tiles(p, l, h.n[l][0], h.n[l][1], h.n[l][2]);
-  }
   // the tail: the coarsest level, and above it every level below the finest
   // with at most tail_cells cells
   h.tail = h.levels > 1 ? h.levels - 1 : 1;
@@ -81,6 +110,16 @@ Hier make_hier(const fld_grid &g, const fld_params &p) {
   // it keeps to the coarsest level)
   const long long tc = p.smoother == FLD_SMOOTH_JACOBI ? 0 : p.tail_cells;
   while (h.tail > 1 && h.cells(h.tail - 1) <= tc) --h.tail;
+  for (int l = 0; l < h.levels; ++l) {
+    h.tiles[l] = count_tiles(p, h.n[l][0], h.n[l][1], h.n[l][2]);
+    h.box[l] = box_level(p, l, h.cells(l));
+    if (l >= h.tail) continue;  // (no pass of its own)
+    int tx, ty, tz;
+    if (h.box[l]) box_shape(h.n[l][0], h.n[l][1], h.n[l][2], tx, ty, tz);
+    else fused_shape(p, l, h.n[l][0], h.n[l][1], h.n[l][2], tx, ty, tz);
+    h.ftiles[l] = ((h.n[l][0] + tx - 1) / tx) * ((h.n[l][1] + ty - 1) / ty) *
+                  ((h.n[l][2] + tz - 1) / tz);
+  }
   return h;
 }
 
@@ -134,7 +173,7 @@ int count_fused_tiles(const fld_params &p, int l, int nx, int ny, int nz) {
 // gives 2048 tiles; a smaller problem keeps the 64 x 4 tiles, whose one cell
 // per thread and plane leaves more workgroups to hide latency.  A property of
 // the problem alone, as the partial sums' order must be.
-bool spmv_on_fused(const Hier &h) { return h.ftiles[0] >= 2048; }
+bool spmv_on_fused(const Hier &h) { return !h.box[0] && h.ftiles[0] >= 2048; }
 
 bool fused_cycle(const fld_params &p) {
   return p.smoother == FLD_SMOOTH_RBGS && p.nu_pre == 1 && p.nu_post == 1;
@@ -251,10 +290,13 @@ size_t problem_bytes(const Hier &h, const fld_params &p) {
 static size_t tables_layout(Carver &cv, const std::vector<Hier> &hs,
                             Engine *e) {
   const int np = (int)hs.size();
-  size_t ntiles = 0, nfine = 0, nranges = 0;
+  size_t ntiles = 0, nfine = 0, nstd = 0, nranges = 0;
+  bool local = false;
   for (const Hier &h : hs) {
     for (int l = 0; l < h.levels; ++l) ntiles += h.tiles[l] + h.ftiles[l];
     nfine += h.tiles[0] + h.ftiles[0];  // partial slots: both finest tilings
+    nstd += h.tiles[0];                 // (the standard tiles come first)
+    local = local || h.local;
   }
   // fine, the two SpMV lists and kListsPerLevel lists per level: at most
   // one range per problem and list, 2 ints each, kListSlots sets
@@ -264,9 +306,9 @@ static size_t tables_layout(Carver &cv, const std::vector<Hier> &hs,
   StepDev *sd = cv.take<StepDev>(np);
   Scal *sc = cv.take<Scal>(np);
   double *part = cv.take<double>(2 * std::max<size_t>(nfine, 1));
-  double *lpart = cv.take<double>(2 * std::max<size_t>(nfine, 1));
+  double *lpart = cv.take<double>(local ? 2 * std::max<size_t>(nstd, 1) : 0);
   CtlDev *ctl = cv.take<CtlDev>(std::max(np, 1));
-  double *gpart = cv.take<double>(kAsmSums * std::max<size_t>(nfine, 1));
+  double *gpart = cv.take<double>(kAsmSums * std::max<size_t>(nstd, 1));
   Tile *tiles = cv.take<Tile>(std::max<size_t>(ntiles, 1));
   int *ranges = cv.take<int>(nranges);
   if (e) {
@@ -340,19 +382,6 @@ int Engine::setup(const fld_params &p, hipStream_t s,
   // (their indices are the partial-sum slots)
   fused = fused_cycle(p);
   lazy = lazy_iteration(p);
-  // levels of each problem run by the fused passes: the finest, then each
-  // coarser one of the problem that still holds 2^20 cells (or fused_levels
-  // of them); a property of the problem alone, so that its result does not
-  // depend on the company it is solved in
-  ftop.assign(np, 1);
-  for (int i = 0; i < np; ++i) {
-    if (p.fused_levels > 0) {
-      ftop[i] = std::min(p.fused_levels, hier[i].levels);
-    } else {
-      for (int l = 1; l < hier[i].levels && hier[i].cells(l) >= (1LL << 20); ++l)
-        ftop[i] = l + 1;
-    }
-  }
   h_tiles.clear();
   tbeg.assign((size_t)np * kMaxLevels, 0);
   fbeg.assign((size_t)np * kMaxLevels, 0);
@@ -368,7 +397,6 @@ int Engine::setup(const fld_params &p, hipStream_t s,
           t.tx = std::min(tx, nx - x0);
           t.ty = std::min(ty, ny - y0);
           t.tz = std::min(tz, nz - z0);
-          t.cpt = 1;
           h_tiles.push_back(t);
         }
   };
@@ -384,9 +412,11 @@ int Engine::setup(const fld_params &p, hipStream_t s,
     for (int i = 0; i < np; ++i) {
       if (l >= hier[i].levels) continue;
       fbeg[(size_t)i * kMaxLevels + l] = (int)h_tiles.size();
+      if (!hier[i].ftiles[l]) continue;
       const int nx = hier[i].n[l][0], ny = hier[i].n[l][1], nz = hier[i].n[l][2];
       int tx, ty, tz;
-      fused_shape(prm, l, nx, ny, nz, tx, ty, tz);
+      if (hier[i].box[l]) box_shape(nx, ny, nz, tx, ty, tz);
+      else fused_shape(prm, l, nx, ny, nz, tx, ty, tz);
       emit(i, nx, ny, nz, tx, ty, tz);
     }
   }
@@ -459,18 +489,13 @@ int Engine::build_lists(const std::vector<char> &member, int slot, ListSet &out)
     out.smooth[l] = make(l, smoothed);
     out.exist[l] = make(l, [&](int) { return l >= 1; });
     out.down[l] = make(l, [&](int i) { return l >= 1 && l <= hier[i].tail; });
-    out.fsm[l] = make_any(l, true, [&](int i) { return smoothed(i) && l < ftop[i]; });
     // (a one-level problem runs the finest down pass too: in the fused PCG
     // iteration it forms the residual)
-    out.fdn[l] = make_any(l, true, [&](int i) {
-      return smoothed(i) && l < ftop[i] && (l < hier[i].levels - 1 || l == 0);
-    });
-    // the fused cycle's per-half-sweep levels, and the levels restricted into
-    // from one of them
-    out.gsm[l] = make(l, [&](int i) { return smoothed(i) && l >= ftop[i]; });
-    out.gdn[l] = make(l, [&](int i) {
-      return l >= 1 && l <= hier[i].tail && l - 1 >= ftop[i];
-    });
+    auto downs = [&](int i) { return smoothed(i) && (l < hier[i].levels - 1 || l == 0); };
+    out.fsm[l] = make_any(l, true, [&](int i) { return smoothed(i) && !hier[i].box[l]; });
+    out.fdn[l] = make_any(l, true, [&](int i) { return downs(i) && !hier[i].box[l]; });
+    out.bsm[l] = make_any(l, true, [&](int i) { return smoothed(i) && hier[i].box[l]; });
+    out.bdn[l] = make_any(l, true, [&](int i) { return downs(i) && hier[i].box[l]; });
   }
   if (h_ranges.size() > per_slot) return ST_EINVAL;
   if (!h_ranges.empty())
@@ -595,25 +620,21 @@ void Engine::enqueue_assemble(const ListSet &ls) {
   need_pro = true;
 }
 
-// The fused V(1,1) cycle after its finest down pass: one sweep each way; the
-// coarse levels with enough cells to fill the GPU run the two fused passes
-// too (they never store the pre-smoothed x), the smaller, latency-bound ones
-// the per-half-sweep kernels; last the finest up pass.
+// The fused V(1,1) cycle after its finest down pass: one sweep each way, two
+// passes a level (marching tiles where the level fills the GPU, boxes
+// elsewhere; neither stores the pre-smoothed x); last the finest up pass.
 void Engine::enqueue_fused_rest(const ListSet &ls) {
   const int prec = mixed;
   const int tri = trilinear();
   for (int l = 1; l < Lmax; ++l) {
     launch_vdown(T, ls.fdn[l], l, prec, VD_ALL, stream);
-    launch_pre0(T, ls.gsm[l], l, prec, stream);
-    if (l + 1 < Lmax) launch_resid_restrict(T, ls.gdn[l + 1], l + 1, prec, stream);
+    launch_bdown(T, ls.bdn[l], l, prec, VD_ALL, stream);
   }
   if (Lmax > 1) launch_vtail(T, prec, 1, 1, tri, tail_big, stream);
-  for (int l = Lmax - 1; l >= 1; --l) {
-    launch_vup(T, ls.fsm[l], l, prec, 0, tri, stream);
-    launch_prolong_black(T, ls.gsm[l], l, prec, tri, stream);
-    launch_half(T, ls.gsm[l], l, 0, prec, stream);
+  for (int l = Lmax - 1; l >= 0; --l) {
+    launch_vup(T, ls.fsm[l], l, prec, l == 0 && mixed, tri, stream);
+    launch_bup(T, ls.bsm[l], l, prec, l == 0 && mixed, tri, stream);
   }
-  launch_vup(T, ls.fsm[0], 0, prec, mixed, tri, stream);
   if (local_on()) {
     for (int k = 0; k < prm.local_sweeps; ++k) {
       launch_local(T, ls.fine, 1, stream);
@@ -630,6 +651,7 @@ void Engine::enqueue_vcycle(const ListSet &ls) {
   const int tri = trilinear();
   if (fused) {
     launch_vdown(T, ls.fdn[0], 0, prec, VD_ALL, stream);
+    launch_bdown(T, ls.bdn[0], 0, prec, VD_ALL, stream);
     enqueue_fused_rest(ls);
     return;
   }
@@ -703,6 +725,7 @@ void Engine::enqueue_iteration(const ListSet &ls) {
     launch_spmv_p(T, ls.spg, 1, kmode(), stream);
     launch_fin(T, FIN_PQ, mixed, stream, 1);
     launch_vdown(T, ls.fdn[0], 0, mixed, VD_CONT, stream);
+    launch_bdown(T, ls.bdn[0], 0, mixed, VD_CONT, stream);
     launch_fin(T, FIN_RR2, mixed, stream, 1);
     return;
   }
@@ -719,6 +742,7 @@ void Engine::enqueue_iteration(const ListSet &ls) {
 void Engine::enqueue_prologue(const ListSet &ls) {
   if (!lazy || !need_pro) return;
   launch_vdown(T, ls.fdn[0], 0, mixed, VD_FRESH, stream);
+  launch_bdown(T, ls.bdn[0], 0, mixed, VD_FRESH, stream);
   launch_fin(T, FIN_FRESH, mixed, stream);
   need_pro = false;
 }
@@ -1020,6 +1044,7 @@ void Engine::enqueue_unit(const ListSet &ls, const CtlParams &cp) {
   launch_fin(T, FIN_STAGE, mixed, stream);
   if (lazy) {
     launch_vdown(T, ls.fdn[0], 0, mixed, VD_FRESH, stream);
+    launch_bdown(T, ls.bdn[0], 0, mixed, VD_FRESH, stream);
     launch_fin(T, FIN_FRESH, mixed, stream);
   }
   enqueue_iteration(ls);

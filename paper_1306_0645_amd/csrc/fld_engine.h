@@ -33,7 +33,9 @@ struct Hier {
   int tail = 1;                 // first level of the single-workgroup tail
   int n[kMaxLevels][3] = {};
   int tiles[kMaxLevels] = {};   // tiles per level
-  int ftiles[kMaxLevels] = {};  // fused-cycle tiles per level
+  int ftiles[kMaxLevels] = {};  // fused-cycle tiles (or boxes) per level
+  bool box[kMaxLevels] = {};    // the fused cycle runs the level box by box
+  bool local = false;           // the cycle may end with local sweeps
   long long cells(int l) const { return (long long)n[l][0] * n[l][1] * n[l][2]; }
 };
 
@@ -46,6 +48,7 @@ int count_tiles(const fld_params &p, int nx, int ny, int nz);
 void fused_shape(const fld_params &p, int l, int nx, int ny, int nz, int &tx,
                  int &ty, int &tz);
 int count_fused_tiles(const fld_params &p, int l, int nx, int ny, int nz);
+void box_shape(int nx, int ny, int nz, int &tx, int &ty, int &tz);
 bool fused_cycle(const fld_params &p);
 bool lazy_iteration(const fld_params &p);
 bool spmv_on_fused(const Hier &h);
@@ -81,10 +84,10 @@ struct ListSet {
   TileList fsm[kMaxLevels]{};   // fused tiles of smoothed levels
   TileList fdn[kMaxLevels]{};   // fused tiles of smoothed levels with a coarser one
   TileList down[kMaxLevels]{};  // levels restricted into from a per-level sweep
-  TileList gsm[kMaxLevels]{};   // fused cycle: per-half-sweep smoothed levels
-  TileList gdn[kMaxLevels]{};   // fused cycle: levels restricted into from one
+  TileList bsm[kMaxLevels]{};   // the same two, of levels run box by box
+  TileList bdn[kMaxLevels]{};
 };
-constexpr int kListsPerLevel = 7;  // smooth, exist, down, fsm, fdn, gsm, gdn
+constexpr int kListsPerLevel = 7;  // smooth, exist, down, fsm, fdn, bsm, bdn
 
 constexpr int kListSlots = 4;  // independent range regions (server phases)
 
@@ -111,7 +114,6 @@ class Engine {
   bool fused = false;      // one-sweep fused V-cycle kernels
   bool lazy = false;       // fused PCG iteration (residual update in the down pass)
   bool need_pro = false;   // some problem (re)starts: enqueue_prologue is due
-  std::vector<int> ftop;   // per problem: levels 0 .. ftop - 1 run the fused passes
   int last_nu = 1;         // sweeps per side of the cycle used by the last solve
   int last_tri = 0;        // the last solve's cycle used trilinear correction
   bool switched = false;   // the adaptive switch changed the handle's cycle

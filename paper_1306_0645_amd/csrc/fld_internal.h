@@ -16,6 +16,7 @@ constexpr int kBlock = 256;          // threads per tile block (4 wave64)
 constexpr int kFinBlock = 1024;      // threads of the per-problem finalize
 constexpr int kTailBlock = 1024;     // threads of the V-cycle tail kernel
 constexpr int kMaxLevels = 12;
+constexpr int kBoxX = 16, kBoxY = 8, kBoxZ = 4;  // largest box of a box pass
 
 // Status values (same numbers as the public fld_status).
 enum : int {
@@ -136,13 +137,12 @@ struct CtlDev {
 };
 
 // A tile: cells [x0, x0+tx) x [y0, y0+ty) x [z0, z0+tz) of one level of one
-// problem.  Each thread owns cpt consecutive x cells of one row and walks the
-// tile's planes.
+// problem.  Each thread owns one column of the tile (tile_col) and walks the
+// tile's planes, unless the kernel says otherwise.
 struct Tile {
   int prob;
   int x0, y0, z0;
-  int tx, ty, tz;
-  int cpt;
+  unsigned short tx, ty, tz, unused;
 };
 
 // Launch context: the tables live in device memory.
@@ -156,10 +156,10 @@ struct Tables {
   ProbDev *pd;      // [nprob]
   StepDev *sd;      // [nprob]
   Scal *sc;         // [nprob]
-  double *part;     // [n finest tiles][2] block partial sums
-  double *lpart;    // [n finest tiles][2] the local sweeps' r.z changes
+  double *part;     // [n finest tiles, standard then fused][2] block partial sums
+  double *lpart;    // [n finest standard tiles][2] the local sweeps' r.z changes
   CtlDev *ctl;      // [nprob] device-side step control
-  double *gpart;    // [n finest tiles][kAsmSums] sums of the assembly
+  double *gpart;    // [n finest standard tiles][kAsmSums] sums of the assembly
   int nprob;
 };
 
@@ -281,6 +281,11 @@ void launch_vdown(const Tables &T, TileList L, int l, int prec, int sel,
                   hipStream_t s);
 void launch_vup(const Tables &T, TileList L, int l, int prec, int flexible,
                 int trilinear, hipStream_t s);
+
+// the same passes box by box, for levels that do not fill the GPU (fld_box.hip)
+void launch_bdown(const Tables &T, TileList L, int l, int prec, int sel, hipStream_t s);
+void launch_bup(const Tables &T, TileList L, int l, int prec, int flexible, int trilinear,
+                hipStream_t s);
 
 // finalize kernels (launch_fin 'which')
 enum : int {

@@ -221,63 +221,61 @@ __global__ __launch_bounds__(kBlock) void k_coarsen(Tables T, TileList LC,
   if (!col.on) return;
   const int fx = F.nx, fy = F.ny, fz = F.nz;
   for (int K = t.z0; K < t.z0 + t.tz; ++K) {
-    for (int e = 0; e < t.cpt; ++e) {
-      const int I = col.i + e, J = col.j;
-      double mass = 0.0, txp = 0.0, txm = 0.0, typ = 0.0, tym = 0.0,
-             tzp = 0.0, tzm = 0.0;
+    const int I = col.i, J = col.j;
+    double mass = 0.0, txp = 0.0, txm = 0.0, typ = 0.0, tym = 0.0,
+           tzp = 0.0, tzm = 0.0;
 #pragma unroll
-      for (int cz = 0; cz < 2; ++cz)
+    for (int cz = 0; cz < 2; ++cz)
 #pragma unroll
-        for (int cy = 0; cy < 2; ++cy)
+      for (int cy = 0; cy < 2; ++cy)
 #pragma unroll
-          for (int cx = 0; cx < 2; ++cx) {
-            const Nb n = nbrs(2 * I + cx, 2 * J + cy, 2 * K + cz, fx, fy, fz);
-            const double fxp = F.Tx[n.c], fxm = F.Tx[n.xm];
-            const double fyp = F.Ty[n.c], fym = F.Ty[n.ym];
-            const double fzp = F.Tz[n.c], fzm = F.Tz[n.zm];
-            mass += F.diag[n.c] - (fxp + fxm + fyp + fym + fzp + fzm);
-            if (op == 0) {
-              if (cx == 1) txp += fxp; else txm += fxm;
-              if (cy == 1) typ += fyp; else tym += fym;
-              if (cz == 1) tzp += fzp; else tzm += fzm;
+        for (int cx = 0; cx < 2; ++cx) {
+          const Nb n = nbrs(2 * I + cx, 2 * J + cy, 2 * K + cz, fx, fy, fz);
+          const double fxp = F.Tx[n.c], fxm = F.Tx[n.xm];
+          const double fyp = F.Ty[n.c], fym = F.Ty[n.ym];
+          const double fzp = F.Tz[n.c], fzm = F.Tz[n.zm];
+          mass += F.diag[n.c] - (fxp + fxm + fyp + fym + fzp + fzm);
+          if (op == 0) {
+            if (cx == 1) txp += fxp; else txm += fxm;
+            if (cy == 1) typ += fyp; else tym += fym;
+            if (cz == 1) tzp += fzp; else tzm += fzm;
+          } else {
+            // a child on the + side: its -face (inner), its +face (the
+            // coarse face) and the neighbour's +face; on the - side: the
+            // -face of the cell two below, its own -face and +face
+            if (cx == 1) {
+              txp += series3(fxm, fxp, F.Tx[n.xp]);
             } else {
-              // a child on the + side: its -face (inner), its +face (the
-              // coarse face) and the neighbour's +face; on the - side: the
-              // -face of the cell two below, its own -face and +face
-              if (cx == 1) {
-                txp += series3(fxm, fxp, F.Tx[n.xp]);
-              } else {
-                const int i2 = 2 * I >= 2 ? 2 * I - 2 : 2 * I - 2 + fx;
-                txm += series3(F.Tx[n.c - 2 * I + i2], fxm, fxp);
-              }
-              if (cy == 1) {
-                typ += series3(fym, fyp, F.Ty[n.yp]);
-              } else {
-                const int j2 = 2 * J >= 2 ? 2 * J - 2 : 2 * J - 2 + fy;
-                tym += series3(F.Ty[n.c + (j2 - 2 * J) * fx], fym, fyp);
-              }
-              if (cz == 1) {
-                tzp += series3(fzm, fzp, F.Tz[n.zp]);
-              } else {
-                const int k2 = 2 * K >= 2 ? 2 * K - 2 : 2 * K - 2 + fz;
-                tzm += series3(F.Tz[n.c + (long long)(k2 - 2 * K) * fx * fy], fzm, fzp);
-              }
+              const int i2 = 2 * I >= 2 ? 2 * I - 2 : 2 * I - 2 + fx;
+              txm += series3(F.Tx[n.c - 2 * I + i2], fxm, fxp);
+            }
+            if (cy == 1) {
+              typ += series3(fym, fyp, F.Ty[n.yp]);
+            } else {
+              const int j2 = 2 * J >= 2 ? 2 * J - 2 : 2 * J - 2 + fy;
+              tym += series3(F.Ty[n.c + (j2 - 2 * J) * fx], fym, fyp);
+            }
+            if (cz == 1) {
+              tzp += series3(fzm, fzp, F.Tz[n.zp]);
+            } else {
+              const int k2 = 2 * K >= 2 ? 2 * K - 2 : 2 * K - 2 + fz;
+              tzm += series3(F.Tz[n.c + (long long)(k2 - 2 * K) * fx * fy], fzm, fzp);
             }
           }
-      const double s2 = op == 0 ? scale : 2.0 * scale;
-      txp *= s2; txm *= s2; typ *= s2; tym *= s2; tzp *= s2; tzm *= s2;
-      const double diag = mass + txp + txm + typ + tym + tzp + tzm;
-      const int o = (K * C.ny + J) * C.nx + I;
-      C.Tx[o] = txp;
-      C.Ty[o] = typ;
-      C.Tz[o] = tzp;
-      C.diag[o] = diag;
-      if (mixed) {
-        C.Tx32[o] = (float)txp;
-        C.Ty32[o] = (float)typ;
-        C.Tz32[o] = (float)tzp;
-        C.diag32[o] = (float)diag;
-      }
+        }
+    const double s2 = op == 0 ? scale : 2.0 * scale;
+    txp *= s2; txm *= s2; typ *= s2; tym *= s2; tzp *= s2; tzm *= s2;
+    const double diag = mass + txp + txm + typ + tym + tzp + tzm;
+    const int o = (K * C.ny + J) * C.nx + I;
+    C.Tx[o] = txp;
+    C.Ty[o] = typ;
+    C.Tz[o] = tzp;
+    C.diag[o] = diag;
+    if (mixed) {
+      C.Tx32[o] = (float)txp;
+      C.Ty32[o] = (float)typ;
+      C.Tz32[o] = (float)tzp;
+      C.diag32[o] = (float)diag;
     }
   }
 }
@@ -428,8 +426,7 @@ __global__ __launch_bounds__(kBlock) void k_half_out(Tables T, TileList TL,
 
 // Residual f - A x on the fine level summed over the 8 children of each
 // coarse cell: the coarse right-hand side (restriction = transpose of the
-// piecewise-constant prolongation).  One thread per coarse cell (cpt of them
-// along x).
+// piecewise-constant prolongation).  One thread per coarse cell.
 template <typename R, bool L0>
 __global__ __launch_bounds__(kBlock) void k_resid_restrict(Tables T,
                                                            TileList LC, int lc) {
@@ -447,21 +444,19 @@ __global__ __launch_bounds__(kBlock) void k_resid_restrict(Tables T,
   if (!col.on) return;
   auto xv = [&](int q) { return x[q]; };
   for (int K = t.z0; K < t.z0 + t.tz; ++K) {
-    for (int e = 0; e < t.cpt; ++e) {
-      const int I = col.i + e;
-      R acc = 0;
+    const int I = col.i;
+    R acc = 0;
 #pragma unroll
-      for (int cz = 0; cz < 2; ++cz)
+    for (int cz = 0; cz < 2; ++cz)
 #pragma unroll
-        for (int cy = 0; cy < 2; ++cy)
+      for (int cy = 0; cy < 2; ++cy)
 #pragma unroll
-          for (int cx = 0; cx < 2; ++cx) {
-            const Nb n = nbrs(2 * I + cx, 2 * col.j + cy, 2 * K + cz, F.nx,
-                              F.ny, F.nz);
-            acc += f(n.c) - (C.d[n.c] * x[n.c] - offsum(C, n, xv));
-          }
-      fc[(K * Cv.ny + col.j) * Cv.nx + I] = acc;
-    }
+        for (int cx = 0; cx < 2; ++cx) {
+          const Nb n = nbrs(2 * I + cx, 2 * col.j + cy, 2 * K + cz, F.nx,
+                            F.ny, F.nz);
+          acc += f(n.c) - (C.d[n.c] * x[n.c] - offsum(C, n, xv));
+        }
+    fc[(K * Cv.ny + col.j) * Cv.nx + I] = acc;
   }
 }
 
@@ -898,12 +893,10 @@ __global__ __launch_bounds__(kBlock) void k_true_resid(Tables T, TileList TL) {
   if (col.on) {
     auto xv = [&](int q) { return P.x[q]; };
     for (int k = t.z0; k < t.z0 + t.tz; ++k) {
-      for (int e = 0; e < t.cpt; ++e) {
-        const Nb n = nbrs(col.i + e, col.j, k, L.nx, L.ny, L.nz);
-        const double r = P.b[n.c] - (C.d[n.c] * P.x[n.c] - offsum(C, n, xv));
-        rcur(P, sc)[n.c] = r;
-        rr += r * r;
-      }
+      const Nb n = nbrs(col.i, col.j, k, L.nx, L.ny, L.nz);
+      const double r = P.b[n.c] - (C.d[n.c] * P.x[n.c] - offsum(C, n, xv));
+      rcur(P, sc)[n.c] = r;
+      rr += r * r;
     }
   }
   write_partials(T, tid, rr, 0.0);
@@ -1126,10 +1119,8 @@ __global__ __launch_bounds__(kBlock) void k_warm_revert(Tables T, TileList TL) {
   if (!col.on) return;
   for (int k = t.z0; k < t.z0 + t.tz; ++k) {
     const int c0 = (k * L.ny + col.j) * L.nx + col.i;
-    for (int e = 0; e < t.cpt; ++e) {
-      P.x[c0 + e] = 0.0;
-      rv[c0 + e] = P.b[c0 + e];
-    }
+    P.x[c0] = 0.0;
+    rv[c0] = P.b[c0];
   }
 }
 
@@ -1143,10 +1134,8 @@ __global__ __launch_bounds__(kBlock) void k_apply(Tables T, TileList TL,
   if (!col.on) return;
   auto uv = [&](int q) { return u[q]; };
   for (int k = t.z0; k < t.z0 + t.tz; ++k) {
-    for (int e = 0; e < t.cpt; ++e) {
-      const Nb n = nbrs(col.i + e, col.j, k, L.nx, L.ny, L.nz);
-      out[n.c] = C.d[n.c] * u[n.c] - offsum(C, n, uv);
-    }
+    const Nb n = nbrs(col.i, col.j, k, L.nx, L.ny, L.nz);
+    out[n.c] = C.d[n.c] * u[n.c] - offsum(C, n, uv);
   }
 }
 
@@ -1164,11 +1153,9 @@ __global__ __launch_bounds__(kBlock) void k_set_r(Tables T, TileList TL,
   if (col.on) {
     for (int k = t.z0; k < t.z0 + t.tz; ++k) {
       const int c0 = (k * L.ny + col.j) * L.nx + col.i;
-      for (int e = 0; e < t.cpt; ++e) {
-        const double r = rin[c0 + e];
-        rv[c0 + e] = r;
-        rr += r * r;
-      }
+      const double r = rin[c0];
+      rv[c0] = r;
+      rr += r * r;
     }
   }
   write_partials(T, tid, rr, 0.0);
@@ -1197,21 +1184,19 @@ __global__ __launch_bounds__(kBlock) void k_update_E(Tables T, TileList TL,
   if (col.on) {
     for (int k = t.z0; k < t.z0 + t.tz; ++k) {
       const int c0 = (k * L.ny + col.j) * L.nx + col.i;
-      for (int e = 0; e < t.cpt; ++e) {
-        const int c = c0 + e;
-        const double d = P.x[c];
-        dd += d * d;
-        if (copy_only) {
-          S.Eout[c] = d;
-        } else {
-          const double en = S.E[c] + d;
-          S.Eout[c] = en;
-          double w = fabs(en);
-          w = (w < floor) ? floor : w;
-          if (w > 0.0) {
-            const double q = d / w;
-            ch += q * q;
-          }
+      const int c = c0;
+      const double d = P.x[c];
+      dd += d * d;
+      if (copy_only) {
+        S.Eout[c] = d;
+      } else {
+        const double en = S.E[c] + d;
+        S.Eout[c] = en;
+        double w = fabs(en);
+        w = (w < floor) ? floor : w;
+        if (w > 0.0) {
+          const double q = d / w;
+          ch += q * q;
         }
       }
     }
