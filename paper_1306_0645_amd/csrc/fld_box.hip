@@ -117,15 +117,15 @@ __device__ __forceinline__ R box_red(const Cell7<R> &a, const R *x, int ex, int 
 template <typename R, bool L0>
 __global__ __launch_bounds__(kBlock) void k_bdown(Tables T, TileList TL, int l, int sel) {
   using FT = typename FSrc<R, L0>::FT;
-  const int tid = get_tile_index(TL);
-  const Tile t = TL.base[tid];
+  int tid;
+  const Tile t = get_tile(TL, tid);
   const Scal &sc = T.sc[t.prob];
   if (!sc.active) return;
   if ((sel == VD_FRESH && !sc.fresh) || (sel == VD_CONT && sc.fresh)) return;
   const LevelDev L = T.lv[l * T.nprob + t.prob];
   const ProbDev &P = T.pd[t.prob];
   const bool has_coarse = l + 1 < P.levels;
-  const LevelDev &Cv = T.lv[(has_coarse ? l + 1 : l) * T.nprob + t.prob];
+  const LevelDev &Cv = T.lv[min(l + 1, kMaxLevels - 1) * T.nprob + t.prob];
   const Coef<R> C = coefs<R>(L);
   const auto f = fsrc<R, L0>(L, P, sc);
   const double inv_s = sc.inv_s;
@@ -234,14 +234,14 @@ __global__ __launch_bounds__(kBlock) void k_bdown(Tables T, TileList TL, int l, 
 template <typename R, bool L0, bool TRI>
 __global__ __launch_bounds__(kBlock) void k_bup(Tables T, TileList TL, int l, int flexible) {
   using FT = typename FSrc<R, L0>::FT;
-  const int tid = get_tile_index(TL);
-  const Tile t = TL.base[tid];
+  int tid;
+  const Tile t = get_tile(TL, tid);
   const Scal &sc = T.sc[t.prob];
   if (!sc.active) return;
   const LevelDev L = T.lv[l * T.nprob + t.prob];
   const ProbDev &P = T.pd[t.prob];
   const bool has_coarse = l + 1 < P.levels;
-  const LevelDev Cl = T.lv[(has_coarse ? l + 1 : l) * T.nprob + t.prob];
+  const LevelDev Cl = T.lv[min(l + 1, kMaxLevels - 1) * T.nprob + t.prob];
   const Coef<R> C = coefs<R>(L);
   const auto f = fsrc<R, L0>(L, P, sc);
   const double inv_s = sc.inv_s, s_out = sc.s, zs_old = sc.zscale;

@@ -24,31 +24,44 @@ __device__ __forceinline__ int xcd_block(int nb) {
   return x * q + (x < rem ? x : rem) + (b >> 3);
 }
 
-__device__ __forceinline__ Tile get_tile(const TileList &L) {
+// The block's tile: idx is its index inside the full table (for per-tile
+// partial sums).  The problem comes with the range, so that the kernel's
+// loads of the problem's descriptors do not wait for the tile's.  A list of
+// one range (a plain handle) carries it in the kernel arguments; up to 64
+// ranges are searched by one load, a range per lane, and a ballot.
+__device__ __forceinline__ Tile get_tile(const TileList &L, int &idx) {
   const int b = xcd_block(L.nblocks);
-  int lo = 0;
+  int p = L.prob, first = L.first, start = 0;
   if (L.nranges > 1) {
-    int hi = L.nranges - 1;
-    while (lo < hi) {
-      const int mid = (lo + hi + 1) >> 1;
-      if (L.ranges[2 * mid] <= b) lo = mid; else hi = mid - 1;
+    int lo = 0;
+    if (L.nranges <= 64) {
+      const int lane = threadIdx.x & 63;
+      const int r = lane < L.nranges ? lane : 0;
+      const int rs = L.ranges[3 * r], rf = L.ranges[3 * r + 1], rp = L.ranges[3 * r + 2];
+      lo = __popcll(__ballot(lane < L.nranges && rs <= b)) - 1;
+      start = __builtin_amdgcn_readlane(rs, lo);
+      first = __builtin_amdgcn_readlane(rf, lo);
+      p = __builtin_amdgcn_readlane(rp, lo);
+    } else {
+      int hi = L.nranges - 1;
+      while (lo < hi) {
+        const int mid = (lo + hi + 1) >> 1;
+        if (L.ranges[3 * mid] <= b) lo = mid; else hi = mid - 1;
+      }
+      start = L.ranges[3 * lo];
+      first = L.ranges[3 * lo + 1];
+      p = L.ranges[3 * lo + 2];
     }
   }
-  return L.base[L.ranges[2 * lo + 1] + (b - L.ranges[2 * lo])];
+  idx = first + (b - start);
+  Tile t = L.base[idx];
+  t.prob = p;
+  return t;
 }
 
-// index of the tile inside the full table (for per-tile partial sums)
-__device__ __forceinline__ int get_tile_index(const TileList &L) {
-  const int b = xcd_block(L.nblocks);
-  int lo = 0;
-  if (L.nranges > 1) {
-    int hi = L.nranges - 1;
-    while (lo < hi) {
-      const int mid = (lo + hi + 1) >> 1;
-      if (L.ranges[2 * mid] <= b) lo = mid; else hi = mid - 1;
-    }
-  }
-  return L.ranges[2 * lo + 1] + (b - L.ranges[2 * lo]);
+__device__ __forceinline__ Tile get_tile(const TileList &L) {
+  int idx;
+  return get_tile(L, idx);
 }
 
 // Thread -> cells: a thread owns the column (i, j) of the tile and walks its

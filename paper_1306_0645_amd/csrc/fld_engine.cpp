@@ -299,8 +299,8 @@ static size_t tables_layout(Carver &cv, const std::vector<Hier> &hs,
     local = local || h.local;
   }
   // fine, the two SpMV lists and kListsPerLevel lists per level: at most
-  // one range per problem and list, 2 ints each, kListSlots sets
-  nranges = (size_t)(kListsPerLevel * kMaxLevels + 3) * np * 2 * kListSlots;
+  // one range per problem and list, 3 ints each, kListSlots sets
+  nranges = (size_t)(kListsPerLevel * kMaxLevels + 3) * np * 3 * kListSlots;
   LevelDev *lv = cv.take<LevelDev>((size_t)kMaxLevels * np);
   ProbDev *pd = cv.take<ProbDev>(np);
   StepDev *sd = cv.take<StepDev>(np);
@@ -466,8 +466,14 @@ int Engine::build_lists(const std::vector<char> &member, int slot, ListSet &out)
     int blocks = 0, nr = 0;
     for (int i = 0; i < np; ++i) {
       if (!member[i] || level >= hier[i].levels || !pred(i)) continue;
+      const int first = (fz ? fbeg : tbeg)[(size_t)i * kMaxLevels + level];
+      if (!nr) {
+        L.first = first;
+        L.prob = i;
+      }
       h_ranges.push_back(blocks);
-      h_ranges.push_back((fz ? fbeg : tbeg)[(size_t)i * kMaxLevels + level]);
+      h_ranges.push_back(first);
+      h_ranges.push_back(i);
       blocks += fz ? hier[i].ftiles[level] : hier[i].tiles[level];
       ++nr;
     }

@@ -456,8 +456,8 @@ __device__ __forceinline__ Q4<R> q_store_plane(const QPlane<R, L0, UP> &pl,
 template <typename R, bool L0>
 __global__ __launch_bounds__(kBlock) void k_vdown(Tables T, TileList TL, int l,
                                                   int sel) {
-  const int tid = get_tile_index(TL);
-  const Tile t = TL.base[tid];
+  int tid;
+  const Tile t = get_tile(TL, tid);
   const Scal &sc = T.sc[t.prob];
   if (!sc.active) return;
   if ((sel == VD_FRESH && !sc.fresh) || (sel == VD_CONT && sc.fresh)) return;
@@ -465,7 +465,7 @@ __global__ __launch_bounds__(kBlock) void k_vdown(Tables T, TileList TL, int l,
   const ProbDev P = T.pd[t.prob];
   // a one-level problem runs this pass only for the residual update
   const bool has_coarse = l + 1 < P.levels;
-  const LevelDev Cv = T.lv[(has_coarse ? l + 1 : l) * T.nprob + t.prob];
+  const LevelDev Cv = T.lv[min(l + 1, kMaxLevels - 1) * T.nprob + t.prob];
   const Coef<R> C = coefs<R>(L);
   const auto f = fsrc<R, L0>(L, P, sc);
   const double inv_s = sc.inv_s;
@@ -586,14 +586,14 @@ template <typename R, bool L0, bool TRI>
 __global__ __launch_bounds__(kBlock, 3) void k_vup(Tables T, TileList TL, int l,
                                                 int flexible) {
   using FT = typename QPlane<R, L0, true>::FT;
-  const int tid = get_tile_index(TL);
-  const Tile t = TL.base[tid];
+  int tid;
+  const Tile t = get_tile(TL, tid);
   const Scal &sc = T.sc[t.prob];
   if (!sc.active) return;
   const LevelDev L = T.lv[l * T.nprob + t.prob];
   const ProbDev P = T.pd[t.prob];
   const bool has_coarse = l + 1 < P.levels;
-  const LevelDev Cl = T.lv[(has_coarse ? l + 1 : l) * T.nprob + t.prob];
+  const LevelDev Cl = T.lv[min(l + 1, kMaxLevels - 1) * T.nprob + t.prob];
   const Coef<R> C = coefs<R>(L);
   const auto f = fsrc<R, L0>(L, P, sc);
   const double inv_s = sc.inv_s;

@@ -163,14 +163,16 @@ struct Tables {
   int nprob;
 };
 
-// A launch covers a subset of the full tile table: ranges[2r] is the first
-// block of range r, ranges[2r+1] the tile it maps to; ranges are sorted by
-// block.  nblocks = total blocks of the launch.
+// A launch covers a subset of the full tile table: ranges[3r] is the first
+// block of range r, ranges[3r+1] the tile it maps to, ranges[3r+2] the problem
+// of its tiles; ranges are sorted by block.  nblocks = total blocks of the
+// launch.  first, prob: the tile and the problem of range 0.
 struct TileList {
   const Tile *base;     // device: full tile table
-  const int *ranges;    // device: 2 * nranges ints
+  const int *ranges;    // device: 3 * nranges ints
   int nranges;
   int nblocks;
+  int first, prob;
 };
 
 // ---- kernel ids of the timing hook (include/fld_profile.h) ----------------

@@ -55,8 +55,8 @@ __global__ __launch_bounds__(kBlock) void k_assemble(Tables T, TileList L0,
                                                      double c, double theta,
                                                      double dmax, double rmin,
                                                      int mixed) {
-  const int tid = get_tile_index(L0);
-  const Tile t = L0.base[tid];
+  int tid;
+  const Tile t = get_tile(L0, tid);
   const Scal &sc = T.sc[t.prob];
   if (!asm_due(sc)) return;
   const LevelDev L = T.lv[t.prob];
@@ -346,7 +346,7 @@ __global__ __launch_bounds__(kBlock) void k_prolong_black(Tables T, TileList TL,
   const LevelDev L = T.lv[l * T.nprob + t.prob];
   const ProbDev P = T.pd[t.prob];
   const bool has_coarse = l + 1 < P.levels;
-  const LevelDev Cl = T.lv[(has_coarse ? l + 1 : l) * T.nprob + t.prob];
+  const LevelDev Cl = T.lv[min(l + 1, kMaxLevels - 1) * T.nprob + t.prob];
   const Coef<R> C = coefs<R>(L);
   const auto f = fsrc<R, L0>(L, P, sc);
   R *x = (R *)L.x;
@@ -388,8 +388,8 @@ __global__ __launch_bounds__(kBlock) void k_prolong_black(Tables T, TileList TL,
 template <typename R>
 __global__ __launch_bounds__(kBlock) void k_half_out(Tables T, TileList TL,
                                                      int flexible) {
-  const int tid = get_tile_index(TL);
-  const Tile t = TL.base[tid];
+  int tid;
+  const Tile t = get_tile(TL, tid);
   const Scal &sc = T.sc[t.prob];
   if (!sc.active) return;
   const LevelDev L = T.lv[t.prob];
@@ -474,8 +474,8 @@ template <typename R, bool L0>
 __global__ __launch_bounds__(kBlock) void k_jacobi(Tables T, TileList TL, int l,
                                                    int mode, int in_x2,
                                                    int flexible) {
-  const int tid = get_tile_index(TL);
-  const Tile t = TL.base[tid];
+  int tid;
+  const Tile t = get_tile(TL, tid);
   const Scal &sc = T.sc[t.prob];
   if (!sc.active) return;
   const LevelDev L = T.lv[l * T.nprob + t.prob];
@@ -534,7 +534,7 @@ __global__ __launch_bounds__(kBlock) void k_prolong_add(Tables T, TileList TL,
   const LevelDev L = T.lv[l * T.nprob + t.prob];
   const ProbDev P = T.pd[t.prob];
   const bool has_coarse = l + 1 < P.levels;  // one-level problem: a copy
-  const LevelDev Cl = T.lv[(has_coarse ? l + 1 : l) * T.nprob + t.prob];
+  const LevelDev Cl = T.lv[min(l + 1, kMaxLevels - 1) * T.nprob + t.prob];
   const R *e = (const R *)Cl.x;
   const R *x = (const R *)L.x;
   R *out = (R *)(to_x2 ? L.x2 : L.x);
@@ -629,8 +629,8 @@ __device__ __forceinline__ double spmv_column(
 template <bool LAZY, int KM>
 __global__ __launch_bounds__(kBlock) void k_spmv_p(Tables T, TileList TL) {
   using D = DirT<KM>;
-  const int tid = get_tile_index(TL);
-  const Tile t = TL.base[tid];
+  int tid;
+  const Tile t = get_tile(TL, tid);
   const Scal &sc = T.sc[t.prob];
   if (!sc.active) return;
   const LevelDev L = T.lv[t.prob];
@@ -773,8 +773,8 @@ __device__ __forceinline__ double spmv_rows(
 template <bool LAZY, int KM>
 __global__ __launch_bounds__(kBlock) void k_spmv_f(Tables T, TileList TL) {
   using D = DirT<KM>;
-  const int tid = get_tile_index(TL);
-  const Tile t = TL.base[tid];
+  int tid;
+  const Tile t = get_tile(TL, tid);
   const Scal &sc = T.sc[t.prob];
   if (!sc.active) return;
   const LevelDev L = T.lv[t.prob];
@@ -852,8 +852,8 @@ __global__ __launch_bounds__(kBlock) void k_xfix(Tables T, TileList TL) {
 // x += alpha p, r -= alpha q, partial ||r||^2
 template <int KM>
 __global__ __launch_bounds__(kBlock) void k_update(Tables T, TileList TL) {
-  const int tid = get_tile_index(TL);
-  const Tile t = TL.base[tid];
+  int tid;
+  const Tile t = get_tile(TL, tid);
   const Scal &sc = T.sc[t.prob];
   if (!sc.active) return;
   const LevelDev L = T.lv[t.prob];
@@ -881,8 +881,8 @@ __global__ __launch_bounds__(kBlock) void k_update(Tables T, TileList TL) {
 // true residual r = b - A x in FP64 (problems whose recursive residual met
 // the tolerance), partial ||r||^2
 __global__ __launch_bounds__(kBlock) void k_true_resid(Tables T, TileList TL) {
-  const int tid = get_tile_index(TL);
-  const Tile t = TL.base[tid];
+  int tid;
+  const Tile t = get_tile(TL, tid);
   const Scal &sc = T.sc[t.prob];
   if (sc.phase != PH_VERIFY) return;
   const LevelDev L = T.lv[t.prob];
@@ -906,8 +906,8 @@ __global__ __launch_bounds__(kBlock) void k_true_resid(Tables T, TileList TL) {
 // dE(n-1), formed at the cell and its neighbours on the fly, and r = b - A x0
 // with the assembled FP64 operator; partial ||r||^2 for FIN_WARM.
 __global__ __launch_bounds__(kBlock) void k_warm_x(Tables T, TileList TL) {
-  const int tid = get_tile_index(TL);
-  const Tile t = TL.base[tid];
+  int tid;
+  const Tile t = get_tile(TL, tid);
   const Scal &sc = T.sc[t.prob];
   const StepDev S = T.sd[t.prob];
   if (!warm_due(sc) || !(S.warm > 1.0) || sc.phase != PH_ITER || sc.cold) return;
@@ -1018,8 +1018,8 @@ __device__ __forceinline__ int box_cell(const Tile &t, int q, int nx, int ny) {
 
 __global__ __launch_bounds__(kBlock) void k_lmask(Tables T, TileList TL,
                                                   double coupling) {
-  const int tid = get_tile_index(TL);
-  const Tile t = TL.base[tid];
+  int tid;
+  const Tile t = get_tile(TL, tid);
   const Scal &sc = T.sc[t.prob];
   if (!asm_due(sc)) return;
   const LevelDev L = T.lv[t.prob];
@@ -1056,8 +1056,8 @@ __global__ __launch_bounds__(kBlock) void k_lmask(Tables T, TileList TL,
 }
 
 __global__ __launch_bounds__(kBlock) void k_local(Tables T, TileList TL, int colour) {
-  const int tid = get_tile_index(TL);
-  const Tile t = TL.base[tid];
+  int tid;
+  const Tile t = get_tile(TL, tid);
   const Scal &sc = T.sc[t.prob];
   if (!sc.active) return;
   const ProbDev P = T.pd[t.prob];
@@ -1142,8 +1142,8 @@ __global__ __launch_bounds__(kBlock) void k_apply(Tables T, TileList TL,
 // load an external residual (preconditioner entry point): r = given, ||r||^2
 __global__ __launch_bounds__(kBlock) void k_set_r(Tables T, TileList TL,
                                                   const double *rin) {
-  const int tid = get_tile_index(TL);
-  const Tile t = TL.base[tid];
+  int tid;
+  const Tile t = get_tile(TL, tid);
   const Scal &sc = T.sc[t.prob];
   const LevelDev L = T.lv[t.prob];
   const ProbDev P = T.pd[t.prob];
@@ -1172,8 +1172,8 @@ __device__ __forceinline__ bool commit_now(const Scal &sc) {
 __global__ __launch_bounds__(kBlock) void k_update_E(Tables T, TileList TL,
                                                      double floor,
                                                      int copy_only, int in_solve) {
-  const int tid = get_tile_index(TL);
-  const Tile t = TL.base[tid];
+  int tid;
+  const Tile t = get_tile(TL, tid);
   const Scal &sc = T.sc[t.prob];
   if (in_solve ? !commit_now(sc) : !sc.live) return;
   const LevelDev L = T.lv[t.prob];
