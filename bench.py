@@ -40,10 +40,13 @@ BYTES_PER_CELL = {
     "assemble": (96.0, 112.0),
     # mixed form: z and p are FP32 (z in, p_old in, p_new out: 4 B each)
     "spmv_p": (64.0, 52.0),
-    # fused iteration's SpMV: also x += alpha p_old (x read and written)
-    "spmv_px": (80.0, 68.0),
-    # the deferred x += alpha p when a solve stops iterating
-    "xfix": (24.0, 20.0),
+    # fused iteration's SpMV, the mean of its two forms: z, p_old and the
+    # operator in, q out (48 B); the same with the previous z, and p and x
+    # written too (72 B)
+    "spmv_px": (80.0, 60.0),
+    # the deferred update of x when a solve stops iterating (mean of the two
+    # forms)
+    "xfix": (24.0, 22.0),
     # Galerkin warm guess: x0 and r = b - A x0 from the operator, b and the
     # two dE (72 B), less the x and r the assembly then leaves to it (16 B)
     "warm_x": (56.0, 56.0),
@@ -71,9 +74,10 @@ BYTES_PER_CELL = {
 }
 
 # The mixed form with an FP64 search direction (direction_fp64) reads and
-# writes p in 8 bytes instead of 4: p_old in and p_new out of the SpMV, p in
-# the update and the deferred x update.
-DIR64_EXTRA = {"spmv_p": 8.0, "spmv_px": 8.0, "xfix": 4.0, "update": 4.0}
+# writes p in 8 bytes instead of 4: p_old in and p_new out of the SpMV (every
+# other time in the fused iteration), p in the update and the deferred x
+# update.
+DIR64_EXTRA = {"spmv_p": 8.0, "spmv_px": 6.0, "xfix": 4.0, "update": 4.0}
 
 
 def bpc(name, prec_idx, dir64=False):
@@ -212,8 +216,8 @@ def measured_traffic(kernel, form, workload=None, root=ROOT):
 PMC_KERNELS = {
     # the fused iteration's SpMV: on the fused tiles where a grid gives 2048
     # of them, else on the 64 x 4 tiles (the first name that ran is taken)
-    ("spmv_px", "mixed_dir64"): ("fld::k_spmv_f<true, 2>", "fld::k_spmv_p<true, 2>"),
-    ("spmv_px", "mixed"): ("fld::k_spmv_f<true, 1>", "fld::k_spmv_p<true, 1>"),
+    ("spmv_px", "mixed_dir64"): ("fld::k_spmv_f<2>", "fld::k_spmv_p<true, 2>"),
+    ("spmv_px", "mixed"): ("fld::k_spmv_f<1>", "fld::k_spmv_p<true, 1>"),
     ("spmv_p", "fp64"): "fld::k_spmv_p<false, 0>",
     ("vup_fine", "mixed"): "fld::k_vup<float, true, false>",
     ("vup_fine", "mixed_tri"): "fld::k_vup<float, true, true>",

@@ -318,8 +318,8 @@ __global__ __launch_bounds__(kBlock) void k_bup(Tables T, TileList TL, int l, in
       f1[u] = f.raw(g + 1);
       if constexpr (L0 && sizeof(R) == 4) {
         if (rd_old) {
-          z0[u] = P.z32[g];
-          z1[u] = P.z32[g + 1];
+          z0[u] = zcur(P, sc)[g];
+          z1[u] = zcur(P, sc)[g + 1];
         }
       }
     }
@@ -392,8 +392,8 @@ __global__ __launch_bounds__(kBlock) void k_bup(Tables T, TileList TL, int l, in
             rzo += f0[u] * ((double)z0[u] * zs_old);
             rzo += f1[u] * ((double)z1[u] * zs_old);
           }
-          P.z32[g] = v0;
-          P.z32[g + 1] = v1;
+          znext(P, sc)[g] = v0;
+          znext(P, sc)[g + 1] = v1;
         } else {
           P.z[g] = w0;
           P.z[g + 1] = w1;

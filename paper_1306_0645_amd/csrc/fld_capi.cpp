@@ -275,7 +275,7 @@ fld_status fld_precondition(fld_handle *h, const double *r, double *z) {
   e.enqueue_vcycle(e.all);
   const ProbDev &P = e.mem[0].pd;
   if (e.mixed) {
-    launch_z_out(e.T, e.all.fine, z, e.stream);
+    launch_z_out(e.T, e.all.fine, e.fused, z, e.stream);
     if (hipGetLastError() != hipSuccess) return FLD_EDEVICE;
   } else if (hipMemcpyAsync(z, P.z, nb, hipMemcpyDeviceToDevice, e.stream) != hipSuccess) {
     return FLD_EDEVICE;

@@ -246,6 +246,15 @@ __device__ __forceinline__ double *rnext(const ProbDev &P, const Scal &sc) {
   return sc.rbuf ? P.r : P.r2;
 }
 
+// mixed form: the newest z (after FIN_RZ), and the buffer that the fused
+// cycle's post-sweep writes
+__device__ __forceinline__ float *zcur(const ProbDev &P, const Scal &sc) {
+  return sc.zbuf ? P.z32b : P.z32;
+}
+__device__ __forceinline__ float *znext(const ProbDev &P, const Scal &sc) {
+  return sc.zbuf ? P.z32 : P.z32b;
+}
+
 template <typename R, bool L0>
 __device__ __forceinline__ FSrc<R, L0> fsrc(const LevelDev &L, const ProbDev &P,
                                              const Scal &sc) {

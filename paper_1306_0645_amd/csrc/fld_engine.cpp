@@ -257,6 +257,7 @@ void carve_problem(Carver &cv, const Hier &h, const fld_params &p, ProbMem &m) {
       P.lcnt = local ? cv.take<int>(2 * (size_t)h.tiles[0]) : nullptr;
       L.x = mixed ? (void *)cv.take<float>(n) : (void *)P.z;
       L.f = nullptr;
+      if (mixed) P.z32b = (float *)L.x;
       if (jacobi) L.x2 = mixed ? (void *)cv.take<float>(n) : (void *)cv.take<double>(n);
     } else {
       if (mixed) {
@@ -1054,8 +1055,10 @@ void Engine::enqueue_unit(const ListSet &ls, const CtlParams &cp) {
     launch_fin(T, FIN_FRESH, mixed, stream);
   }
   enqueue_iteration(ls);
-  launch_xfix(T, ls.fine, kmode(), stream);
-  launch_fin(T, FIN_XFIX, mixed, stream);
+  if (lazy) {
+    launch_xfix(T, ls.fine, kmode(), stream);
+    launch_fin(T, FIN_XFIX, mixed, stream);
+  }
   launch_true_resid(T, ls.fine, stream);
   launch_fin(T, FIN_TRUE, mixed, stream);
   launch_update_E(T, ls.fine, prm.e_floor, 0, stream, 1);

@@ -604,6 +604,8 @@ __global__ __launch_bounds__(kBlock, 3) void k_vup(Tables T, TileList TL, int l,
   // the mixed form keeps z as the cycle's FP32 output, z = zscale z32
   const bool rd_old = flexible && !sc.restart;
   const double zs_old = sc.zscale;
+  const float *zold = zcur(P, sc);
+  float *znew = znext(P, sc);
   __shared__ R vs[3][kE2];
   __shared__ R xs[3][kE1];
   // trilinear: the coarse planes under the tile, a ring of 3 (corr_lds); the
@@ -671,8 +673,8 @@ __global__ __launch_bounds__(kBlock, 3) void k_vup(Tables T, TileList TL, int l,
       ld2(src + o0 + nx, H.v01, H.v11);
       if constexpr (L0 && sizeof(R) == 4) {
         if (rd_old) {
-          ld2(P.z32 + o0, zo00, zo10);
-          ld2(P.z32 + o0 + nx, zo01, zo11);
+          ld2(zold + o0, zo00, zo10);
+          ld2(zold + o0 + nx, zo01, zo11);
         }
       }
     }
@@ -743,8 +745,8 @@ __global__ __launch_bounds__(kBlock, 3) void k_vup(Tables T, TileList TL, int l,
         if (rd_old) rzo += H.v11 * ((double)zo11 * zs_old);
         rz += H.v11 * z11;
         if constexpr (sizeof(R) == 4) {
-          st2(P.z32 + o0, v00, v10);
-          st2(P.z32 + o0 + nx, v01, v11);
+          st2(znew + o0, v00, v10);
+          st2(znew + o0 + nx, v01, v11);
         } else {
           st2(P.z + o0, z00, z10);
           st2(P.z + o0 + nx, z01, z11);

@@ -55,8 +55,10 @@ struct ProbDev {
   double *p0, *p1;       // FP64 direction (FP64 form; mixed with direction_fp64)
   // mixed form: the V-cycle's FP32 output as it is, z = zscale * z32, and
   // the search direction either in FP32 at the scale of the z it was formed
-  // from, p = pscale * pf0 (or pf1), or in FP64 in p0 / p1
-  float *z32, *pf0, *pf1;
+  // from, p = pscale * pf0 (or pf1), or in FP64 in p0 / p1.  The fused
+  // iteration alternates between z32 and z32b (the finest iterate buffer,
+  // which its cycle does not use), so that the previous z stays readable
+  float *z32, *z32b, *pf0, *pf1;
   double *r2;            // second residual buffer (fused V(1,1) iteration)
   // local smoothing (mixed fused cycle): the cells whose coupling to the
   // neighbours dominates the diagonal (sum of faces > local_coupling x
@@ -109,6 +111,14 @@ struct Scal {
   // forms r - alpha q; xlag: x still lacks alpha p (added by the next SpMV,
   // or by k_xfix when the iteration stops)
   int rbuf, has_dir, xlag, snew;
+  // fused iteration, the direction stored every other time: the base p (in
+  // the buffer pbuf names) exists from hasb on; lag = 1: the newest direction
+  // p = z + beta base was formed but not stored, and x lacks alpha1 base +
+  // alpha p; lag = 0: the newest direction is the base, and x lacks alpha
+  // base (both while xlag).  zbuf: the buffer of the newest z; beta1, alpha1,
+  // zscale1: the values of the iteration before
+  int lag, hasb, zbuf;
+  double alpha1, beta1, zscale1;
   int fresh;             // (re)started: the finest down pass is still due
   int committed;         // E += dE of this solve is done (FIN_STEP)
   // device-controlled stepping (fld_advance): ctl = 1 while the device runs
@@ -236,14 +246,13 @@ void launch_prolong_add(const Tables &T, TileList L, int l, int prec,
 // Krylov storage of the finest level (Engine::kmode): 0 = FP64 z and p,
 // 1 = mixed form with FP32 z and p (each at a per-problem scale), 2 = mixed
 // form with FP32 z and an FP64 search direction p
-// lazy = 1 (fused iteration): also x += alpha p_old, the update deferred
-// from the previous iteration (mixed forms only)
-// the fused iteration's SpMV (x += alpha p_old, p = z + beta p_old, q = A p)
-// on the finest fused tiles; its partials sum over the fused range
+// lazy = 1 (mixed forms): the fused iteration's SpMV, which stores the
+// direction and updates x every other time; launch_spmv_f: the same on the
+// finest fused tiles, its partials summed over the fused range
 void launch_spmv_f(const Tables &T, TileList F0, int km, hipStream_t s);
 void launch_spmv_p(const Tables &T, TileList L0, int lazy, int km, hipStream_t s);
-// out = s * z32 right after a mixed-form V-cycle (the preconditioner alone)
-void launch_z_out(const Tables &T, TileList L0, double *out, hipStream_t s);
+// out = s * z right after a mixed-form V-cycle (the preconditioner alone)
+void launch_z_out(const Tables &T, TileList L0, int fused, double *out, hipStream_t s);
 // x += alpha p for problems that stopped iterating with the update pending
 void launch_xfix(const Tables &T, TileList L0, int km, hipStream_t s);
 void launch_update(const Tables &T, TileList L0, int km, hipStream_t s);

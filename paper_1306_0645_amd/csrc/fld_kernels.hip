@@ -553,74 +553,165 @@ __global__ __launch_bounds__(kBlock) void k_prolong_add(Tables T, TileList TL,
 // Krylov kernels (FP64, finest level; two x-consecutive cells per thread)
 // ---------------------------------------------------------------------------
 
-// p_new = z + beta p_old (formed at the cell and its neighbours on the fly),
-// q = A p_new, partial p_new . q.  p is double-buffered so neighbours read
-// the old direction while the new one is written.  Each thread walks its
-// column in z keeping p_new at planes k-1, k, k+1 and the -z face in
-// registers.
-// LAZY: also x += alpha_old p_old at the cell (the fused iteration defers
-// that update of the previous iteration to here, where p_old is read anyway).
+// p = z + beta p_old (formed at the cell and its neighbours on the fly),
+// q = A p, partial p . q.  p is double-buffered so neighbours read the old
+// direction while the new one is written.  Each thread walks its column in z
+// keeping p at planes k-1, k, k+1 and the -z face in registers.
 // Krylov storage modes (KM): KM_FP64: z and p FP64.  KM_MIX32 (mixed form):
-// z, p_old and p_new FP32 at a scale each (zs for z and p_new, ps for
-// p_old); p_new is rounded to FP32 before it is used, so q, the dot and the
-// later x update all see the direction that is stored.  KM_MIX64 (mixed form
-// with an FP64 direction): z FP32 at the scale zs (the V-cycle's output as
-// it is), p_old and p_new FP64.
+// z, p_old and p FP32 at a scale each (zs for z and p, ps for p_old); p is
+// rounded to FP32 before it is used, so q, the dot and the later x update all
+// see the direction that is stored.  KM_MIX64 (mixed form with an FP64
+// direction): z FP32 at the scale zs (the V-cycle's output as it is), p_old
+// and p FP64.
+//
+// The fused iteration (mixed forms) stores the direction every other time:
+//   F_SKIP:  p_k = z_k + beta_k base; neither p nor x is written;
+//   F_STORE: p_k again from z_k (kept in the other z buffer) and the base,
+//            p_{k+1} = z_{k+1} + beta_{k+1} p_k is stored as the next base,
+//            and x += alpha_{k-1} base + alpha_k p_k, both updates at once.
+// p_k comes out of the same fused multiply-adds both times, so q, x and the
+// stored directions are bit for bit those of an iteration that stores every
+// direction and updates x each time, for 52 and 80 B a cell instead of 76
+// and 76 (FP64 direction; FP32: 48 and 72 instead of 68 and 68).  Bound by
+// these bytes: 640^3, FP64 direction, 4252 -> 3712 us a launch (4.67 TB/s of
+// them).  F_PLAIN (the other iterations): p is stored every time, x updated
+// in k_update.
 enum : int { KM_FP64 = 0, KM_MIX32 = 1, KM_MIX64 = 2 };
+enum : int { F_PLAIN = 0, F_SKIP = 1, F_STORE = 2 };
 
 template <int KM>
 using ZT = std::conditional_t<KM == KM_FP64, double, float>;
 template <int KM>
 using DirT = std::conditional_t<KM == KM_MIX32, float, double>;
 
-template <bool BETA, bool LAZY, int KM>
-__device__ __forceinline__ double spmv_column(
-    const Tile &t, const Col &col, int nx, int ny, int nz, double beta,
-    const ZT<KM> *__restrict__ z, double zs, const DirT<KM> *__restrict__ po,
-    double ps, DirT<KM> *__restrict__ pn, double *__restrict__ q,
-    const double *__restrict__ Tx, const double *__restrict__ Ty,
-    const double *__restrict__ Tz, const double *__restrict__ Dg,
-    double alpha_old, double *__restrict__ x) {
+// what the directions are formed from; BASE: a base exists (beta != 0)
+template <int F, bool BASE, int KM>
+struct DirSrc {
   using D = DirT<KM>;
-  const double cb = KM == KM_MIX32 ? beta * ps / zs : beta;  // p_old's share, in z's scale
-  auto raw = [&](int g) -> D {  // p_new as stored
-    if constexpr (KM == KM_MIX32)
-      return BETA ? (float)((double)z[g] + cb * (double)po[g]) : z[g];
-    else if constexpr (KM == KM_MIX64)
-      return BETA ? zs * (double)z[g] + beta * po[g] : zs * (double)z[g];
-    else return BETA ? z[g] + beta * po[g] : z[g];
+  const ZT<KM> *__restrict__ z;    // this iteration's z
+  const ZT<KM> *__restrict__ z1;   // F_STORE: the z before
+  const D *__restrict__ po;        // base (p_old)
+  double zs, zs1, ps;              // scales of z, z1 and (KM_MIX32) the base
+  double c, c1;                    // the direction's coefficient of the one before
+  double a, a1;                    // F_STORE: x += a1 base + a mid
+  // loads at a cell, then the direction there; F_STORE: mid is p_k
+  struct In {
+    ZT<KM> z, z1;
+    D po;
   };
-  auto val = [&](D v) -> double {  // its value
+  __device__ __forceinline__ In load(int g) const {
+    In v;
+    v.z = z[g];
+    v.z1 = F == F_STORE ? z1[g] : (ZT<KM>)0;
+    v.po = BASE ? po[g] : (D)0;
+    return v;
+  }
+  __device__ __forceinline__ static D one(ZT<KM> zv, double s, double cf, D prev) {
+    if constexpr (KM == KM_MIX32) return (float)__builtin_fma(cf, (double)prev, (double)zv);
+    else if constexpr (KM == KM_MIX64) return __builtin_fma(cf, prev, s * (double)zv);
+    else return __builtin_fma(cf, prev, zv);
+  }
+  __device__ __forceinline__ static D first(ZT<KM> zv, double s) {
+    if constexpr (KM == KM_MIX64) return s * (double)zv;
+    else return zv;
+  }
+  __device__ __forceinline__ D make(const In &v, D &mid) const {
+    if constexpr (F == F_STORE) {
+      mid = BASE ? one(v.z1, zs1, c1, v.po) : first(v.z1, zs1);
+      return one(v.z, zs, c, mid);
+    } else {
+      mid = (D)0;
+      return BASE ? one(v.z, zs, c, v.po) : first(v.z, zs);
+    }
+  }
+  __device__ __forceinline__ D raw(int g) const {
+    D mid;
+    return make(load(g), mid);
+  }
+  __device__ __forceinline__ double val(D v) const {
     if constexpr (KM == KM_MIX32) return zs * (double)v;
     else return v;
-  };
+  }
+  // x with the two pending updates
+  __device__ __forceinline__ double advance(double x, D base, D mid) const {
+    if constexpr (KM == KM_MIX32) {
+      if (BASE) x = __builtin_fma(a1, ps * (double)base, x);
+      return __builtin_fma(a, zs1 * (double)mid, x);
+    } else {
+      if (BASE) x = __builtin_fma(a1, base, x);
+      return __builtin_fma(a, mid, x);
+    }
+  }
+};
+
+template <int F, bool BASE, int KM>
+__device__ __forceinline__ DirSrc<F, BASE, KM> dir_src(const ProbDev &P, const Scal &sc) {
+  DirSrc<F, BASE, KM> S;
+  if constexpr (KM == KM_FP64) {
+    S.z = S.z1 = P.z;
+  } else {
+    S.z = zcur(P, sc);
+    S.z1 = znext(P, sc);
+  }
+  if constexpr (KM == KM_MIX32) S.po = sc.pbuf ? P.pf1 : P.pf0;
+  else S.po = sc.pbuf ? P.p1 : P.p0;
+  S.zs = sc.zscale;
+  S.zs1 = sc.zscale1;
+  S.ps = sc.pscale;
+  S.c = sc.beta;
+  S.c1 = sc.beta1;
+  if constexpr (KM == KM_MIX32) {
+    // the previous direction's share, in z's scale
+    S.c = F == F_STORE ? sc.beta * sc.zscale1 / sc.zscale : sc.beta * sc.pscale / sc.zscale;
+    S.c1 = sc.beta1 * sc.pscale / sc.zscale1;
+  }
+  S.a = sc.alpha;
+  S.a1 = sc.alpha1;
+  return S;
+}
+
+template <int KM>
+__device__ __forceinline__ DirT<KM> *dir_next(const ProbDev &P, const Scal &sc) {
+  if constexpr (KM == KM_MIX32) return sc.pbuf ? P.pf0 : P.pf1;
+  else return sc.pbuf ? P.p0 : P.p1;
+}
+
+template <int F, bool BASE, int KM>
+__device__ __forceinline__ double spmv_column(
+    const Tile &t, const Col &col, int nx, int ny, int nz, const DirSrc<F, BASE, KM> &S,
+    DirT<KM> *__restrict__ pn, double *__restrict__ q, const double *__restrict__ Tx,
+    const double *__restrict__ Ty, const double *__restrict__ Tz,
+    const double *__restrict__ Dg, double *__restrict__ x) {
+  using D = DirT<KM>;
   const int plane = nx * ny, i = col.i, j = col.j;
   const int dxm = (i == 0) ? nx - 1 : -1, dxp = (i == nx - 1) ? 1 - nx : 1;
   const int dym = (j == 0) ? (ny - 1) * nx : -nx;
   const int dyp = (j == ny - 1) ? -(ny - 1) * nx : nx;
   int c = t.z0 * plane + j * nx + i;
   const int cm0 = (t.z0 == 0) ? c + (nz - 1) * plane : c - plane;
-  D r_m = raw(cm0), r_c = raw(c);
+  const auto ic = S.load(c);
+  D m_c, m_p;            // F_STORE: p_k at planes k, k + 1, and the base there
+  D r_m = S.raw(cm0), r_c = S.make(ic, m_c), b_c = ic.po;
   double tz_m = Tz[cm0];
   double acc = 0.0;
   for (int k = t.z0; k < t.z0 + t.tz; ++k) {
     const int cp = (k == nz - 1) ? c - (nz - 1) * plane : c + plane;
-    const D r_p = raw(cp);
-    const double s = Tx[c] * val(raw(c + dxp)) + Tx[c + dxm] * val(raw(c + dxm)) +
-                     Ty[c] * val(raw(c + dyp)) + Ty[c + dym] * val(raw(c + dym)) +
-                     Tz[c] * val(r_p) + tz_m * val(r_m);
-    const double p_c = val(r_c);
+    const auto ip = S.load(cp);
+    const D r_p = S.make(ip, m_p);
+    const double s = Tx[c] * S.val(S.raw(c + dxp)) + Tx[c + dxm] * S.val(S.raw(c + dxm)) +
+                     Ty[c] * S.val(S.raw(c + dyp)) + Ty[c + dym] * S.val(S.raw(c + dym)) +
+                     Tz[c] * S.val(r_p) + tz_m * S.val(r_m);
+    const double p_c = S.val(r_c);
     const double qq = Dg[c] * p_c - s;
-    if constexpr (LAZY) {
-      if constexpr (KM == KM_MIX32) x[c] = x[c] + alpha_old * (ps * (double)po[c]);
-      else x[c] = x[c] + alpha_old * po[c];
-    }
-    pn[c] = r_c;
+    if constexpr (F == F_STORE) x[c] = S.advance(x[c], b_c, m_c);
+    if constexpr (F != F_SKIP) pn[c] = r_c;
     q[c] = qq;
     acc += p_c * qq;
     tz_m = Tz[c];
     r_m = r_c;
     r_c = r_p;
+    m_c = m_p;
+    b_c = ip.po;
     c = cp;
   }
   return acc;
@@ -628,38 +719,31 @@ __device__ __forceinline__ double spmv_column(
 
 template <bool LAZY, int KM>
 __global__ __launch_bounds__(kBlock) void k_spmv_p(Tables T, TileList TL) {
-  using D = DirT<KM>;
   int tid;
   const Tile t = get_tile(TL, tid);
   const Scal &sc = T.sc[t.prob];
   if (!sc.active) return;
   const LevelDev L = T.lv[t.prob];
   const ProbDev P = T.pd[t.prob];
-  const double beta = sc.beta, alpha = sc.alpha, zs = sc.zscale, ps = sc.pscale;
-  const ZT<KM> *z;
-  const D *po;
-  D *pn;
-  if constexpr (KM == KM_FP64) z = P.z;
-  else z = P.z32;
-  if constexpr (KM == KM_MIX32) {
-    po = sc.pbuf ? P.pf1 : P.pf0;
-    pn = sc.pbuf ? P.pf0 : P.pf1;
-  } else {
-    po = sc.pbuf ? P.p1 : P.p0;
-    pn = sc.pbuf ? P.p0 : P.p1;
-  }
   const Col col = tile_col(t);
   double pq = 0.0;
   if (col.on) {
-    if (LAZY && sc.xlag)
-      pq = spmv_column<true, true, KM>(t, col, L.nx, L.ny, L.nz, beta, z, zs, po, ps,
-                                       pn, P.q, L.Tx, L.Ty, L.Tz, L.diag, alpha, P.x);
-    else if (beta != 0.0)
-      pq = spmv_column<true, false, KM>(t, col, L.nx, L.ny, L.nz, beta, z, zs, po, ps,
-                                        pn, P.q, L.Tx, L.Ty, L.Tz, L.diag, 0.0, P.x);
-    else
-      pq = spmv_column<false, false, KM>(t, col, L.nx, L.ny, L.nz, beta, z, zs, po,
-                                         ps, pn, P.q, L.Tx, L.Ty, L.Tz, L.diag, 0.0, P.x);
+    auto run = [&](auto S) {
+      return spmv_column(t, col, L.nx, L.ny, L.nz, S, dir_next<KM>(P, sc), P.q, L.Tx, L.Ty,
+                         L.Tz, L.diag, P.x);
+    };
+    if constexpr (LAZY) {
+      if (sc.lag) {
+        if (sc.hasb) pq = run(dir_src<F_STORE, true, KM>(P, sc));
+        else pq = run(dir_src<F_STORE, false, KM>(P, sc));
+      } else {
+        if (sc.hasb) pq = run(dir_src<F_SKIP, true, KM>(P, sc));
+        else pq = run(dir_src<F_SKIP, false, KM>(P, sc));
+      }
+    } else {
+      if (sc.beta != 0.0) pq = run(dir_src<F_PLAIN, true, KM>(P, sc));
+      else pq = run(dir_src<F_PLAIN, false, KM>(P, sc));
+    }
   }
   write_partials(T, tid, pq, 0.0);
 }
@@ -677,44 +761,30 @@ __global__ __launch_bounds__(kBlock) void k_spmv_p(Tables T, TileList TL) {
 // arithmetic is spmv_column's, term by term, so q and p are the same.
 constexpr int kSpRows = 4;
 
-template <bool BETA, bool LAZY, int KM>
+template <int F, bool BASE, int KM>
 __device__ __forceinline__ double spmv_rows(
-    const Tile &t, int lx, int i, int j0, int nr, int nx, int ny, int nz, double beta,
-    const ZT<KM> *__restrict__ z, double zs, const DirT<KM> *__restrict__ po,
-    double ps, DirT<KM> *__restrict__ pn, double *__restrict__ q,
+    const Tile &t, int lx, int i, int j0, int nr, int nx, int ny, int nz,
+    const DirSrc<F, BASE, KM> &S, DirT<KM> *__restrict__ pn, double *__restrict__ q,
     const double *__restrict__ Tx, const double *__restrict__ Ty,
-    const double *__restrict__ Tz, const double *__restrict__ Dg, double alpha_old,
-    double *__restrict__ x) {
+    const double *__restrict__ Tz, const double *__restrict__ Dg, double *__restrict__ x) {
   using D = DirT<KM>;
-  const double cb = KM == KM_MIX32 ? beta * ps / zs : beta;
-  // p_new as stored, from z and p_old at a cell
-  auto mk = [&](ZT<KM> zv, D pv) -> D {
-    if constexpr (KM == KM_MIX32)
-      return BETA ? (float)((double)zv + cb * (double)pv) : zv;
-    else if constexpr (KM == KM_MIX64)
-      return BETA ? zs * (double)zv + beta * pv : zs * (double)zv;
-    else return BETA ? zv + beta * pv : zv;
-  };
-  auto raw = [&](int g) -> D { return mk(z[g], BETA ? po[g] : (D)0); };
-  auto val = [&](D v) -> double {
-    if constexpr (KM == KM_MIX32) return zs * (double)v;
-    else return v;
-  };
   const int plane = nx * ny;
   const int dxm = (i == 0) ? nx - 1 : -1, dxp = (i == nx - 1) ? 1 - nx : 1;
   const bool ledge = lx == 0, redge = lx == t.tx - 1;
   const int rlo = (j0 == 0 ? ny - 1 : j0 - 1) * nx;        // the row below
   const int rhi = (j0 + nr == ny ? 0 : j0 + nr) * nx;      // the row above
   const int km0 = t.z0 == 0 ? nz - 1 : t.z0 - 1;
-  D pm[kSpRows], pc[kSpRows], oc[kSpRows];  // p_new at k - 1, k; p_old at k
+  D pm[kSpRows], pc[kSpRows];  // p at k - 1, k
+  D oc[kSpRows], mc[kSpRows];  // base and (F_STORE) p_k at k
   double tzm[kSpRows];
 #pragma unroll
   for (int r = 0; r < kSpRows; ++r) {
     if (r < nr) {
       const int o = (j0 + r) * nx + i, c = t.z0 * plane + o;
-      pm[r] = raw(km0 * plane + o);
-      oc[r] = BETA ? po[c] : (D)0;
-      pc[r] = mk(z[c], oc[r]);
+      pm[r] = S.raw(km0 * plane + o);
+      const auto in = S.load(c);
+      oc[r] = in.po;
+      pc[r] = S.make(in, mc[r]);
       tzm[r] = Tz[km0 * plane + o];
     }
   }
@@ -722,36 +792,33 @@ __device__ __forceinline__ double spmv_rows(
   for (int k = t.z0; k < t.z0 + t.tz; ++k) {
     const int kp = (k == nz - 1) ? 0 : k + 1;
     const int b = k * plane + i;
-    D pp[kSpRows], op[kSpRows];
+    D pp[kSpRows], op[kSpRows], mp[kSpRows];
 #pragma unroll
     for (int r = 0; r < kSpRows; ++r) {
       if (r < nr) {
-        const int g = kp * plane + (j0 + r) * nx + i;
-        op[r] = BETA ? po[g] : (D)0;
-        pp[r] = mk(z[g], op[r]);
+        const auto in = S.load(kp * plane + (j0 + r) * nx + i);
+        op[r] = in.po;
+        pp[r] = S.make(in, mp[r]);
       }
     }
-    const D plo = raw(b + rlo), phi = raw(b + rhi);
+    const D plo = S.raw(b + rlo), phi = S.raw(b + rhi);
     double tyd = Ty[b + rlo];  // the -y face of the next row
 #pragma unroll
     for (int r = 0; r < kSpRows; ++r) {
       if (r < nr) {
         const int c = b + (j0 + r) * nx;
         D xl = __shfl_up(pc[r], 1, 64), xr = __shfl_down(pc[r], 1, 64);
-        if (ledge) xl = raw(c + dxm);
-        if (redge) xr = raw(c + dxp);
+        if (ledge) xl = S.raw(c + dxm);
+        if (redge) xr = S.raw(c + dxp);
         const D dn = r == 0 ? plo : pc[r > 0 ? r - 1 : 0];
         const D up = r + 1 == nr ? phi : pc[r + 1 < kSpRows ? r + 1 : r];
         const double tyc = Ty[c];
-        const double sm = Tx[c] * val(xr) + Tx[c + dxm] * val(xl) + tyc * val(up) +
-                          tyd * val(dn) + Tz[c] * val(pp[r]) + tzm[r] * val(pm[r]);
-        const double p_c = val(pc[r]);
+        const double sm = Tx[c] * S.val(xr) + Tx[c + dxm] * S.val(xl) + tyc * S.val(up) +
+                          tyd * S.val(dn) + Tz[c] * S.val(pp[r]) + tzm[r] * S.val(pm[r]);
+        const double p_c = S.val(pc[r]);
         const double qq = Dg[c] * p_c - sm;
-        if constexpr (LAZY) {
-          if constexpr (KM == KM_MIX32) x[c] = x[c] + alpha_old * (ps * (double)oc[r]);
-          else x[c] = x[c] + alpha_old * oc[r];
-        }
-        pn[c] = pc[r];
+        if constexpr (F == F_STORE) x[c] = S.advance(x[c], oc[r], mc[r]);
+        if constexpr (F != F_SKIP) pn[c] = pc[r];
         q[c] = qq;
         acc += p_c * qq;
         tzm[r] = Tz[c];
@@ -764,64 +831,55 @@ __device__ __forceinline__ double spmv_rows(
         pm[r] = pc[r];
         pc[r] = pp[r];
         oc[r] = op[r];
+        mc[r] = mp[r];
       }
     }
   }
   return acc;
 }
 
-template <bool LAZY, int KM>
+template <int KM>
 __global__ __launch_bounds__(kBlock) void k_spmv_f(Tables T, TileList TL) {
-  using D = DirT<KM>;
   int tid;
   const Tile t = get_tile(TL, tid);
   const Scal &sc = T.sc[t.prob];
   if (!sc.active) return;
   const LevelDev L = T.lv[t.prob];
   const ProbDev P = T.pd[t.prob];
-  const double beta = sc.beta, alpha = sc.alpha, zs = sc.zscale, ps = sc.pscale;
-  const ZT<KM> *z;
-  const D *po;
-  D *pn;
-  if constexpr (KM == KM_FP64) z = P.z;
-  else z = P.z32;
-  if constexpr (KM == KM_MIX32) {
-    po = sc.pbuf ? P.pf1 : P.pf0;
-    pn = sc.pbuf ? P.pf0 : P.pf1;
-  } else {
-    po = sc.pbuf ? P.p1 : P.p0;
-    pn = sc.pbuf ? P.p0 : P.p1;
-  }
   const int lx = threadIdx.x & 63, g = threadIdx.x >> 6;
   const int nr = min(kSpRows, t.ty - kSpRows * g);
   double pq = 0.0;
   if (lx < t.tx && nr > 0) {
     const int i = t.x0 + lx, j0 = t.y0 + kSpRows * g;
-    if (LAZY && sc.xlag)
-      pq = spmv_rows<true, true, KM>(t, lx, i, j0, nr, L.nx, L.ny, L.nz, beta, z, zs, po,
-                                     ps, pn, P.q, L.Tx, L.Ty, L.Tz, L.diag, alpha, P.x);
-    else if (beta != 0.0)
-      pq = spmv_rows<true, false, KM>(t, lx, i, j0, nr, L.nx, L.ny, L.nz, beta, z, zs, po,
-                                      ps, pn, P.q, L.Tx, L.Ty, L.Tz, L.diag, 0.0, P.x);
-    else
-      pq = spmv_rows<false, false, KM>(t, lx, i, j0, nr, L.nx, L.ny, L.nz, beta, z, zs,
-                                       po, ps, pn, P.q, L.Tx, L.Ty, L.Tz, L.diag, 0.0, P.x);
+    auto run = [&](auto S) {
+      return spmv_rows(t, lx, i, j0, nr, L.nx, L.ny, L.nz, S, dir_next<KM>(P, sc), P.q, L.Tx,
+                       L.Ty, L.Tz, L.diag, P.x);
+    };
+    if (sc.lag) {
+      if (sc.hasb) pq = run(dir_src<F_STORE, true, KM>(P, sc));
+      else pq = run(dir_src<F_STORE, false, KM>(P, sc));
+    } else {
+      if (sc.hasb) pq = run(dir_src<F_SKIP, true, KM>(P, sc));
+      else pq = run(dir_src<F_SKIP, false, KM>(P, sc));
+    }
   }
   write_partials(T, tid, pq, 0.0);
 }
 
 // out = s z32 right after a mixed-form cycle (s: the scale it ran at)
-__global__ __launch_bounds__(kBlock) void k_z_out(Tables T, TileList TL,
+__global__ __launch_bounds__(kBlock) void k_z_out(Tables T, TileList TL, int fused,
                                                   double *__restrict__ out) {
   const Tile t = get_tile(TL);
   const LevelDev L = T.lv[t.prob];
   const ProbDev P = T.pd[t.prob];
-  const double zs = T.sc[t.prob].s;
+  const Scal &sc = T.sc[t.prob];
+  const double zs = sc.s;
+  const float *z = fused ? znext(P, sc) : zcur(P, sc);
   const Col col = tile_col(t);
   if (!col.on) return;
   const int plane = L.nx * L.ny;
   int c = t.z0 * plane + col.j * L.nx + col.i;
-  for (int k = 0; k < t.tz; ++k, c += plane) out[c] = (double)P.z32[c] * zs;
+  for (int k = 0; k < t.tz; ++k, c += plane) out[c] = (double)z[c] * zs;
 }
 
 // the newest direction p at cell c (after FIN_PQ has swapped the buffers)
@@ -831,8 +889,9 @@ __device__ __forceinline__ double newest_p(const ProbDev &P, const Scal &sc, int
   else return (sc.pbuf ? P.p1 : P.p0)[c];
 }
 
-// x += alpha p (the newest direction) for problems that stopped iterating
-// while the fused iteration's x update was still pending
+// the pending update of x for problems that stopped iterating in the fused
+// iteration: alpha1 base + alpha (z + beta base) where the newest direction
+// was not stored, alpha base where it was (mixed forms)
 template <int KM>
 __global__ __launch_bounds__(kBlock) void k_xfix(Tables T, TileList TL) {
   const Tile t = get_tile(TL);
@@ -840,13 +899,26 @@ __global__ __launch_bounds__(kBlock) void k_xfix(Tables T, TileList TL) {
   if (!sc.xlag || sc.phase == PH_ITER) return;
   const LevelDev L = T.lv[t.prob];
   const ProbDev P = T.pd[t.prob];
-  const double alpha = sc.alpha;
   const Col col = tile_col(t);
   if (!col.on) return;
   const int plane = L.nx * L.ny;
   int c = t.z0 * plane + col.j * L.nx + col.i;
-  for (int k = 0; k < t.tz; ++k, c += plane)
-    P.x[c] = P.x[c] + alpha * newest_p<KM>(P, sc, c);
+  if (!sc.lag) {
+    for (int k = 0; k < t.tz; ++k, c += plane)
+      P.x[c] = __builtin_fma(sc.alpha, newest_p<KM>(P, sc, c), P.x[c]);
+    return;
+  }
+  auto run = [&](auto S) {
+    S.zs1 = sc.zscale;  // the unstored direction is the newest
+    for (int k = 0; k < t.tz; ++k, c += plane) {
+      const auto in = S.load(c);
+      DirT<KM> mid;
+      const DirT<KM> p = S.make(in, mid);
+      P.x[c] = S.advance(P.x[c], in.po, p);
+    }
+  };
+  if (sc.hasb) run(dir_src<F_SKIP, true, KM>(P, sc));
+  else run(dir_src<F_SKIP, false, KM>(P, sc));
 }
 
 // x += alpha p, r -= alpha q, partial ||r||^2
@@ -1074,7 +1146,7 @@ __global__ __launch_bounds__(kBlock) void k_local(Tables T, TileList TL, int col
   const Coef<float> C = coefs<float>(L);
   const double *r = rcur(P, sc);
   const double inv_s = sc.inv_s, s = sc.s;
-  float *z = P.z32;
+  float *z = znext(P, sc);
   const int plane = L.nx * L.ny;
   double dz = 0.0;
   for (int q = threadIdx.x; q < cnt; q += kBlock) {
@@ -1263,6 +1335,7 @@ __global__ __launch_bounds__(kFinBlock) void k_fin_bb(Tables T, int mixed) {
   sc.restarts = 0;
   sc.pbuf = 0;
   sc.has_dir = sc.xlag = sc.snew = 0;
+  sc.lag = sc.hasb = sc.zbuf = 0;
   sc.fresh = 1;
   sc.committed = 0;
   sc.status = ST_OK;
@@ -1375,28 +1448,42 @@ __global__ __launch_bounds__(kFinBlock) void k_fin(Tables T, int which, int mixe
   if (threadIdx.x != 0) return;
   switch (which) {
     case FIN_RZ: {
-      sc.zscale = sc.s;  // the scale z was just formed with
       sc.rho = a0;
       sc.rzo = a1;
+      // (a failed solve keeps the z and the scale that its pending update of
+      // x is formed from)
       if (!finite(a0) || !finite(a1)) { fail(sc, ST_ENONFINITE); break; }
       if (!(a0 > 0.0)) { fail(sc, ST_ENOCONV); break; }
+      sc.zscale1 = sc.zscale;
+      sc.zscale = sc.s;  // the scale z was just formed with
+      if (mixed && alt) sc.zbuf ^= 1;  // the fused cycle wrote the other buffer
       double beta = 0.0;
       if (!sc.restart) beta = mixed ? (a0 - a1) / sc.rho_old : a0 / sc.rho_old;
+      sc.beta1 = sc.beta;
       sc.beta = beta;
       sc.restart = 0;
       sc.rho_old = a0;
       break;
     }
     case FIN_PQ:
-      sc.pscale = sc.zscale;  // the direction just formed has z's scale
       sc.pq = a0;
+      // (fused iteration: the SpMV that stores also brings x up to date)
+      if (alt && sc.lag) sc.xlag = 0;
       if (!finite(a0)) { fail(sc, ST_ENONFINITE); break; }
       if (!(a0 > 0.0)) { fail(sc, ST_ENOCONV); break; }
+      sc.alpha1 = sc.alpha;
       sc.alpha = sc.rho / a0;
-      sc.pbuf ^= 1;
+      if (alt && !sc.lag) {
+        sc.lag = 1;
+      } else {
+        sc.pscale = sc.zscale;  // the direction just stored has z's scale
+        sc.pbuf ^= 1;
+        sc.lag = 0;
+        sc.hasb = alt;
+      }
       if (alt) {
         // fused iteration: r -= alpha q happens in the next down pass, x +=
-        // alpha p in the next SpMV; the V-cycle scale changes between cycles
+        // alpha p in a later SpMV; the V-cycle scale changes between cycles
         sc.has_dir = 1;
         sc.xlag = 1;
         if (sc.snew) {
@@ -1428,7 +1515,7 @@ __global__ __launch_bounds__(kFinBlock) void k_fin(Tables T, int which, int mixe
       }
       break;
     case FIN_XFIX:
-      sc.xlag = 0;
+      sc.xlag = sc.lag = sc.hasb = 0;
       break;
     case FIN_FRESH:
       sc.fresh = 0;
@@ -1469,6 +1556,7 @@ __global__ __launch_bounds__(kFinBlock) void k_fin(Tables T, int which, int mixe
         sc.restart = 1;
         sc.restarts += 1;
         sc.has_dir = sc.snew = 0;
+        sc.lag = sc.hasb = 0;
         sc.fresh = 1;
         set_scale(sc, P.n, mixed);
       } else {
@@ -1485,6 +1573,7 @@ __global__ __launch_bounds__(kFinBlock) void k_fin(Tables T, int which, int mixe
       sc.active = 1;
       sc.phase = PH_ITER;
       sc.has_dir = sc.xlag = sc.snew = sc.fresh = 0;
+      sc.lag = sc.hasb = sc.zbuf = 0;
       set_scale(sc, P.n, mixed);
       break;
   }
@@ -1631,8 +1720,8 @@ void launch_prolong_black(const Tables &T, TileList L, int l, int prec,
 
 void launch_spmv_f(const Tables &T, TileList F0, int km, hipStream_t s) {
   if (!F0.nblocks) return;
-  if (km == KM_MIX64) LAUNCH(K_SPMV_PX, (k_spmv_f<true, KM_MIX64>), F0.nblocks, kBlock, s, T, F0);
-  else LAUNCH(K_SPMV_PX, (k_spmv_f<true, KM_MIX32>), F0.nblocks, kBlock, s, T, F0);
+  if (km == KM_MIX64) LAUNCH(K_SPMV_PX, k_spmv_f<KM_MIX64>, F0.nblocks, kBlock, s, T, F0);
+  else LAUNCH(K_SPMV_PX, k_spmv_f<KM_MIX32>, F0.nblocks, kBlock, s, T, F0);
 }
 
 void launch_spmv_p(const Tables &T, TileList L0, int lazy, int km, hipStream_t s) {
@@ -1644,15 +1733,14 @@ void launch_spmv_p(const Tables &T, TileList L0, int lazy, int km, hipStream_t s
   else LAUNCH(K_SPMV_P, (k_spmv_p<false, KM_FP64>), L0.nblocks, kBlock, s, T, L0);
 }
 
-void launch_z_out(const Tables &T, TileList L0, double *out, hipStream_t s) {
-  if (L0.nblocks) LAUNCH(K_APPLY, k_z_out, L0.nblocks, kBlock, s, T, L0, out);
+void launch_z_out(const Tables &T, TileList L0, int fused, double *out, hipStream_t s) {
+  if (L0.nblocks) LAUNCH(K_APPLY, k_z_out, L0.nblocks, kBlock, s, T, L0, fused, out);
 }
 
 void launch_xfix(const Tables &T, TileList L0, int km, hipStream_t s) {
   if (!L0.nblocks) return;
   if (km == KM_MIX32) LAUNCH(K_XFIX, k_xfix<KM_MIX32>, L0.nblocks, kBlock, s, T, L0);
-  else if (km == KM_MIX64) LAUNCH(K_XFIX, k_xfix<KM_MIX64>, L0.nblocks, kBlock, s, T, L0);
-  else LAUNCH(K_XFIX, k_xfix<KM_FP64>, L0.nblocks, kBlock, s, T, L0);
+  else LAUNCH(K_XFIX, k_xfix<KM_MIX64>, L0.nblocks, kBlock, s, T, L0);
 }
 
 void launch_update(const Tables &T, TileList L0, int km, hipStream_t s) {
