@@ -42,15 +42,17 @@ BYTES_PER_CELL = {
     "spmv_p": (64.0, 52.0),
     # fused iteration's SpMV, the mean of its two forms: z, p_old and the
     # operator in, q out (48 B); the same with the previous z, and p and x
-    # written too (72 B)
-    "spmv_px": (80.0, 60.0),
+    # written too (72 B); FP64 form: 56 and 88 B
+    "spmv_px": (72.0, 60.0),
     # the deferred update of x when a solve stops iterating (mean of the two
     # forms)
-    "xfix": (24.0, 22.0),
+    "xfix": (28.0, 22.0),
     # Galerkin warm guess: x0 and r = b - A x0 from the operator, b and the
     # two dE (72 B), less the x and r the assembly then leaves to it (16 B)
     "warm_x": (56.0, 56.0),
     "update": (48.0, 44.0),
+    # FP64 form of the fused cycle's iterations: r -= alpha q alone
+    "update_r": (24.0, 24.0),
     "pre0_fine": (48.0, 28.0),
     "half_fine": (56.0, 32.0),
     # mixed: reads the old FP32 z (flexible PCG) and writes the new one
@@ -152,15 +154,15 @@ def model_step_bytes(cells, iters, nu, prec_idx, levels, steps=1, warm=False,
         # and the x update in the SpMV
         per_iter = B["vdown_fine"] + B["vup_fine"] + cf * coarse + B["spmv_px"]
     elif nu == 1:
-        per_iter = (B["vdown_fine"] + B["vup_fine"] + cf * coarse + B["spmv_p"]
-                    + B["update"])
+        per_iter = (B["vdown_fine"] + B["vup_fine"] + cf * coarse + B["spmv_px"]
+                    + B["update_r"])
     else:
         fine = (B["pre0_fine"] + B["resid_restrict_fine"] + B["prolong_black_fine"]
                 + B["half_out"] + (4 * (nu - 1)) * B["half_fine"])
         per_iter = fine + cf * coarse + B["spmv_p"] + B["update"]
     coarsen = 32.0 * (1.0 + cf - 8.0 ** -(levels - 1)) + (48.0 if prec_idx else 32.0) * cf
     fixed = B["assemble"] + coarsen + B["true_resid"] + B["update_E"]
-    if nu == 1 and prec_idx == 1:
+    if nu == 1:
         fixed += B["xfix"]
     if prec_idx == 1:
         fixed -= OLD_Z_BYTES  # no old z in the first cycle of the solve
@@ -218,20 +220,20 @@ PMC_KERNELS = {
     # of them, else on the 64 x 4 tiles (the first name that ran is taken)
     ("spmv_px", "mixed_dir64"): ("fld::k_spmv_f<2>", "fld::k_spmv_p<true, 2>"),
     ("spmv_px", "mixed"): ("fld::k_spmv_f<1>", "fld::k_spmv_p<true, 1>"),
-    ("spmv_p", "fp64"): "fld::k_spmv_p<false, 0>",
+    ("spmv_px", "fp64"): "fld::k_spmv_p<true, 0>",
     ("vup_fine", "mixed"): "fld::k_vup<float, true, false>",
     ("vup_fine", "mixed_tri"): "fld::k_vup<float, true, true>",
     ("vup_fine", "fp64"): "fld::k_vup<double, true, false>",
     ("vdown_fine", "mixed"): "fld::k_vdown<float, true>",
     ("vdown_fine", "fp64"): "fld::k_vdown<double, true>",
-    ("update", "fp64"): "fld::k_update<0>",
+    ("update_r", "fp64"): "fld::k_update<0, false>",
     ("true_resid", "any"): "fld::k_true_resid",
     ("assemble", "any"): "fld::k_assemble",
     ("local", "mixed"): "fld::k_local",
     ("lmask", "mixed"): "fld::k_lmask",
 }
 PMC_SOURCES = {
-    "fld_kernels.hip": ("spmv_px", "spmv_p", "update", "true_resid", "assemble", "local",
+    "fld_kernels.hip": ("spmv_px", "update_r", "true_resid", "assemble", "local",
                         "lmask"),
     "fld_fused.hip": ("vup_fine", "vdown_fine"),
 }

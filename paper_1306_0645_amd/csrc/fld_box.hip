@@ -395,8 +395,8 @@ __global__ __launch_bounds__(kBlock) void k_bup(Tables T, TileList TL, int l, in
           znext(P, sc)[g] = v0;
           znext(P, sc)[g + 1] = v1;
         } else {
-          P.z[g] = w0;
-          P.z[g + 1] = w1;
+          znext<R>(P, sc)[g] = w0;
+          znext<R>(P, sc)[g + 1] = w1;
         }
       } else {
         ((R *)L.x)[g] = v0;

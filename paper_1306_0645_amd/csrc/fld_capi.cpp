@@ -273,11 +273,11 @@ fld_status fld_precondition(fld_handle *h, const double *r, double *z) {
   launch_set_r(e.T, e.all.fine, r, e.mixed, e.stream);
   launch_fin(e.T, FIN_SETR, e.mixed, e.stream);
   e.enqueue_vcycle(e.all);
-  const ProbDev &P = e.mem[0].pd;
+  const ProbDev &P = e.h_pd[0];
   if (e.mixed) {
     launch_z_out(e.T, e.all.fine, e.fused, z, e.stream);
     if (hipGetLastError() != hipSuccess) return FLD_EDEVICE;
-  } else if (hipMemcpyAsync(z, P.z, nb, hipMemcpyDeviceToDevice, e.stream) != hipSuccess) {
+  } else if (hipMemcpyAsync(z, e.fused ? P.zb : P.z, nb, hipMemcpyDeviceToDevice, e.stream) != hipSuccess) {
     return FLD_EDEVICE;
   }
   int st = e.download_sc();  // also syncs

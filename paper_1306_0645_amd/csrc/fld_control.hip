@@ -50,6 +50,7 @@ __device__ void next_substep(const Tables &T, int p, CtlDev &c, const CtlParams 
     P.x = P.xb[nxt];
     c.xold = a;
     c.xcur = nxt;
+    if (P.zb) P.zb = P.xb[spare_buffer(nxt, a)];
   }
   const bool last = c.dt - (c.t + c.h) <= 1e-12 * c.dt;
   c.target = (!c.in_work && last) ? 1 : 2;

@@ -246,13 +246,17 @@ __device__ __forceinline__ double *rnext(const ProbDev &P, const Scal &sc) {
   return sc.rbuf ? P.r : P.r2;
 }
 
-// mixed form: the newest z (after FIN_RZ), and the buffer that the fused
-// cycle's post-sweep writes
-__device__ __forceinline__ float *zcur(const ProbDev &P, const Scal &sc) {
-  return sc.zbuf ? P.z32b : P.z32;
+// the newest z (after FIN_RZ), and the buffer that the fused cycle's
+// post-sweep writes
+template <typename R = float>
+__device__ __forceinline__ R *zcur(const ProbDev &P, const Scal &sc) {
+  if constexpr (sizeof(R) == 4) return sc.zbuf ? P.z32b : P.z32;
+  else return sc.zbuf ? P.zb : P.z;
 }
-__device__ __forceinline__ float *znext(const ProbDev &P, const Scal &sc) {
-  return sc.zbuf ? P.z32 : P.z32b;
+template <typename R = float>
+__device__ __forceinline__ R *znext(const ProbDev &P, const Scal &sc) {
+  if constexpr (sizeof(R) == 4) return sc.zbuf ? P.z32 : P.z32b;
+  else return sc.zbuf ? P.z : P.zb;
 }
 
 template <typename R, bool L0>

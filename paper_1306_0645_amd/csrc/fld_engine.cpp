@@ -438,7 +438,8 @@ int Engine::setup(const fld_params &p, hipStream_t s,
     h_pd[i].t1 = h_pd[i].t0 + hier[i].tiles[0];
     h_pd[i].f0 = fbeg[(size_t)i * kMaxLevels];
     h_pd[i].f1 = h_pd[i].f0 + hier[i].ftiles[0];
-    h_pd[i].spf = spmv_on_fused(hier[i]) ? 1 : 0;
+    h_pd[i].spf = mixed && spmv_on_fused(hier[i]) ? 1 : 0;
+    set_x(i);
     h_sc[i].phase = PH_DONE;
     h_sc[i].tol2 = prm.rtol * prm.rtol;
     h_sc[i].max_iter = prm.max_iter;
@@ -723,7 +724,8 @@ void Engine::enqueue_vcycle(const ListSet &ls) {
 // after the finest down pass, which the previous unit (or, for a problem
 // starting or restarting, enqueue_prologue) has done, so the host sees a
 // converged problem at the end of a batch instead of one unit later.  The
-// other forms update x and r in a pass of their own.
+// FP64 form of the fused cycle updates r in a pass of its own and x in the
+// SpMV; the other cycles update both in a pass of their own.
 void Engine::enqueue_iteration(const ListSet &ls) {
   if (lazy) {
     enqueue_fused_rest(ls);
@@ -737,10 +739,10 @@ void Engine::enqueue_iteration(const ListSet &ls) {
     return;
   }
   enqueue_vcycle(ls);
-  launch_fin(T, FIN_RZ, mixed, stream, fused ? 1 : 0);
-  launch_spmv_p(T, ls.fine, 0, kmode(), stream);
-  launch_fin(T, FIN_PQ, mixed, stream, 0);
-  launch_update(T, ls.fine, kmode(), stream);
+  launch_fin(T, FIN_RZ, mixed, stream, fused);
+  launch_spmv_p(T, ls.fine, fused, kmode(), stream);
+  launch_fin(T, FIN_PQ, mixed, stream, fused);
+  launch_update(T, ls.fine, kmode(), fused, stream);
   launch_fin(T, FIN_RR, mixed, stream);
 }
 
@@ -876,10 +878,17 @@ bool Engine::set_warm(int p, double h) {
   while (nxt == a || nxt == b) ++nxt;
   S.h1 = mem[p].xb[a];
   S.h2 = two ? mem[p].xb[b] : nullptr;
-  mem[p].pd.x = h_pd[p].x = mem[p].xb[nxt];
   xold[p] = a;
   xcur[p] = nxt;
+  set_x(p);
   return true;
+}
+
+// the iterate, and the FP64 form's second z in the dE buffer that is neither
+// the iterate nor the newest history entry
+void Engine::set_x(int p) {
+  mem[p].pd.x = h_pd[p].x = mem[p].xb[xcur[p]];
+  if (!mixed) h_pd[p].zb = mem[p].xb[spare_buffer(xcur[p], xold[p])];
 }
 
 // After the assembly of warm-started problems: the Galerkin guess and its
@@ -1055,7 +1064,7 @@ void Engine::enqueue_unit(const ListSet &ls, const CtlParams &cp) {
     launch_fin(T, FIN_FRESH, mixed, stream);
   }
   enqueue_iteration(ls);
-  if (lazy) {
+  if (fused) {
     launch_xfix(T, ls.fine, kmode(), stream);
     launch_fin(T, FIN_XFIX, mixed, stream);
   }

@@ -162,6 +162,7 @@ class Engine {
   // switch the V-cycle sweep counts (re-captures the graph next solve)
   int set_switched(bool on);
   bool set_warm(int p, double h);
+  void set_x(int p);
   void note_success(int p, double h);
   int upload_pd();
   int trilinear() const;

@@ -604,8 +604,8 @@ __global__ __launch_bounds__(kBlock, 3) void k_vup(Tables T, TileList TL, int l,
   // the mixed form keeps z as the cycle's FP32 output, z = zscale z32
   const bool rd_old = flexible && !sc.restart;
   const double zs_old = sc.zscale;
-  const float *zold = zcur(P, sc);
-  float *znew = znext(P, sc);
+  const R *zold = zcur<R>(P, sc);
+  R *znew = znext<R>(P, sc);
   __shared__ R vs[3][kE2];
   __shared__ R xs[3][kE1];
   // trilinear: the coarse planes under the tile, a ring of 3 (corr_lds); the
@@ -748,8 +748,8 @@ __global__ __launch_bounds__(kBlock, 3) void k_vup(Tables T, TileList TL, int l,
           st2(znew + o0, v00, v10);
           st2(znew + o0 + nx, v01, v11);
         } else {
-          st2(P.z + o0, z00, z10);
-          st2(P.z + o0 + nx, z01, z11);
+          st2(znew + o0, z00, z10);
+          st2(znew + o0 + nx, z01, z11);
         }
       } else {
         st2(xout + o0, v00, v10);

@@ -51,7 +51,11 @@ struct LevelDev {
 struct ProbDev {
   int nx, ny, nz, n;
   double *x, *r, *q, *b;
-  double *z;             // FP64 form (null in the mixed form)
+  // FP64 form (null in the mixed form): z, and the buffer that the fused
+  // cycle alternates with, the dE buffer that holds neither the iterate nor
+  // the newest history entry (the assembly and the warm start, which read the
+  // older one, are done when the first cycle writes it)
+  double *z, *zb;
   double *p0, *p1;       // FP64 direction (FP64 form; mixed with direction_fp64)
   // mixed form: the V-cycle's FP32 output as it is, z = zscale * z32, and
   // the search direction either in FP32 at the scale of the z it was formed
@@ -76,6 +80,13 @@ struct ProbDev {
   double *xb[3];         // the dE buffers (iterate and warm-start history)
   double *Ework;         // working copy of E while a step is subcycled
 };
+
+// the dE buffer (of three) that is neither cur nor old (old may be -1)
+__host__ __device__ inline int spare_buffer(int cur, int old) {
+  int k = 0;
+  while (k == cur || k == old) ++k;
+  return k;
+}
 
 // Per-step inputs of one problem (uploaded by the host at each assembly).
 struct StepDev {
@@ -193,7 +204,7 @@ enum : int {
   K_UPDATE_E, K_VDOWN_F, K_VDOWN_C, K_VUP_F, K_VUP_C, K_CHEM_H, K_ION_SUM,
   K_WARM_REVERT, K_JACOBI0_F, K_JACOBI_F, K_JACOBI_OUT,
   K_JACOBI_C, K_PROLONG_ADD_F, K_PROLONG_ADD_C, K_SPMV_PX, K_XFIX, K_WARM_X,
-  K_LMASK, K_LOCAL, K_CONTROL, K_COPY_E, K_NUM
+  K_LMASK, K_LOCAL, K_CONTROL, K_COPY_E, K_UPDATE_R, K_NUM
 };
 
 // Brackets one launch with hipEvents when its kernel id is selected.
@@ -246,7 +257,7 @@ void launch_prolong_add(const Tables &T, TileList L, int l, int prec,
 // Krylov storage of the finest level (Engine::kmode): 0 = FP64 z and p,
 // 1 = mixed form with FP32 z and p (each at a per-problem scale), 2 = mixed
 // form with FP32 z and an FP64 search direction p
-// lazy = 1 (mixed forms): the fused iteration's SpMV, which stores the
+// lazy = 1: the SpMV of the fused cycle's iterations, which stores the
 // direction and updates x every other time; launch_spmv_f: the same on the
 // finest fused tiles, its partials summed over the fused range
 void launch_spmv_f(const Tables &T, TileList F0, int km, hipStream_t s);
@@ -255,7 +266,8 @@ void launch_spmv_p(const Tables &T, TileList L0, int lazy, int km, hipStream_t s
 void launch_z_out(const Tables &T, TileList L0, int fused, double *out, hipStream_t s);
 // x += alpha p for problems that stopped iterating with the update pending
 void launch_xfix(const Tables &T, TileList L0, int km, hipStream_t s);
-void launch_update(const Tables &T, TileList L0, int km, hipStream_t s);
+// r -= alpha q, and x += alpha p unless x is updated in the SpMV (r_only)
+void launch_update(const Tables &T, TileList L0, int km, int r_only, hipStream_t s);
 void launch_true_resid(const Tables &T, TileList L0, hipStream_t s);
 void launch_warm_revert(const Tables &T, TileList L0, hipStream_t s);
 // x0 = c1 dE(n) + c2 dE(n-1), r = b - A x0 (Galerkin warm guesses)

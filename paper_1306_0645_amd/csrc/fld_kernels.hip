@@ -564,7 +564,7 @@ __global__ __launch_bounds__(kBlock) void k_prolong_add(Tables T, TileList TL,
 // direction): z FP32 at the scale zs (the V-cycle's output as it is), p_old
 // and p FP64.
 //
-// The fused iteration (mixed forms) stores the direction every other time:
+// The iterations of the fused cycle store the direction every other time:
 //   F_SKIP:  p_k = z_k + beta_k base; neither p nor x is written;
 //   F_STORE: p_k again from z_k (kept in the other z buffer) and the base,
 //            p_{k+1} = z_{k+1} + beta_{k+1} p_k is stored as the next base,
@@ -572,7 +572,8 @@ __global__ __launch_bounds__(kBlock) void k_prolong_add(Tables T, TileList TL,
 // p_k comes out of the same fused multiply-adds both times, so q, x and the
 // stored directions are bit for bit those of an iteration that stores every
 // direction and updates x each time, for 52 and 80 B a cell instead of 76
-// and 76 (FP64 direction; FP32: 48 and 72 instead of 68 and 68).  Bound by
+// and 76 (FP64 direction; FP32: 48 and 72 instead of 68 and 68; in the FP64
+// form 56 and 88 instead of 64 and, in k_update, 24 of its 48).  Bound by
 // these bytes: 640^3, FP64 direction, 4252 -> 3712 us a launch (4.67 TB/s of
 // them).  F_PLAIN (the other iterations): p is stored every time, x updated
 // in k_update.
@@ -647,12 +648,8 @@ struct DirSrc {
 template <int F, bool BASE, int KM>
 __device__ __forceinline__ DirSrc<F, BASE, KM> dir_src(const ProbDev &P, const Scal &sc) {
   DirSrc<F, BASE, KM> S;
-  if constexpr (KM == KM_FP64) {
-    S.z = S.z1 = P.z;
-  } else {
-    S.z = zcur(P, sc);
-    S.z1 = znext(P, sc);
-  }
+  S.z = zcur<ZT<KM>>(P, sc);
+  S.z1 = znext<ZT<KM>>(P, sc);
   if constexpr (KM == KM_MIX32) S.po = sc.pbuf ? P.pf1 : P.pf0;
   else S.po = sc.pbuf ? P.p1 : P.p0;
   S.zs = sc.zscale;
@@ -891,7 +888,7 @@ __device__ __forceinline__ double newest_p(const ProbDev &P, const Scal &sc, int
 
 // the pending update of x for problems that stopped iterating in the fused
 // iteration: alpha1 base + alpha (z + beta base) where the newest direction
-// was not stored, alpha base where it was (mixed forms)
+// was not stored, alpha base where it was
 template <int KM>
 __global__ __launch_bounds__(kBlock) void k_xfix(Tables T, TileList TL) {
   const Tile t = get_tile(TL);
@@ -921,8 +918,8 @@ __global__ __launch_bounds__(kBlock) void k_xfix(Tables T, TileList TL) {
   else run(dir_src<F_SKIP, false, KM>(P, sc));
 }
 
-// x += alpha p, r -= alpha q, partial ||r||^2
-template <int KM>
+// r -= alpha q, partial ||r||^2, and (X) x += alpha p
+template <int KM, bool X>
 __global__ __launch_bounds__(kBlock) void k_update(Tables T, TileList TL) {
   int tid;
   const Tile t = get_tile(TL, tid);
@@ -940,9 +937,8 @@ __global__ __launch_bounds__(kBlock) void k_update(Tables T, TileList TL) {
     const int plane = L.nx * L.ny;
     int c = t.z0 * plane + col.j * L.nx + col.i;
     for (int k = 0; k < t.tz; ++k, c += plane) {
-      const double pc = newest_p<KM>(P, sc, c), qc = q[c], xc = x[c], rc = r[c];
-      x[c] = xc + alpha * pc;
-      const double rn = rc - alpha * qc;
+      if constexpr (X) x[c] = x[c] + alpha * newest_p<KM>(P, sc, c);
+      const double rn = r[c] - alpha * q[c];
       r[c] = rn;
       rr += rn * rn;
     }
@@ -1456,7 +1452,7 @@ __global__ __launch_bounds__(kFinBlock) void k_fin(Tables T, int which, int mixe
       if (!(a0 > 0.0)) { fail(sc, ST_ENOCONV); break; }
       sc.zscale1 = sc.zscale;
       sc.zscale = sc.s;  // the scale z was just formed with
-      if (mixed && alt) sc.zbuf ^= 1;  // the fused cycle wrote the other buffer
+      if (alt) sc.zbuf ^= 1;  // the fused cycle wrote the other buffer
       double beta = 0.0;
       if (!sc.restart) beta = mixed ? (a0 - a1) / sc.rho_old : a0 / sc.rho_old;
       sc.beta1 = sc.beta;
@@ -1591,7 +1587,7 @@ static const char *kKernelNames[K_NUM] = {
     "vdown_coarse", "vup_fine", "vup_coarse", "chem_h", "ionized_sum",
     "warm_revert", "jacobi0_fine", "jacobi_fine", "jacobi_out",
     "jacobi_coarse", "prolong_add_fine", "prolong_add_coarse", "spmv_px",
-    "xfix", "warm_x", "lmask", "local", "control", "copy_E"};
+    "xfix", "warm_x", "lmask", "local", "control", "copy_E", "update_r"};
 
 namespace prof {
 struct Rec {
@@ -1726,7 +1722,8 @@ void launch_spmv_f(const Tables &T, TileList F0, int km, hipStream_t s) {
 
 void launch_spmv_p(const Tables &T, TileList L0, int lazy, int km, hipStream_t s) {
   if (!L0.nblocks) return;
-  if (lazy && km == KM_MIX64) LAUNCH(K_SPMV_PX, (k_spmv_p<true, KM_MIX64>), L0.nblocks, kBlock, s, T, L0);
+  if (lazy && km == KM_FP64) LAUNCH(K_SPMV_PX, (k_spmv_p<true, KM_FP64>), L0.nblocks, kBlock, s, T, L0);
+  else if (lazy && km == KM_MIX64) LAUNCH(K_SPMV_PX, (k_spmv_p<true, KM_MIX64>), L0.nblocks, kBlock, s, T, L0);
   else if (lazy) LAUNCH(K_SPMV_PX, (k_spmv_p<true, KM_MIX32>), L0.nblocks, kBlock, s, T, L0);
   else if (km == KM_MIX64) LAUNCH(K_SPMV_P, (k_spmv_p<false, KM_MIX64>), L0.nblocks, kBlock, s, T, L0);
   else if (km == KM_MIX32) LAUNCH(K_SPMV_P, (k_spmv_p<false, KM_MIX32>), L0.nblocks, kBlock, s, T, L0);
@@ -1740,14 +1737,16 @@ void launch_z_out(const Tables &T, TileList L0, int fused, double *out, hipStrea
 void launch_xfix(const Tables &T, TileList L0, int km, hipStream_t s) {
   if (!L0.nblocks) return;
   if (km == KM_MIX32) LAUNCH(K_XFIX, k_xfix<KM_MIX32>, L0.nblocks, kBlock, s, T, L0);
-  else LAUNCH(K_XFIX, k_xfix<KM_MIX64>, L0.nblocks, kBlock, s, T, L0);
+  else if (km == KM_MIX64) LAUNCH(K_XFIX, k_xfix<KM_MIX64>, L0.nblocks, kBlock, s, T, L0);
+  else LAUNCH(K_XFIX, k_xfix<KM_FP64>, L0.nblocks, kBlock, s, T, L0);
 }
 
-void launch_update(const Tables &T, TileList L0, int km, hipStream_t s) {
+void launch_update(const Tables &T, TileList L0, int km, int r_only, hipStream_t s) {
   if (!L0.nblocks) return;
-  if (km == KM_MIX32) LAUNCH(K_UPDATE, k_update<KM_MIX32>, L0.nblocks, kBlock, s, T, L0);
-  else if (km == KM_MIX64) LAUNCH(K_UPDATE, k_update<KM_MIX64>, L0.nblocks, kBlock, s, T, L0);
-  else LAUNCH(K_UPDATE, k_update<KM_FP64>, L0.nblocks, kBlock, s, T, L0);
+  if (r_only) LAUNCH(K_UPDATE_R, (k_update<KM_FP64, false>), L0.nblocks, kBlock, s, T, L0);
+  else if (km == KM_MIX32) LAUNCH(K_UPDATE, (k_update<KM_MIX32, true>), L0.nblocks, kBlock, s, T, L0);
+  else if (km == KM_MIX64) LAUNCH(K_UPDATE, (k_update<KM_MIX64, true>), L0.nblocks, kBlock, s, T, L0);
+  else LAUNCH(K_UPDATE, (k_update<KM_FP64, true>), L0.nblocks, kBlock, s, T, L0);
 }
 
 void launch_true_resid(const Tables &T, TileList L0, hipStream_t s) {

@@ -194,7 +194,7 @@ int fld_server::rebuild() {
     eng->xcur[i] = q->xcur;
     eng->xold[i] = q->xold;
     eng->warm_now[i] = q->warm_now;
-    eng->mem[i].pd.x = eng->h_pd[i].x = eng->mem[i].xb[q->xcur];
+    eng->set_x((int)i);
   }
   st = eng->upload_pd();
   if (st) return st;

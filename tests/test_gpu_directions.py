@@ -25,16 +25,16 @@ def fld():
 
 @pytest.mark.parametrize("shape,fused_tile_z", [((12, 20, 36), 0), ((24, 40, 96), 8),
                                                 ((96, 194, 320), 4)])
-@pytest.mark.parametrize("d64", [1, 0])
-def test_iterate_belongs_to_the_residual(fld, shape, fused_tile_z, d64):
+@pytest.mark.parametrize("prec,d64", [(1, 1), (1, 0), (0, 1)])
+def test_iterate_belongs_to_the_residual(fld, shape, fused_tile_z, prec, d64):
     """Boxes, marching tiles with the 64 x 4 SpMV tiles, and the fused-tile
     SpMV (2080 tiles)."""
     import torch
-    log_case("directions", shape=shape, d64=d64)
+    log_case("directions", shape=shape, prec=prec, d64=d64)
     p = synth.random_problem(shape, 66, sigma_ln=1.5, n_src=3, dt_factor=2.0)
     E, K, H = dev(p["E"]), dev(p["kappa"]), dev(p["eta"])
     for m in range(1, 7):
-        prm = params(fld, p, precision=1, direction_fp64=d64, max_iter=m, rtol=1e-13,
+        prm = params(fld, p, precision=prec, direction_fp64=d64, max_iter=m, rtol=1e-13,
                      cycle_switch=0, fused_tile_z=fused_tile_z, use_graph=m & 1)
         S = fld.Solver(shape, p["h"], prm)
         S.assemble(E, K, H, p["dt"])
