@@ -8,6 +8,7 @@
 
 #include <type_traits>
 
+#define FLD_KERNELS 1
 #include "fld_internal.h"
 
 namespace fld {

@@ -18,6 +18,20 @@ constexpr int kTailBlock = 1024;     // threads of the V-cycle tail kernel
 constexpr int kMaxLevels = 12;
 constexpr int kBoxX = 16, kBoxY = 8, kBoxZ = 4;  // largest box of a box pass
 
+// A pointer to device memory.  Device code has to say so: a pointer that it
+// reads from a table is otherwise a generic one, whose loads and stores are
+// flat operations.  Those count as LDS operations too, so every barrier (and
+// every wait for LDS) waited for the memory loads in flight, which undid the
+// kernels' prefetching.  (FLD_KERNELS: the file holds kernels; host code, which
+// fills the tables, sees plain pointers in both compilations.)
+#if defined(__HIP_DEVICE_COMPILE__) && defined(FLD_KERNELS)
+template <typename T>
+using gptr = __attribute__((address_space(1))) T *;
+#else
+template <typename T>
+using gptr = T *;
+#endif
+
 // Status values (same numbers as the public fld_status).
 enum : int {
   ST_OK = 0,
@@ -39,46 +53,46 @@ enum : int {
 // One multigrid level of one problem.
 struct LevelDev {
   int nx, ny, nz, n;
-  double *Tx, *Ty, *Tz, *diag;       // FP64: -A_{p,p+e_d} on +faces; A_pp
-  float *Tx32, *Ty32, *Tz32, *diag32;// FP32 copies (mixed precision)
-  void *x;                           // V-cycle iterate (level precision);
+  gptr<double> Tx, Ty, Tz, diag;     // FP64: -A_{p,p+e_d} on +faces; A_pp
+  gptr<float> Tx32, Ty32, Tz32, diag32; // FP32 copies (mixed precision)
+  gptr<void> x;                      // V-cycle iterate (level precision);
                                      // finest level FP64 mode: aliases z
-  void *f;                           // V-cycle right-hand side (levels >= 1)
-  void *x2;                          // second iterate buffer (Jacobi smoother)
+  gptr<void> f;                      // V-cycle right-hand side (levels >= 1)
+  gptr<void> x2;                     // second iterate buffer (Jacobi smoother)
 };
 
 // One problem's finest-level Krylov state.
 struct ProbDev {
   int nx, ny, nz, n;
-  double *x, *r, *q, *b;
+  gptr<double> x, r, q, b;
   // FP64 form (null in the mixed form): z, and the buffer that the fused
   // cycle alternates with, the dE buffer that holds neither the iterate nor
   // the newest history entry (the assembly and the warm start, which read the
   // older one, are done when the first cycle writes it)
-  double *z, *zb;
-  double *p0, *p1;       // FP64 direction (FP64 form; mixed with direction_fp64)
+  gptr<double> z, zb;
+  gptr<double> p0, p1;   // FP64 direction (FP64 form; mixed with direction_fp64)
   // mixed form: the V-cycle's FP32 output as it is, z = zscale * z32, and
   // the search direction either in FP32 at the scale of the z it was formed
   // from, p = pscale * pf0 (or pf1), or in FP64 in p0 / p1.  The fused
   // iteration alternates between z32 and z32b (the finest iterate buffer,
   // which its cycle does not use), so that the previous z stays readable
-  float *z32, *z32b, *pf0, *pf1;
-  double *r2;            // second residual buffer (fused V(1,1) iteration)
+  gptr<float> z32, z32b, pf0, pf1;
+  gptr<double> r2;       // second residual buffer (fused V(1,1) iteration)
   // local smoothing (mixed fused cycle): the cells whose coupling to the
   // neighbours dominates the diagonal (sum of faces > local_coupling x
   // diagonal), listed per finest tile at the tile's own cells, and the
   // counts per tile and colour, lcnt[2 (t - t0) + colour] (k_lmask); kept
   // with the problem, since a server's tables are rebuilt between the
   // assembly and the sweeps that read them
-  int *llist, *lcnt;
-  double *cs;            // coarsest-level CG scratch: 4 * n_coarsest doubles
+  gptr<int> llist, lcnt;
+  gptr<double> cs;       // coarsest-level CG scratch: 4 * n_coarsest doubles
   int levels;            // number of multigrid levels
   int t0, t1;            // range of this problem's tiles in the finest list
   int f0, f1;            // range of its fused-cycle finest tiles
   int spf;               // the fused iteration's SpMV runs on the fused tiles
   int tail;              // first level of the single-workgroup V-cycle tail
-  double *xb[3];         // the dE buffers (iterate and warm-start history)
-  double *Ework;         // working copy of E while a step is subcycled
+  gptr<double> xb[3];    // the dE buffers (iterate and warm-start history)
+  gptr<double> Ework;    // working copy of E while a step is subcycled
 };
 
 // the dE buffer (of three) that is neither cur nor old (old may be -1)
@@ -90,8 +104,8 @@ __host__ __device__ inline int spare_buffer(int cur, int old) {
 
 // Per-step inputs of one problem (uploaded by the host at each assembly).
 struct StepDev {
-  const double *E, *kappa, *eta;
-  double *Eout;          // destination of E + dE (may equal E)
+  gptr<const double> E, kappa, eta;
+  gptr<double> Eout;     // destination of E + dE (may equal E)
   double dt, adot_a;     // dt and adot/a
   double idx, idy, idz;  // 1 / dx, 1 / dy, 1 / dz (comoving cell sizes)
   // warm start: 0: x0 = 0; 1: x0 = w1 dE(n) + w2 dE(n-1) (extrapolation);
@@ -99,7 +113,7 @@ struct StepDev {
   // new operator, (dE(i), A dE(j)) c_j = (dE(i), b)
   double warm;
   double w1, w2;
-  const double *h1, *h2; // dE(n), dE(n-1) (h2 null when w2 = 0); never P.x
+  gptr<const double> h1, h2; // dE(n), dE(n-1) (h2 null when w2 = 0); never P.x
 };
 
 // Per-problem PCG scalars (device resident, read back by the host).
@@ -141,7 +155,7 @@ struct Scal {
 // Device-side step control of one problem (fld_advance): the requested run,
 // its progress, and the warm-start history the host keeps otherwise.
 struct CtlDev {
-  double *E;             // the caller's E: E^0 in, E after the last step out
+  gptr<double> E;        // the caller's E: E^0 in, E after the last step out
   double dt0, t_end;     // step size (adaptive: the first step's); end time
   int n_steps, adaptive; // fixed steps of dt0, or steps of the controller's
                          // dt_next until t_end
@@ -173,14 +187,14 @@ struct Tile {
 enum : int { AS_BB, AS_RR, AS_G11, AS_G12, AS_G22, AS_B1, AS_B2, kAsmSums };
 
 struct Tables {
-  LevelDev *lv;     // [kMaxLevels][nprob]
-  ProbDev *pd;      // [nprob]
-  StepDev *sd;      // [nprob]
-  Scal *sc;         // [nprob]
-  double *part;     // [n finest tiles, standard then fused][2] block partial sums
-  double *lpart;    // [n finest standard tiles][2] the local sweeps' r.z changes
-  CtlDev *ctl;      // [nprob] device-side step control
-  double *gpart;    // [n finest standard tiles][kAsmSums] sums of the assembly
+  gptr<LevelDev> lv; // [kMaxLevels][nprob]
+  gptr<ProbDev> pd; // [nprob]
+  gptr<StepDev> sd; // [nprob]
+  gptr<Scal> sc;    // [nprob]
+  gptr<double> part; // [n finest tiles, standard then fused][2] block partial sums
+  gptr<double> lpart; // [n finest standard tiles][2] the local sweeps' r.z changes
+  gptr<CtlDev> ctl; // [nprob] device-side step control
+  gptr<double> gpart; // [n finest standard tiles][kAsmSums] sums of the assembly
   int nprob;
 };
 
@@ -189,8 +203,8 @@ struct Tables {
 // of its tiles; ranges are sorted by block.  nblocks = total blocks of the
 // launch.  first, prob: the tile and the problem of range 0.
 struct TileList {
-  const Tile *base;     // device: full tile table
-  const int *ranges;    // device: 3 * nranges ints
+  gptr<const Tile> base; // device: full tile table
+  gptr<const int> ranges; // device: 3 * nranges ints
   int nranges;
   int nblocks;
   int first, prob;
