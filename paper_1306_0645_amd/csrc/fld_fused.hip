@@ -67,7 +67,7 @@ __device__ __forceinline__ void st2(R *p, R u, R v) {
   Vec2<R> w;
   w.x = u;
   w.y = v;
-  *reinterpret_cast<Vec2<R> *>(p) = w;
+  stream_out(reinterpret_cast<Vec2<R> *>(p), w);
 }
 
 // in-plane faces of one quad: Tx, Ty at (a, b) (the + faces of each cell),

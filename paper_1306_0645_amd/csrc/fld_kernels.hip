@@ -128,19 +128,19 @@ __global__ __launch_bounds__(kBlock) void k_assemble(Tables T, TileList L0,
       const double LE = (Dxp * (Exp - Ec) - Dxm * (Ec - Exm)) * ix2 +
                         (Dyp * (Eyp - Ec) - Dym * (Ec - Eym)) * iy2 +
                         (Dzp * (Ep - Ec) - Dzm * (Ec - Em)) * iz2 - mu * Ec;
-      const double b = S.dt * (LE + eta[cc]);
+      const double b = S.dt * (LE + stream_in(&eta[cc]));
       const double tx = tdt * Dxp * ix2, ty = tdt * Dyp * iy2, tz = tdt * Dzp * iz2;
-      Tx[cc] = tx;
-      Ty[cc] = ty;
-      Tz[cc] = tz;
-      Dg[cc] = diag;
+      stream_out(&Tx[cc], tx);
+      stream_out(&Ty[cc], ty);
+      stream_out(&Tz[cc], tz);
+      stream_out(&Dg[cc], diag);
       if (mixed) {
-        L.Tx32[cc] = (float)tx;
-        L.Ty32[cc] = (float)ty;
-        L.Tz32[cc] = (float)tz;
-        L.diag32[cc] = (float)diag;
+        stream_out(&L.Tx32[cc], (float)tx);
+        stream_out(&L.Ty32[cc], (float)ty);
+        stream_out(&L.Tz32[cc], (float)tz);
+        stream_out(&L.diag32[cc], (float)diag);
       }
-      bv[cc] = b;
+      stream_out(&bv[cc], b);
       bb += b * b;
       if (gal) {
         // A h at the cell for h = dE(n) and dE(n-1); x and r are k_warm_x's
@@ -173,14 +173,14 @@ __global__ __launch_bounds__(kBlock) void k_assemble(Tables T, TileList L0,
                            ty * guess(cc + dyp) + tym * guess(cc + dym) +
                            tz * gp + tzm * gm;
         const double r = b - (diag * gc - off);
-        xv[cc] = gc;
-        rv[cc] = r;
+        stream_out(&xv[cc], gc);
+        stream_out(&rv[cc], r);
         rr += r * r;
         gm = gc;
         gc = gp;
       } else {
-        xv[cc] = 0.0;
-        rv[cc] = b;
+        stream_out(&xv[cc], 0.0);
+        stream_out(&rv[cc], b);
       }
       Em = Ec;
       Km = Kc;
@@ -673,7 +673,7 @@ __device__ __forceinline__ DirT<KM> *dir_next(const ProbDev &P, const Scal &sc) 
   else return sc.pbuf ? P.p0 : P.p1;
 }
 
-template <int F, bool BASE, int KM>
+template <bool NT, int F, bool BASE, int KM>
 __device__ __forceinline__ double spmv_column(
     const Tile &t, const Col &col, int nx, int ny, int nz, const DirSrc<F, BASE, KM> &S,
     DirT<KM> *__restrict__ pn, double *__restrict__ q, const double *__restrict__ Tx,
@@ -699,10 +699,10 @@ __device__ __forceinline__ double spmv_column(
                      Ty[c] * S.val(S.raw(c + dyp)) + Ty[c + dym] * S.val(S.raw(c + dym)) +
                      Tz[c] * S.val(r_p) + tz_m * S.val(r_m);
     const double p_c = S.val(r_c);
-    const double qq = Dg[c] * p_c - s;
-    if constexpr (F == F_STORE) x[c] = S.advance(x[c], b_c, m_c);
-    if constexpr (F != F_SKIP) pn[c] = r_c;
-    q[c] = qq;
+    const double qq = stream_in<NT>(&Dg[c]) * p_c - s;
+    if constexpr (F == F_STORE) stream_out<NT>(&x[c], S.advance(stream_in<NT>(&x[c]), b_c, m_c));
+    if constexpr (F != F_SKIP) stream_out<NT>(&pn[c], r_c);
+    stream_out<NT>(&q[c], qq);
     acc += p_c * qq;
     tz_m = Tz[c];
     r_m = r_c;
@@ -726,8 +726,11 @@ __global__ __launch_bounds__(kBlock) void k_spmv_p(Tables T, TileList TL) {
   double pq = 0.0;
   if (col.on) {
     auto run = [&](auto S) {
-      return spmv_column(t, col, L.nx, L.ny, L.nz, S, dir_next<KM>(P, sc), P.q, L.Tx, L.Ty,
-                         L.Tz, L.diag, P.x);
+      if (beyond_cache(L.n))
+        return spmv_column<true>(t, col, L.nx, L.ny, L.nz, S, dir_next<KM>(P, sc), P.q, L.Tx,
+                                 L.Ty, L.Tz, L.diag, P.x);
+      return spmv_column<false>(t, col, L.nx, L.ny, L.nz, S, dir_next<KM>(P, sc), P.q, L.Tx,
+                                L.Ty, L.Tz, L.diag, P.x);
     };
     if constexpr (LAZY) {
       if (sc.lag) {
@@ -813,10 +816,10 @@ __device__ __forceinline__ double spmv_rows(
         const double sm = Tx[c] * S.val(xr) + Tx[c + dxm] * S.val(xl) + tyc * S.val(up) +
                           tyd * S.val(dn) + Tz[c] * S.val(pp[r]) + tzm[r] * S.val(pm[r]);
         const double p_c = S.val(pc[r]);
-        const double qq = Dg[c] * p_c - sm;
-        if constexpr (F == F_STORE) x[c] = S.advance(x[c], oc[r], mc[r]);
-        if constexpr (F != F_SKIP) pn[c] = pc[r];
-        q[c] = qq;
+        const double qq = stream_in(&Dg[c]) * p_c - sm;
+        if constexpr (F == F_STORE) stream_out(&x[c], S.advance(stream_in(&x[c]), oc[r], mc[r]));
+        if constexpr (F != F_SKIP) stream_out(&pn[c], pc[r]);
+        stream_out(&q[c], qq);
         acc += p_c * qq;
         tzm[r] = Tz[c];
         tyd = tyc;
@@ -937,9 +940,9 @@ __global__ __launch_bounds__(kBlock) void k_update(Tables T, TileList TL) {
     const int plane = L.nx * L.ny;
     int c = t.z0 * plane + col.j * L.nx + col.i;
     for (int k = 0; k < t.tz; ++k, c += plane) {
-      if constexpr (X) x[c] = x[c] + alpha * newest_p<KM>(P, sc, c);
-      const double rn = r[c] - alpha * q[c];
-      r[c] = rn;
+      if constexpr (X) stream_out(&x[c], stream_in(&x[c]) + alpha * newest_p<KM>(P, sc, c));
+      const double rn = r[c] - alpha * stream_in(&q[c]);
+      stream_out(&r[c], rn);
       rr += rn * rn;
     }
   }
@@ -962,8 +965,8 @@ __global__ __launch_bounds__(kBlock) void k_true_resid(Tables T, TileList TL) {
     auto xv = [&](int q) { return P.x[q]; };
     for (int k = t.z0; k < t.z0 + t.tz; ++k) {
       const Nb n = nbrs(col.i, col.j, k, L.nx, L.ny, L.nz);
-      const double r = P.b[n.c] - (C.d[n.c] * P.x[n.c] - offsum(C, n, xv));
-      rcur(P, sc)[n.c] = r;
+      const double r = stream_in(&P.b[n.c]) - (stream_in(&C.d[n.c]) * P.x[n.c] - offsum(C, n, xv));
+      stream_out(&rcur(P, sc)[n.c], r);
       rr += r * r;
     }
   }
@@ -1006,9 +1009,9 @@ __global__ __launch_bounds__(kBlock) void k_warm_x(Tables T, TileList TL) {
       const double off = Tx[c] * g(c + dxp) + Tx[c + dxm] * g(c + dxm) +
                          Ty[c] * g(c + dyp) + Ty[c + dym] * g(c + dym) +
                          Tz[c] * x_p + tz_m * x_m;
-      const double r = P.b[c] - (L.diag[c] * x_c - off);
-      P.x[c] = x_c;
-      rv[c] = r;
+      const double r = stream_in(&P.b[c]) - (stream_in(&L.diag[c]) * x_c - off);
+      stream_out(&P.x[c], x_c);
+      stream_out(&rv[c], r);
       rr += r * r;
       tz_m = Tz[c];
       x_m = x_c;
@@ -1256,10 +1259,10 @@ __global__ __launch_bounds__(kBlock) void k_update_E(Tables T, TileList TL,
       const double d = P.x[c];
       dd += d * d;
       if (copy_only) {
-        S.Eout[c] = d;
+        stream_out(&S.Eout[c], d);
       } else {
-        const double en = S.E[c] + d;
-        S.Eout[c] = en;
+        const double en = stream_in(&S.E[c]) + d;
+        stream_out(&S.Eout[c], en);
         double w = fabs(en);
         w = (w < floor) ? floor : w;
         if (w > 0.0) {
