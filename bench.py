@@ -230,11 +230,9 @@ PMC_KERNELS = {
     ("true_resid", "any"): "fld::k_true_resid",
     ("assemble", "any"): "fld::k_assemble",
     ("local", "mixed"): "fld::k_local",
-    ("lmask", "mixed"): "fld::k_lmask",
 }
 PMC_SOURCES = {
-    "fld_kernels.hip": ("spmv_px", "update_r", "true_resid", "assemble", "local",
-                        "lmask"),
+    "fld_kernels.hip": ("spmv_px", "update_r", "true_resid", "assemble", "local"),
     "fld_fused.hip": ("vup_fine", "vdown_fine"),
 }
 

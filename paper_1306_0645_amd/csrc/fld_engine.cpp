@@ -619,11 +619,10 @@ void Engine::fill_step(int p, const double *E, const double *kappa,
 }
 
 void Engine::enqueue_assemble(const ListSet &ls) {
-  launch_assemble(T, ls.fine, prm.c, prm.theta, prm.d_max, prm.r_min, mixed, stream);
+  launch_assemble(T, ls.fine, prm.c, prm.theta, prm.d_max, prm.r_min, mixed,
+                  mixed && prm.local_sweeps > 0, prm.local_coupling, stream);
   for (int l = 1; l < Lmax; ++l)
     launch_coarsen(T, ls.exist[l], l, prm.coarse_scale, mixed, prm.coarse_op, stream);
-  if (mixed && prm.local_sweeps > 0)
-    launch_lmask(T, ls.fine, prm.local_coupling, stream);
   launch_fin(T, FIN_BB, mixed, stream);
   need_pro = true;
 }
@@ -1046,11 +1045,10 @@ int Engine::run_steps(std::vector<Job> &jobs) {
 // the fused iteration, one PCG iteration, the true-residual verification,
 // E += dE, the controller and the copy of a finished run's E.
 void Engine::enqueue_unit(const ListSet &ls, const CtlParams &cp) {
-  launch_assemble(T, ls.fine, prm.c, prm.theta, prm.d_max, prm.r_min, mixed, stream);
+  launch_assemble(T, ls.fine, prm.c, prm.theta, prm.d_max, prm.r_min, mixed,
+                  mixed && prm.local_sweeps > 0, prm.local_coupling, stream);
   for (int l = 1; l < Lmax; ++l)
     launch_coarsen(T, ls.exist[l], l, prm.coarse_scale, mixed, prm.coarse_op, stream);
-  if (mixed && prm.local_sweeps > 0)
-    launch_lmask(T, ls.fine, prm.local_coupling, stream);
   launch_fin(T, FIN_BB, mixed, stream);
   if (prm.warm_start > 1) {
     launch_warm_x(T, ls.fine, stream);

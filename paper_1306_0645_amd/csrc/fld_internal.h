@@ -81,7 +81,7 @@ struct ProbDev {
   // local smoothing (mixed fused cycle): the cells whose coupling to the
   // neighbours dominates the diagonal (sum of faces > local_coupling x
   // diagonal), listed per finest tile at the tile's own cells, and the
-  // counts per tile and colour, lcnt[2 (t - t0) + colour] (k_lmask); kept
+  // counts per tile and colour, lcnt[2 (t - t0) + colour] (k_assemble); kept
   // with the problem, since a server's tables are rebuilt between the
   // assembly and the sweeps that read them
   gptr<int> llist, lcnt;
@@ -218,7 +218,7 @@ enum : int {
   K_UPDATE_E, K_VDOWN_F, K_VDOWN_C, K_VUP_F, K_VUP_C, K_CHEM_H, K_ION_SUM,
   K_WARM_REVERT, K_JACOBI0_F, K_JACOBI_F, K_JACOBI_OUT,
   K_JACOBI_C, K_PROLONG_ADD_F, K_PROLONG_ADD_C, K_SPMV_PX, K_XFIX, K_WARM_X,
-  K_LMASK, K_LOCAL, K_CONTROL, K_COPY_E, K_UPDATE_R, K_NUM
+  K_LOCAL, K_CONTROL, K_COPY_E, K_UPDATE_R, K_NUM
 };
 
 // Brackets one launch with hipEvents when its kernel id is selected.
@@ -238,8 +238,10 @@ struct ProfScope {
 
 // ---- launchers (fld_kernels.hip, fld_fused.hip) ---------------------------
 // prec: 0 = FP64 V-cycle, 1 = FP32 V-cycle.
+// local: also list the strongly coupled cells (coupling) for the local sweeps
 void launch_assemble(const Tables &T, TileList L0, double c, double theta,
-                     double dmax, double rmin, int mixed, hipStream_t s);
+                     double dmax, double rmin, int mixed, int local,
+                     double coupling, hipStream_t s);
 // op: 0 = coarse faces from the 4 fine faces they cover, 1 = from the fine
 // rows through them, three faces in series (k_coarsen)
 void launch_coarsen(const Tables &T, TileList coarse, int lc, double scale,
@@ -286,11 +288,10 @@ void launch_true_resid(const Tables &T, TileList L0, hipStream_t s);
 void launch_warm_revert(const Tables &T, TileList L0, hipStream_t s);
 // x0 = c1 dE(n) + c2 dE(n-1), r = b - A x0 (Galerkin warm guesses)
 void launch_warm_x(const Tables &T, TileList L0, hipStream_t s);
-// local smoothing of the mixed fused cycle: the list of strongly coupled
-// finest cells (after the assembly), and one red/black sweep over them
+// local smoothing of the mixed fused cycle: one red/black sweep over the
+// strongly coupled finest cells that the assembly listed
 // (colour 1 = black, then 0 = red) after the finest post-sweep, in z32,
 // with the change of r.z per tile in lpart[2 t + colour]
-void launch_lmask(const Tables &T, TileList L0, double coupling, hipStream_t s);
 void launch_local(const Tables &T, TileList L0, int colour, hipStream_t s);
 // device-controlled stepping (fld_control.hip): the controller after each
 // unit's verification and commit (one block per problem), and the copy of a

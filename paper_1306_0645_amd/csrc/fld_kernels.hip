@@ -48,13 +48,88 @@ __device__ __forceinline__ double face_D(double e1, double e2, double k1,
   return (D > dmax) ? dmax : D;
 }
 
+// exclusive prefix sums of a and b over the block's threads (thread order)
+// and their totals
+__device__ __forceinline__ void block_scan2(int a, int b, int *sh, int &ea, int &eb,
+                                            int &ta, int &tb) {
+  constexpr int NW = kBlock / 64;
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  int ia = a, ib = b;
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) {
+    const int ua = __shfl_up(ia, d, 64), ub = __shfl_up(ib, d, 64);
+    if (lane >= d) {
+      ia += ua;
+      ib += ub;
+    }
+  }
+  if (lane == 63) {
+    sh[w] = ia;
+    sh[NW + w] = ib;
+  }
+  __syncthreads();
+  int oa = 0, ob = 0;
+  ta = 0;
+  tb = 0;
+#pragma unroll
+  for (int i = 0; i < NW; ++i) {
+    if (i < w) {
+      oa += sh[i];
+      ob += sh[NW + i];
+    }
+    ta += sh[i];
+    tb += sh[NW + i];
+  }
+  ea = oa + ia - a;
+  eb = ob + ib - b;
+}
+
+// index of the q-th cell of tile t's box (x fastest)
+__device__ __forceinline__ int box_cell(const Tile &t, int q, int nx, int ny) {
+  const int txy = t.tx * t.ty, lz = q / txy, rm = q - lz * txy, ly = rm / t.tx;
+  return ((t.z0 + lz) * ny + t.y0 + ly) * nx + t.x0 + (rm - ly * t.tx);
+}
+
+// the tile's listed cells (bits: the listed planes of the thread's column, m0
+// and m1 of them of colour 0 and 1) into llist and lcnt
+__device__ __forceinline__ void list_cells(const Tile &t, const Col &col, int tid,
+                                           const ProbDev &P, int nx, int ny,
+                                           unsigned long long bits, int m0, int m1) {
+  __shared__ int sh[2 * (kBlock / 64)];
+  int e0, e1, n0, n1;
+  block_scan2(m0, m1, sh, e0, e1, n0, n1);
+  while (bits) {
+    const int b = __ffsll((long long)bits) - 1;
+    bits &= bits - 1;
+    const int k = t.z0 + b;
+    const int q = ((col.i + col.j + k) & 1) ? n0 + e1++ : e0++;
+    P.llist[box_cell(t, q, nx, ny)] = (k * ny + col.j) * nx + col.i;
+  }
+  if (threadIdx.x == 0) {
+    P.lcnt[2 * (tid - P.t0)] = n0;
+    P.lcnt[2 * (tid - P.t0) + 1] = n1;
+  }
+}
+
+// edge faces of an assembly tile: kEdgeZ planes at a time, of at most 64
+// columns (or, in a tile 4 wide, 64 rows)
+constexpr int kEdgeZ = 8, kEdge = kEdgeZ * 64;
+
 // One thread per (x, y) column of the tile, walking z: E and kappa of the
 // column at k-1, k, k+1 stay in registers and the -z face of plane k is the +z
-// face computed at plane k-1, so each cell evaluates 5 limiters, not 6.
+// face computed at plane k-1.  A limiter costs some 60 instructions (three
+// divisions and a root), so the -x and -y faces are not evaluated again but
+// taken, through LDS, from the threads whose + faces they are; the tile's own
+// -x and -y edges are evaluated for 8 planes at a time: 3.5 limiters a cell in
+// a tile of 64 x 4 x 8 instead of 5.  The cells of the local sweeps are listed
+// here too (local; see k_local), where their faces are at hand.  Measured at
+// 256^3, mixed, warm: 545 + 116 us with five limiters a cell and the lists in a
+// pass of their own, 494 us together.
 __global__ __launch_bounds__(kBlock) void k_assemble(Tables T, TileList L0,
-                                                     double c, double theta,
+                                                     double c_light, double theta,
                                                      double dmax, double rmin,
-                                                     int mixed) {
+                                                     int mixed, int local,
+                                                     double coupling) {
   int tid;
   const Tile t = get_tile(L0, tid);
   const Scal &sc = T.sc[t.prob];
@@ -87,9 +162,30 @@ __global__ __launch_bounds__(kBlock) void k_assemble(Tables T, TileList L0,
   auto guess = [&](int g) { return h2 ? w1 * h1[g] + w2 * h2[g] : w1 * h1[g]; };
   double bb = 0.0, rr = 0.0, g11 = 0.0, g12 = 0.0, g22 = 0.0, gb1 = 0.0,
          gb2 = 0.0;
-  if (col.on) {
-    const int nx = L.nx, ny = L.ny, nz = L.nz, plane = nx * ny;
-    const int i = col.i, j = col.j;
+  const int nx = L.nx, ny = L.ny, nz = L.nz, plane = nx * ny;
+  __shared__ double sx[2][kBlock], sy[2][kBlock];  // Dxp, Dyp of a plane
+  __shared__ double ex[kEdge], ey[kEdge];          // edge faces [plane][row], [plane][column]
+  // -x faces of column x0 and -y faces of row y0 of the tile on planes
+  // z0 + l0 .. z0 + l0 + n - 1
+  auto edges = [&](int l0, int n) {
+    for (int q = threadIdx.x; q < n * (t.ty + t.tx); q += kBlock) {
+      const bool isx = q < n * t.ty;
+      const int u = isx ? q : q - n * t.ty, w = isx ? t.ty : t.tx;
+      const int lz = u / w, lw = u - lz * w;
+      const int i = isx ? t.x0 : t.x0 + lw, j = isx ? t.y0 + lw : t.y0;
+      const int c = (t.z0 + l0 + lz) * plane + j * nx + i;
+      const int m = isx ? (i == 0 ? c + nx - 1 : c - 1) : (j == 0 ? c + (ny - 1) * nx : c - nx);
+      const double D = face_D(E[m], E[c], K[m], K[c], isx ? S.idx : S.idy, c_light, dmax, rmin);
+      if (isx) ex[u] = D;
+      else ey[u] = D;
+    }
+  };
+  unsigned long long bits = 0;  // listed planes of the column: bit k - z0
+  int m0 = 0, m1 = 0;           // listed cells of colour 0, 1
+  const int lx = col.i - t.x0, ly = col.j - t.y0;
+  {
+    // (threads beyond the tile's rows follow row 0 up to the barriers)
+    const int i = col.i, j = col.on ? col.j : t.y0;
     const int dxm = (i == 0) ? nx - 1 : -1, dxp = (i == nx - 1) ? 1 - nx : 1;
     const int dym = (j == 0) ? (ny - 1) * nx : -nx;
     const int dyp = (j == ny - 1) ? -(ny - 1) * nx : nx;
@@ -97,7 +193,7 @@ __global__ __launch_bounds__(kBlock) void k_assemble(Tables T, TileList L0,
     const int cm = (t.z0 == 0) ? cc + (nz - 1) * plane : cc - plane;
     double Em = E[cm], Km = K[cm];
     double Ec = E[cc], Kc = K[cc];
-    double Dzm = face_D(Em, Ec, Km, Kc, S.idz, c, dmax, rmin);
+    double Dzm = face_D(Em, Ec, Km, Kc, S.idz, c_light, dmax, rmin);
     double gm = 0.0, gc = 0.0;  // guess (Galerkin: dE(n)) at planes k - 1, k
     double um = 0.0, uc = 0.0;  // Galerkin: dE(n-1) at planes k - 1, k
     if (gal) {
@@ -112,16 +208,31 @@ __global__ __launch_bounds__(kBlock) void k_assemble(Tables T, TileList L0,
       gc = guess(cc);
     }
     for (int k = t.z0; k < t.z0 + t.tz; ++k) {
+      const int lz = k - t.z0, le = lz % kEdgeZ;
+      if (le == 0) {
+        if (lz) __syncthreads();  // the last planes' edge faces are read
+        edges(lz, min(kEdgeZ, t.tz - lz));
+      }
       const int cp = (k == nz - 1) ? cc - (nz - 1) * plane : cc + plane;
       const double Ep = E[cp], Kp = K[cp];
       const double Exp = E[cc + dxp], Exm = E[cc + dxm];
       const double Eyp = E[cc + dyp], Eym = E[cc + dym];
-      const double Dxp = face_D(Ec, Exp, Kc, K[cc + dxp], S.idx, c, dmax, rmin);
-      const double Dxm = face_D(Exm, Ec, K[cc + dxm], Kc, S.idx, c, dmax, rmin);
-      const double Dyp = face_D(Ec, Eyp, Kc, K[cc + dyp], S.idy, c, dmax, rmin);
-      const double Dym = face_D(Eym, Ec, K[cc + dym], Kc, S.idy, c, dmax, rmin);
-      const double Dzp = face_D(Ec, Ep, Kc, Kp, S.idz, c, dmax, rmin);
-      const double mu = S.adot_a + c * Kc;
+      const double Dxp = face_D(Ec, Exp, Kc, K[cc + dxp], S.idx, c_light, dmax, rmin);
+      const double Dyp = face_D(Ec, Eyp, Kc, K[cc + dyp], S.idy, c_light, dmax, rmin);
+      const double Dzp = face_D(Ec, Ep, Kc, Kp, S.idz, c_light, dmax, rmin);
+      const int sl = lz & 1;
+      sx[sl][threadIdx.x] = Dxp;
+      sy[sl][threadIdx.x] = Dyp;
+      // (two slots: a plane's reads and the writes of the plane after the next
+      // are a barrier apart)
+      __syncthreads();
+      if (!col.on) {
+        cc = cp;
+        continue;
+      }
+      const double Dxm = lx > 0 ? sx[sl][threadIdx.x - 1] : ex[le * t.ty + ly];
+      const double Dym = ly > 0 ? sy[sl][threadIdx.x - t.tx] : ey[le * t.tx + lx];
+      const double mu = S.adot_a + c_light * Kc;
       const double faces =
           (Dxp + Dxm) * ix2 + (Dyp + Dym) * iy2 + (Dzp + Dzm) * iz2;
       const double diag = 1.0 + tdt * (mu + faces);
@@ -130,6 +241,12 @@ __global__ __launch_bounds__(kBlock) void k_assemble(Tables T, TileList L0,
                         (Dzp * (Ep - Ec) - Dzm * (Ec - Em)) * iz2 - mu * Ec;
       const double b = S.dt * (LE + stream_in(&eta[cc]));
       const double tx = tdt * Dxp * ix2, ty = tdt * Dyp * iy2, tz = tdt * Dzp * iz2;
+      const double txm = tdt * Dxm * ix2, tym = tdt * Dym * iy2, tzm = tdt * Dzm * iz2;
+      if (local && tx + txm + ty + tym + tz + tzm > coupling * diag) {
+        bits |= 1ull << lz;
+        if ((i + j + k) & 1) ++m1;
+        else ++m0;
+      }
       stream_out(&Tx[cc], tx);
       stream_out(&Ty[cc], ty);
       stream_out(&Tz[cc], tz);
@@ -144,8 +261,6 @@ __global__ __launch_bounds__(kBlock) void k_assemble(Tables T, TileList L0,
       bb += b * b;
       if (gal) {
         // A h at the cell for h = dE(n) and dE(n-1); x and r are k_warm_x's
-        const double txm = tdt * Dxm * ix2, tym = tdt * Dym * iy2,
-                     tzm = tdt * Dzm * iz2;
         const double gp = h1[cp];
         const double a1 = diag * gc - (tx * h1[cc + dxp] + txm * h1[cc + dxm] +
                                        ty * h1[cc + dyp] + tym * h1[cc + dym] +
@@ -167,8 +282,6 @@ __global__ __launch_bounds__(kBlock) void k_assemble(Tables T, TileList L0,
         }
       } else if (warm) {
         const double gp = guess(cp);
-        const double txm = tdt * Dxm * ix2, tym = tdt * Dym * iy2,
-                     tzm = tdt * Dzm * iz2;
         const double off = tx * guess(cc + dxp) + txm * guess(cc + dxm) +
                            ty * guess(cc + dyp) + tym * guess(cc + dym) +
                            tz * gp + tzm * gm;
@@ -192,6 +305,7 @@ __global__ __launch_bounds__(kBlock) void k_assemble(Tables T, TileList L0,
   }
   const double sums[kAsmSums] = {bb, rr, g11, g12, g22, gb1, gb2};
   write_sums(T.gpart, tid, sums);
+  if (local) list_cells(t, col, tid, P, nx, ny, bits, m0, m1);
 }
 
 // Coarse operator of level lc from level lc-1 (one thread per coarse cell).
@@ -1028,8 +1142,8 @@ __global__ __launch_bounds__(kBlock) void k_warm_x(Tables T, TileList TL) {
 // is smooth inside the bubble nearly untouched and the coarse levels, whose
 // cells mix bubble and neutral children, do not represent it; extra sweeps
 // restricted to those cells act on it at a small fraction of a full sweep's
-// cost.  k_lmask marks them once per assembly from the FP64 finest operator
-// and lists them per tile and colour; k_local runs one half-sweep of colour
+// cost.  k_assemble marks them from the FP64 finest operator and lists them
+// per tile and colour (list_cells); k_local runs one half-sweep of colour
 // `colour` over a tile's listed cells, in place in the cycle's FP32 output
 // z32, with the cycle's scaled right-hand side and FP32 coefficients, and
 // records the change of r.z that the update makes (r the FP64 residual the
@@ -1045,94 +1159,13 @@ __global__ __launch_bounds__(kBlock) void k_warm_x(Tables T, TileList TL) {
 // that colour reads only cells of the other), so k_local gives every listed
 // cell a thread of its own.
 
-// exclusive prefix sums of a and b over the block's threads (thread order)
-// and their totals
-__device__ __forceinline__ void block_scan2(int a, int b, int *sh, int &ea, int &eb,
-                                            int &ta, int &tb) {
-  constexpr int NW = kBlock / 64;
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  int ia = a, ib = b;
-#pragma unroll
-  for (int d = 1; d < 64; d <<= 1) {
-    const int ua = __shfl_up(ia, d, 64), ub = __shfl_up(ib, d, 64);
-    if (lane >= d) {
-      ia += ua;
-      ib += ub;
-    }
-  }
-  if (lane == 63) {
-    sh[w] = ia;
-    sh[NW + w] = ib;
-  }
-  __syncthreads();
-  int oa = 0, ob = 0;
-  ta = 0;
-  tb = 0;
-#pragma unroll
-  for (int i = 0; i < NW; ++i) {
-    if (i < w) {
-      oa += sh[i];
-      ob += sh[NW + i];
-    }
-    ta += sh[i];
-    tb += sh[NW + i];
-  }
-  ea = oa + ia - a;
-  eb = ob + ib - b;
-}
-
-// index of the q-th cell of tile t's box (x fastest)
-__device__ __forceinline__ int box_cell(const Tile &t, int q, int nx, int ny) {
-  const int txy = t.tx * t.ty, lz = q / txy, rm = q - lz * txy, ly = rm / t.tx;
-  return ((t.z0 + lz) * ny + t.y0 + ly) * nx + t.x0 + (rm - ly * t.tx);
-}
-
-__global__ __launch_bounds__(kBlock) void k_lmask(Tables T, TileList TL,
-                                                  double coupling) {
-  int tid;
-  const Tile t = get_tile(TL, tid);
-  const Scal &sc = T.sc[t.prob];
-  if (!asm_due(sc)) return;
-  const LevelDev L = T.lv[t.prob];
-  const ProbDev P = T.pd[t.prob];
-  const Col col = tile_col(t);
-  unsigned long long bits = 0;  // marked planes of the column: bit k - z0
-  int m0 = 0, m1 = 0;           // marked cells of colour 0, 1
-  if (col.on) {
-    for (int k = t.z0; k < t.z0 + t.tz; ++k) {
-      const Nb n = nbrs(col.i, col.j, k, L.nx, L.ny, L.nz);
-      const double faces = L.Tx[n.c] + L.Tx[n.xm] + L.Ty[n.c] + L.Ty[n.ym] +
-                           L.Tz[n.c] + L.Tz[n.zm];
-      if (faces > coupling * L.diag[n.c]) {
-        bits |= 1ull << (k - t.z0);
-        if ((col.i + col.j + k) & 1) ++m1;
-        else ++m0;
-      }
-    }
-  }
-  __shared__ int sh[2 * (kBlock / 64)];
-  int e0, e1, n0, n1;
-  block_scan2(m0, m1, sh, e0, e1, n0, n1);
-  while (bits) {
-    const int b = __ffsll((long long)bits) - 1;
-    bits &= bits - 1;
-    const int k = t.z0 + b;
-    const int q = ((col.i + col.j + k) & 1) ? n0 + e1++ : e0++;
-    P.llist[box_cell(t, q, L.nx, L.ny)] = (k * L.ny + col.j) * L.nx + col.i;
-  }
-  if (threadIdx.x == 0) {
-    P.lcnt[2 * (tid - P.t0)] = n0;
-    P.lcnt[2 * (tid - P.t0) + 1] = n1;
-  }
-}
-
 __global__ __launch_bounds__(kBlock) void k_local(Tables T, TileList TL, int colour) {
   int tid;
   const Tile t = get_tile(TL, tid);
   const Scal &sc = T.sc[t.prob];
   if (!sc.active) return;
   const ProbDev P = T.pd[t.prob];
-  // the counts come from k_lmask; bounded by the tile's box all the same, so
+  // the counts come from the assembly; bounded by the tile's box all the same, so
   // that no read of the list can leave the tile's own cells
   const int u = tid - P.t0, box = t.tx * t.ty * t.tz;
   const int first = colour ? min(max(P.lcnt[2 * u], 0), box) : 0;
@@ -1590,7 +1623,7 @@ static const char *kKernelNames[K_NUM] = {
     "vdown_coarse", "vup_fine", "vup_coarse", "chem_h", "ionized_sum",
     "warm_revert", "jacobi0_fine", "jacobi_fine", "jacobi_out",
     "jacobi_coarse", "prolong_add_fine", "prolong_add_coarse", "spmv_px",
-    "xfix", "warm_x", "lmask", "local", "control", "copy_E", "update_r"};
+    "xfix", "warm_x", "local", "control", "copy_E", "update_r"};
 
 namespace prof {
 struct Rec {
@@ -1644,8 +1677,9 @@ ProfScope::~ProfScope() {
 #define LAUNCH FLD_LAUNCH
 
 void launch_assemble(const Tables &T, TileList L0, double c, double theta,
-                     double dmax, double rmin, int mixed, hipStream_t s) {
-  if (L0.nblocks) LAUNCH(K_ASSEMBLE, k_assemble, L0.nblocks, kBlock, s, T, L0, c, theta, dmax, rmin, mixed);
+                     double dmax, double rmin, int mixed, int local,
+                     double coupling, hipStream_t s) {
+  if (L0.nblocks) LAUNCH(K_ASSEMBLE, k_assemble, L0.nblocks, kBlock, s, T, L0, c, theta, dmax, rmin, mixed, local, coupling);
 }
 
 void launch_coarsen(const Tables &T, TileList LC, int lc, double scale,
@@ -1756,10 +1790,6 @@ void launch_true_resid(const Tables &T, TileList L0, hipStream_t s) {
   if (L0.nblocks) LAUNCH(K_TRUE_RESID, k_true_resid, L0.nblocks, kBlock, s, T, L0);
 }
 
-
-void launch_lmask(const Tables &T, TileList L0, double coupling, hipStream_t s) {
-  if (L0.nblocks) LAUNCH(K_LMASK, k_lmask, L0.nblocks, kBlock, s, T, L0, coupling);
-}
 
 void launch_local(const Tables &T, TileList L0, int colour, hipStream_t s) {
   if (L0.nblocks) LAUNCH(K_LOCAL, k_local, L0.nblocks, kBlock, s, T, L0, colour);
