@@ -110,6 +110,15 @@ Hier make_hier(const fld_grid &g, const fld_params &p) {
   // it keeps to the coarsest level)
   const long long tc = p.smoother == FLD_SMOOTH_JACOBI ? 0 : p.tail_cells;
   while (h.tail > 1 && h.cells(h.tail - 1) <= tc) --h.tail;
+  // A cycle of per-sweep passes pays a launch per half-sweep, so from 512 on
+  // it takes the level above as well, as far as the tail kernel holds it in
+  // LDS (32^3 step, FP64 V(2,2): 281 -> 226 us; batch of 24, mixed V(2,2):
+  // 2.90 -> 2.82 ms).  The fused cycle's two box passes cost what the level
+  // costs the one workgroup (64^3 mixed 3500 -> 3470 us, 96 x 64 x 40 FP64
+  // 1285 -> 1310, 256^3 mixed 15.75 -> 15.82 ms): it keeps them
+  h.tail_sweeps = h.tail;
+  while (tc >= 512 && h.tail_sweeps > 1 && h.cells(h.tail_sweeps - 1) <= kTailTop)
+    --h.tail_sweeps;
   for (int l = 0; l < h.levels; ++l) {
     h.tiles[l] = count_tiles(p, h.n[l][0], h.n[l][1], h.n[l][2]);
     h.box[l] = box_level(p, l, h.cells(l));
@@ -275,6 +284,7 @@ void carve_problem(Carver &cv, const Hier &h, const fld_params &p, ProbMem &m) {
   m.xb[2] = cv.take<double>((size_t)h.cells(0));
   m.pd.levels = h.levels;
   m.pd.tail = h.tail;
+  m.pd.tail_sweeps = h.tail_sweeps;
   m.pd.cs = cv.take<double>(4 * (size_t)h.cells(h.levels - 1));
   m.E_work = cv.take<double>((size_t)h.cells(0));
   for (int k = 0; k < 3; ++k) m.pd.xb[k] = m.xb[k];
@@ -363,11 +373,12 @@ int Engine::setup(const fld_params &p, hipStream_t s,
   hier.resize(np);
   mem.resize(np);
   Lmax = 0;
-  tail_big = 0;
+  tail_routes = 0;
   for (int i = 0; i < np; ++i) {
     hier[i] = make_hier(g[i], p);
     Lmax = std::max(Lmax, hier[i].levels);
-    if (hier[i].cells(hier[i].levels - 1) > 2 * kTailBlock) tail_big = 1;
+    if (hier[i].levels > 1)
+      tail_routes |= hier[i].cells(hier[i].levels - 1) > 2 * kTailBlock ? 2 : 1;
   }
   tables_layout(tbl, hier, this);
   for (int i = 0; i < np; ++i) {
@@ -489,14 +500,15 @@ int Engine::build_lists(const std::vector<char> &member, int slot, ListSet &out)
   out.spf = make_any(0, true, [&](int i) { return spmv_on_fused(hier[i]); });
   out.spg = make(0, [&](int i) { return !spmv_on_fused(hier[i]); });
   for (int l = 0; l < kMaxLevels; ++l) {
-    // per-level sweeps: every level above the tail (the single level of a
-    // one-level hierarchy)
+    // every level above the tail (the single level of a one-level hierarchy)
+    out.smooth[l] = make(l, [&](int i) {
+      return hier[i].levels == 1 ? l == 0 : l < hier[i].tail_sweeps;
+    });
     auto smoothed = [&](int i) {
       return hier[i].levels == 1 ? l == 0 : l < hier[i].tail;
     };
-    out.smooth[l] = make(l, smoothed);
     out.exist[l] = make(l, [&](int) { return l >= 1; });
-    out.down[l] = make(l, [&](int i) { return l >= 1 && l <= hier[i].tail; });
+    out.down[l] = make(l, [&](int i) { return l >= 1 && l <= hier[i].tail_sweeps; });
     // (a one-level problem runs the finest down pass too: in the fused PCG
     // iteration it forms the residual)
     auto downs = [&](int i) { return smoothed(i) && (l < hier[i].levels - 1 || l == 0); };
@@ -637,7 +649,7 @@ void Engine::enqueue_fused_rest(const ListSet &ls) {
     launch_vdown(T, ls.fdn[l], l, prec, VD_ALL, stream);
     launch_bdown(T, ls.bdn[l], l, prec, VD_ALL, stream);
   }
-  if (Lmax > 1) launch_vtail(T, prec, 1, 1, tri, tail_big, stream);
+  if (Lmax > 1) launch_vtail(T, prec, 1, 1, tri, tail_routes, 0, stream);
   for (int l = Lmax - 1; l >= 0; --l) {
     launch_vup(T, ls.fsm[l], l, prec, l == 0 && mixed, tri, stream);
     launch_bup(T, ls.bsm[l], l, prec, l == 0 && mixed, tri, stream);
@@ -679,7 +691,7 @@ void Engine::enqueue_vcycle(const ListSet &ls) {
       }
       if (l + 1 < Lmax) launch_resid_restrict(T, down[l + 1], l + 1, prec, stream);
     }
-    if (Lmax > 1) launch_vtail(T, prec, np, nq, tri, tail_big, stream);
+    if (Lmax > 1) launch_vtail(T, prec, np, nq, tri, tail_routes, 1, stream);
     for (int l = Lmax - 1; l >= 0; --l) {
       if (smooth[l].nblocks == 0) continue;
       int in2 = nq & 1;  // buffer the correction lands in
@@ -701,7 +713,7 @@ void Engine::enqueue_vcycle(const ListSet &ls) {
     }
     if (l + 1 < Lmax) launch_resid_restrict(T, down[l + 1], l + 1, prec, stream);
   }
-  if (Lmax > 1) launch_vtail(T, prec, prm.nu_pre, prm.nu_post, tri, tail_big, stream);
+  if (Lmax > 1) launch_vtail(T, prec, prm.nu_pre, prm.nu_post, tri, tail_routes, 1, stream);
   for (int l = Lmax - 1; l >= 0; --l) {
     if (smooth[l].nblocks == 0) continue;
     launch_prolong_black(T, smooth[l], l, prec, tri, stream);

@@ -30,7 +30,9 @@ struct Carver {
 // multigrid hierarchy shape of one grid
 struct Hier {
   int levels = 0;
-  int tail = 1;                 // first level of the single-workgroup tail
+  // first level of the single-workgroup tail: of the fused cycle, and of the
+  // cycles of per-sweep passes
+  int tail = 1, tail_sweeps = 1;
   int n[kMaxLevels][3] = {};
   int tiles[kMaxLevels] = {};   // tiles per level
   int ftiles[kMaxLevels] = {};  // fused-cycle tiles (or boxes) per level
@@ -100,7 +102,7 @@ class Engine {
   std::vector<Hier> hier;
   std::vector<ProbMem> mem;
   int Lmax = 0;
-  int tail_big = 0;        // a coarsest level of more than 2 kTailBlock cells
+  int tail_routes = 0;     // tail kernels that some problem needs (launch_vtail)
 
   // host mirrors of the device tables
   std::vector<LevelDev> h_lv;

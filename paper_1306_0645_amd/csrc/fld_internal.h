@@ -15,6 +15,7 @@ namespace fld {
 constexpr int kBlock = 256;          // threads per tile block (4 wave64)
 constexpr int kFinBlock = 1024;      // threads of the per-problem finalize
 constexpr int kTailBlock = 1024;     // threads of the V-cycle tail kernel
+constexpr int kTailTop = 4 * kTailBlock;  // cells of the largest level it holds in LDS
 constexpr int kMaxLevels = 12;
 constexpr int kBoxX = 16, kBoxY = 8, kBoxZ = 4;  // largest box of a box pass
 
@@ -90,7 +91,8 @@ struct ProbDev {
   int t0, t1;            // range of this problem's tiles in the finest list
   int f0, f1;            // range of its fused-cycle finest tiles
   int spf;               // the fused iteration's SpMV runs on the fused tiles
-  int tail;              // first level of the single-workgroup V-cycle tail
+  int tail, tail_sweeps; // first level of the single-workgroup V-cycle tail:
+                         // fused cycle, cycles of per-sweep passes
   gptr<double> xb[3];    // the dE buffers (iterate and warm-start history)
   gptr<double> Ework;    // working copy of E while a step is subcycled
 };
@@ -259,9 +261,10 @@ void launch_resid_restrict(const Tables &T, TileList coarse, int lc, int prec,
                            hipStream_t s);
 void launch_prolong_black(const Tables &T, TileList L, int l, int prec,
                           int trilinear, hipStream_t s);
-// big: some problem's coarsest level has more than 2048 cells
+// routes: 1: some problem's coarsest level has at most 2048 cells, 2: some
+// problem's has more.  sweeps: the tail starts at tail_sweeps
 void launch_vtail(const Tables &T, int prec, int nu_pre, int nu_post,
-                  int trilinear, int big, hipStream_t s);
+                  int trilinear, int routes, int sweeps, hipStream_t s);
 // weighted Jacobi smoother: mode 0 = first sweep from x = 0, 1 = sweep,
 // 2 = last finest-level sweep writing z and the r.z partials (in = x2);
 // in_x2 selects the input buffer, the output is the other one

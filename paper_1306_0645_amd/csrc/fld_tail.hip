@@ -1,14 +1,15 @@
 // Tail of the V-cycle, one workgroup per problem: the coarsest level's
-// Jacobi-CG solve and, above it, the levels from P.tail down (each small):
-// pre-smoothing and restriction down to the coarsest level, the solve, then
-// prolongation and post-smoothing back up to P.tail, in the order of the
-// per-level path (red/black, red = even i+j+k).
+// Jacobi-CG solve and, above it, the levels from the tail's first down (each
+// small): pre-smoothing and restriction down to the coarsest level, the solve,
+// then prolongation and post-smoothing back up, in the order of the per-level
+// path (red/black, red = even i+j+k).
 //
 // One workgroup on one CU is bound by latency: of a memory access, of a
 // barrier and of a reduction, each paid once per phase.  So everything a
 // thread needs is loaded at the start in one round of independent loads (its
-// cell's coefficients on every level, one cell per thread), the values that
-// cross threads live in LDS, reductions take one barrier (wave sums by DPP
+// cell's coefficients on every level, one cell per thread; two x-pairs per
+// thread of a level of up to 4096 cells), the values that cross threads live
+// in LDS, reductions take one barrier (wave sums by DPP
 // row operations, then every wave sums the 16 wave results), and a coarsest
 // level of at most 64 cells is solved by one wave without any barrier.  The
 // CG carries r.z and ||r||^2 through one reduction and scales by the
@@ -20,7 +21,7 @@
 // (before: every phase through memory, three reductions of two barriers each
 // per CG iteration, exact divisions): 8^3 and 4^3 levels of 64^3 and 256^3
 // 21.3 -> 8.0 us, of 256^3 in FP64 24.8 -> 10.0 us; one 4^3 level 8.1 ->
-// 2.8 us; 20^3 under 640^3 98 -> 48 us; 25^3 under 200^3 292 -> 146 us.
+// 2.8 us; 20^3 under 640^3 98 -> 48 us; 25^3 under 200^3 292 -> 133 us.
 #include "fld_device.h"
 
 namespace fld {
@@ -310,6 +311,255 @@ __device__ __forceinline__ void tail_up(const TailCell<R> &a, R f, int nu, R *x,
   }
 }
 
+// ---- the level above them, two x-pairs of cells per thread, in LDS -----------
+
+// Red and black values lie in arrays of their own, at the pair's index q =
+// (k ny + j) nx / 2 + i / 2: a cell's neighbours along y and z are the other
+// colour's entries at q +- one row and plane, those along x at q itself and
+// at q - 1 or q + 1.
+template <typename R>
+struct TopPair {
+  R xo;                           // the face between the two cells
+  R xr, yrp, yrm, zrp, zrm, dr;   // the red cell's other faces, diagonal
+  R xb, ybp, ybm, zbp, zbm, db;   // the black cell's
+  R fr, fb;
+};
+
+struct TopIdx {
+  bool on;
+  int q, side_r, side_b, yp, ym, zp, zm;
+  int i, j, k;  // the red cell
+};
+
+__device__ __forceinline__ void top_index(TopIdx &a, const LevelDev &L, int q) {
+  const int hx = L.nx >> 1;
+  a.on = q < L.n >> 1;
+  if (!a.on) return;
+  const int px = q % hx, j = q / hx % L.ny, k = q / (hx * L.ny);
+  const Nb n = nbrs(px, j, k, hx, L.ny, L.nz);
+  const int odd = (j + k) & 1;
+  a.q = q;
+  a.side_r = odd ? n.xp : n.xm;
+  a.side_b = odd ? n.xm : n.xp;
+  a.yp = n.yp;
+  a.ym = n.ym;
+  a.zp = n.zp;
+  a.zm = n.zm;
+  a.i = 2 * px + odd;
+  a.j = j;
+  a.k = k;
+}
+
+template <typename R>
+__device__ __forceinline__ void top_load(TopPair<R> &v, const TopIdx &a, const LevelDev &L) {
+  typedef R R2 __attribute__((ext_vector_type(2)));
+  if (!a.on) return;
+  const Coef<R> C = coefs<R>(L);
+  const bool odd = a.i & 1;
+  auto pair = [&](const R *p, int q) { return ((const R2 *)p)[q]; };
+  const R2 tx = pair(C.tx, a.q), yp = pair(C.ty, a.q), ym = pair(C.ty, a.ym),
+           zp = pair(C.tz, a.q), zm = pair(C.tz, a.zm), d = pair(C.d, a.q),
+           f = pair((const R *)L.f, a.q);
+  // the face below the pair's first cell
+  const R xm = C.tx[2 * (odd ? a.side_b : a.side_r) + 1];
+  v.xo = tx.x;
+  v.xr = odd ? tx.y : xm;
+  v.xb = odd ? xm : tx.y;
+  v.yrp = odd ? yp.y : yp.x;
+  v.ybp = odd ? yp.x : yp.y;
+  v.yrm = odd ? ym.y : ym.x;
+  v.ybm = odd ? ym.x : ym.y;
+  v.zrp = odd ? zp.y : zp.x;
+  v.zbp = odd ? zp.x : zp.y;
+  v.zrm = odd ? zm.y : zm.x;
+  v.zbm = odd ? zm.x : zm.y;
+  v.dr = odd ? d.y : d.x;
+  v.db = odd ? d.x : d.y;
+  v.fr = odd ? f.y : f.x;
+  v.fb = odd ? f.x : f.y;
+}
+
+__device__ __forceinline__ void top_index(TopIdx (&a)[2], const LevelDev &L, int c) {
+  top_index(a[0], L, c);
+  top_index(a[1], L, c + kTailBlock);
+}
+
+template <typename R>
+__device__ __forceinline__ void top_load(TopPair<R> (&v)[2], TopIdx (&a)[2], const LevelDev &L,
+                                         int c) {
+  top_index(a, L, c);
+  top_load(v[0], a[0], L);
+  top_load(v[1], a[1], L);
+}
+
+// sum of T x over the red cell's (black) neighbours, and the black cell's
+template <typename R>
+__device__ __forceinline__ R top_off_r(const TopPair<R> &v, const TopIdx &a, const R *xk) {
+  return v.xo * xk[a.q] + v.xr * xk[a.side_r] + v.yrp * xk[a.yp] + v.yrm * xk[a.ym] +
+         v.zrp * xk[a.zp] + v.zrm * xk[a.zm];
+}
+
+template <typename R>
+__device__ __forceinline__ R top_off_b(const TopPair<R> &v, const TopIdx &a, const R *xr) {
+  return v.xo * xr[a.q] + v.xb * xr[a.side_b] + v.ybp * xr[a.yp] + v.ybm * xr[a.ym] +
+         v.zbp * xr[a.zp] + v.zbm * xr[a.zm];
+}
+
+template <typename R>
+__device__ __forceinline__ void top_half_r(const TopPair<R> (&v)[2], const TopIdx (&a)[2], R *xr,
+                                           const R *xk) {
+#pragma unroll
+  for (int u = 0; u < 2; ++u)
+    if (a[u].on) xr[a[u].q] = (v[u].fr + top_off_r(v[u], a[u], xk)) * recip(v[u].dr);
+  __syncthreads();
+}
+
+template <typename R>
+__device__ __forceinline__ void top_half_b(const TopPair<R> (&v)[2], const TopIdx (&a)[2],
+                                           const R *xr, R *xk) {
+#pragma unroll
+  for (int u = 0; u < 2; ++u)
+    if (a[u].on) xk[a[u].q] = (v[u].fb + top_off_b(v[u], a[u], xr)) * recip(v[u].db);
+  __syncthreads();
+}
+
+// nu sweeps from x = 0, and the coarse right-hand side of coarse cell tid:
+// the residuals of its four red children (a black cell's is zero after the
+// black half)
+template <typename R>
+__device__ __forceinline__ R top_down(const TopPair<R> (&v)[2], const TopIdx (&a)[2], int nu,
+                                      R *xr, R *xk, R *rs, const LevelDev &LF,
+                                      const LevelDev &LC) {
+#pragma unroll
+  for (int u = 0; u < 2; ++u)
+    if (a[u].on) xr[a[u].q] = v[u].fr * recip(v[u].dr);
+  __syncthreads();
+  top_half_b(v, a, xr, xk);
+  for (int s = 1; s < nu; ++s) {
+    top_half_r(v, a, xr, xk);
+    top_half_b(v, a, xr, xk);
+  }
+#pragma unroll
+  for (int u = 0; u < 2; ++u)
+    if (a[u].on)
+      rs[a[u].q] = v[u].fr - (v[u].dr * xr[a[u].q] - top_off_r(v[u], a[u], xk));
+  __syncthreads();
+  R acc = 0;
+  const int c = threadIdx.x;
+  if (c < LC.n) {
+    const int I = c % LC.nx, J = (c / LC.nx) % LC.ny, K = c / (LC.nx * LC.ny);
+#pragma unroll
+    for (int cz = 0; cz < 2; ++cz)
+#pragma unroll
+      for (int cy = 0; cy < 2; ++cy) acc += rs[((2 * K + cz) * LF.ny + 2 * J + cy) * LC.nx + I];
+  }
+  return acc;
+}
+
+// the correction e of the coarse level at the red cells, then nu sweeps
+// (black, red); the result goes to x in memory
+template <typename R>
+__device__ __forceinline__ void top_up(const TopPair<R> (&v)[2], const TopIdx (&a)[2], int nu,
+                                       R *xr, R *xk, const R *e, const LevelDev &LF,
+                                       const LevelDev &LC, bool tri) {
+#pragma unroll
+  for (int u = 0; u < 2; ++u)
+    if (a[u].on)
+      xr[a[u].q] += coarse_corr(e, a[u].i, a[u].j, a[u].k, LC.nx, LC.ny, LC.nz, tri);
+  __syncthreads();
+  for (int s = 0; s < nu; ++s) {
+    top_half_b(v, a, xr, xk);
+    top_half_r(v, a, xr, xk);
+  }
+  typedef R R2 __attribute__((ext_vector_type(2)));
+#pragma unroll
+  for (int u = 0; u < 2; ++u)
+    if (a[u].on) {
+      const R r = xr[a[u].q], b = xk[a[u].q];
+      R2 o;
+      o.x = a[u].i & 1 ? b : r;
+      o.y = a[u].i & 1 ? r : b;
+      ((R2 *)(R *)LF.x)[a[u].q] = o;
+    }
+}
+
+// The whole tail in LDS, every load of the pass issued at the start: TOP: a
+// level of two pairs of cells per thread, then up to two levels of one cell
+// per thread, then the coarsest.
+template <typename R, bool TOP>
+__device__ __forceinline__ void tail_lds(const Tables &T, int p, int lt, int lc, int nu_pre,
+                                         int nu_post, bool tri, double *sp, double *red,
+                                         R *const (&lx)[4]) {
+  // (FP64: a top level's coefficients would not leave registers for the
+  // others' and are loaded again on the way up)
+  constexpr bool kKeep = TOP && sizeof(R) == 4;
+  const int li = TOP ? lt + 1 : lt, ns = lc - li;
+  const int c = threadIdx.x;
+  R *xa = lx[0], *xb = lx[1], *xc = lx[2], *rs = lx[3];
+  R *xr = (R *)(sp + kTailBlock), *xk = xr + kTailTop / 2, *rt = xk + kTailTop / 2;
+  const LevelDev LT = T.lv[lt * T.nprob + p];
+  const LevelDev L0 = T.lv[li * T.nprob + p];
+  const LevelDev L1 = T.lv[min(li + 1, lc) * T.nprob + p];
+  const LevelDev L2 = T.lv[lc * T.nprob + p];
+  TopPair<R> tp[kKeep ? 2 : 1];
+  TailCell<R> a, b;
+  CgCell cell[1];
+  R fa = 0, fb = 0, fcg = 0;
+  if constexpr (TOP && !kKeep) {
+    TopPair<R> t2[2];
+    TopIdx ti[2];
+    top_load(t2, ti, LT, c);
+    fa = fcg = top_down(t2, ti, nu_pre, xr, xk, rt, LT, L0);
+    asm volatile("" ::: "memory");
+  }
+  a.on = b.on = b.red = false;
+  if (!TOP || ns >= 1) tail_load(a, L0);
+  if (ns == 2) tail_load(b, L1);
+  if (c < L2.n) cg_load(cell[0], L2, c);
+  if constexpr (kKeep) {
+    TopIdx ti[2];
+    top_load(tp, ti, LT, c);
+    fa = fcg = top_down(tp, ti, nu_pre, xr, xk, rt, LT, L0);
+  }
+  if constexpr (!TOP) {
+    if (a.on) fa = ((const R *)L0.f)[c];
+  }
+  if (!TOP || ns >= 1) fcg = tail_down(a, fa, nu_pre, xa, rs, L0, L1);
+  if (ns == 2) {
+    fb = fcg;
+    fcg = tail_down(b, fb, nu_pre, xb, rs, L1, L2);
+  }
+  const double f[1] = {c < L2.n ? (double)fcg : 0.0};
+  double x[1] = {0.0};
+  if (L2.n <= 64) {
+    if (c < 64) coarse_cg<1, true, true>(L2, cell, f, x, nullptr, sp, red);
+  } else {
+    coarse_cg<1, false, true>(L2, cell, f, x, nullptr, sp, red);
+  }
+  R *xl = ns == 2 ? xc : (!TOP || ns == 1) ? xb : xa;
+  if (c < L2.n) xl[c] = (R)x[0];
+  __syncthreads();
+  if (ns == 2) tail_up(b, fb, nu_post, xb, xc, L1, L2, tri);
+  if (!TOP || ns >= 1) tail_up(a, fa, nu_post, xa, xb, L0, L1, tri);
+  if constexpr (TOP) {
+    // (the thread index is opaque: the compiler would otherwise keep the
+    // indices, and in FP64 the coefficients, through the levels below)
+    int c1 = c;
+    asm volatile("" : "+v"(c1)::"memory");
+    TopIdx ti[2];
+    if constexpr (kKeep) {
+      top_index(ti, LT, c1);
+      top_up(tp, ti, nu_post, xr, xk, xa, LT, L0, tri);
+    } else {
+      TopPair<R> t2[2];
+      top_load(t2, ti, LT, c1);
+      top_up(t2, ti, nu_post, xr, xk, xa, LT, L0, tri);
+    }
+  } else if (a.on) {
+    ((R *)L0.x)[c] = xa[c];
+  }
+}
+
 // ---- smoothing levels through memory (more than kTailBlock cells) ------------
 
 template <typename R>
@@ -495,52 +745,33 @@ constexpr int kTailSmall = 2 * kTailBlock, kTailBig = 16 * kTailBlock;
 
 template <typename R, int CAP>
 __global__ __launch_bounds__(kTailBlock) void k_vtail(Tables T, int nu_pre,
-                                                     int nu_post, int trilinear) {
+                                                     int nu_post, int trilinear, int sweeps) {
   const int p = blockIdx.x;
   const Scal &sc = T.sc[p];
   const ProbDev &P = T.pd[p];
-  const int levels = P.levels, lt = P.tail, lc = levels - 1;
+  const int levels = P.levels, lt = sweeps ? P.tail_sweeps : P.tail, lc = levels - 1;
   if (!sc.active || levels < 2) return;
-  __shared__ double sp[CAP];
+  constexpr bool kBig = CAP > kTailSmall;
+  const LevelDev LC = T.lv[lc * T.nprob + p];
+  if ((LC.n > kTailSmall) != kBig) return;  // (the other launch's)
+  // the CG's direction; a level of more than kTailBlock cells keeps its
+  // values and residuals behind the first kTailBlock entries
+  __shared__ double sp[kBig ? CAP : kTailBlock + 3 * kTailTop / 2];
   __shared__ double red[2 * 2 * kTW];
-  // (each level has an eighth of the cells of the one above)
-  __shared__ R xa[kTailBlock], xb[kTailBlock / 8], xc[kTailBlock / 64], rs[kTailBlock];
   const bool tri = trilinear != 0;
-  const int ns = lc - lt;  // smoothing levels of the tail
-  const LevelDev L0 = T.lv[lt * T.nprob + p];
-  if (ns >= 1 && ns <= 2 && L0.n <= kTailBlock) {
-    // one cell per thread on every level, values in LDS.  Every load of the
-    // pass is issued here
-    const LevelDev L1 = T.lv[(lt + 1) * T.nprob + p];
-    const LevelDev L2 = T.lv[lc * T.nprob + p];
-    const int c = threadIdx.x;
-    TailCell<R> a, b;
-    CgCell cell[1];
-    tail_load(a, L0);
-    b.on = b.red = false;
-    if (ns == 2) tail_load(b, L1);
-    if (c < L2.n) cg_load(cell[0], L2, c);
-    R fa = 0, fb = 0, fcg;
-    if (a.on) fa = ((const R *)L0.f)[c];
-    fcg = tail_down(a, fa, nu_pre, xa, rs, L0, L1);
-    if (ns == 2) {
-      fb = fcg;
-      fcg = tail_down(b, fb, nu_pre, xb, rs, L1, L2);
+  if constexpr (!kBig) {
+    // (each level has an eighth of the cells of the one above)
+    __shared__ R xa[kTailBlock], xb[kTailBlock / 8], xc[kTailBlock / 64], rs[kTailBlock];
+    R *lx[4] = {xa, xb, xc, rs};
+    const int n = T.lv[lt * T.nprob + p].n;
+    if (n > kTailBlock && n <= kTailTop && lt < lc && lc - lt <= 3) {
+      tail_lds<R, true>(T, p, lt, lc, nu_pre, nu_post, tri, sp, red, lx);
+      return;
     }
-    const double f[1] = {c < L2.n ? (double)fcg : 0.0};
-    double x[1] = {0.0};
-    if (L2.n <= 64) {
-      if (c < 64) coarse_cg<1, true, true>(L2, cell, f, x, nullptr, sp, red);
-    } else {
-      coarse_cg<1, false, true>(L2, cell, f, x, nullptr, sp, red);
+    if (n <= kTailBlock && lt < lc && lc - lt <= 2) {
+      tail_lds<R, false>(T, p, lt, lc, nu_pre, nu_post, tri, sp, red, lx);
+      return;
     }
-    R *xl = ns == 2 ? xc : xb;
-    if (c < L2.n) xl[c] = (R)x[0];
-    __syncthreads();
-    if (ns == 2) tail_up(b, fb, nu_post, xb, xc, L1, L2, tri);
-    tail_up(a, fa, nu_post, xa, xb, L0, L1, tri);
-    if (a.on) ((R *)L0.x)[c] = xa[c];
-    return;
   }
   for (int l = lt; l < lc; ++l) {
     const LvlView<R> V = lvl_view<R>(T, l, p);
@@ -555,8 +786,7 @@ __global__ __launch_bounds__(kTailBlock) void k_vtail(Tables T, int nu_pre,
     mem_restrict(V, lvl_view<R>(T, l + 1, p));
     __syncthreads();
   }
-  const LevelDev LC = T.lv[lc * T.nprob + p];
-  if (LC.n <= kTailBlock) {
+  if constexpr (!kBig) {
     if (LC.n <= 64) {
       if (threadIdx.x < 64) {
         CgCell cell[1];
@@ -569,19 +799,16 @@ __global__ __launch_bounds__(kTailBlock) void k_vtail(Tables T, int nu_pre,
         coarse_cg<1, true, true>(LC, cell, f, x, nullptr, sp, red);
         if (c < LC.n) ((R *)LC.x)[c] = (R)x[0];
       }
-    } else {
+    } else if (LC.n <= kTailBlock) {
       level_cg<R, 1, true>(LC, P.cs, sp, red);
+    } else {
+      level_cg<R, 2, true>(LC, P.cs, sp, red);
     }
-  } else if (LC.n <= 2 * kTailBlock) {
-    level_cg<R, 2, true>(LC, P.cs, sp, red);
-  } else if (CAP >= kTailBig && LC.n <= 4 * kTailBlock) {
-    if constexpr (CAP >= kTailBig) level_cg<R, 4, false>(LC, P.cs, sp, red);
-  } else if (CAP >= kTailBig && LC.n <= 8 * kTailBlock) {
-    if constexpr (CAP >= kTailBig) level_cg<R, 8, false>(LC, P.cs, sp, red);
-  } else if (CAP >= kTailBig && LC.n <= kTailBig) {
-    if constexpr (CAP >= kTailBig) level_cg<R, 16, false>(LC, P.cs, sp, red);
   } else {
-    mem_coarse_solve<R>(LC, P, red);
+    if (LC.n <= 4 * kTailBlock) level_cg<R, 4, false>(LC, P.cs, sp, red);
+    else if (LC.n <= 8 * kTailBlock) level_cg<R, 8, false>(LC, P.cs, sp, red);
+    else if (LC.n <= kTailBig) level_cg<R, 16, false>(LC, P.cs, sp, red);
+    else mem_coarse_solve<R>(LC, P, red);
   }
   __syncthreads();
   for (int l = lc - 1; l >= lt; --l) {
@@ -599,23 +826,26 @@ __global__ __launch_bounds__(kTailBlock) void k_vtail(Tables T, int nu_pre,
   }
 }
 
+// routes: 1: some problem's coarsest level has at most kTailSmall cells, 2:
+// some problem's has more (a kernel each: the one holds its levels in LDS and
+// registers, the other the LDS for the streamed solve)
 void launch_vtail(const Tables &T, int prec, int nu_pre, int nu_post, int trilinear,
-                  int big, hipStream_t s) {
+                  int routes, int sweeps, hipStream_t s) {
   if (!T.nprob) return;
   if (prec) {
-    if (big)
-      FLD_LAUNCH(K_COARSE_SOLVE, (k_vtail<float, kTailBig>), T.nprob, kTailBlock, s, T,
-                 nu_pre, nu_post, trilinear);
-    else
+    if (routes & 1)
       FLD_LAUNCH(K_COARSE_SOLVE, (k_vtail<float, kTailSmall>), T.nprob, kTailBlock, s, T,
-                 nu_pre, nu_post, trilinear);
+                 nu_pre, nu_post, trilinear, sweeps);
+    if (routes & 2)
+      FLD_LAUNCH(K_COARSE_SOLVE, (k_vtail<float, kTailBig>), T.nprob, kTailBlock, s, T,
+                 nu_pre, nu_post, trilinear, sweeps);
   } else {
-    if (big)
-      FLD_LAUNCH(K_COARSE_SOLVE, (k_vtail<double, kTailBig>), T.nprob, kTailBlock, s, T,
-                 nu_pre, nu_post, trilinear);
-    else
+    if (routes & 1)
       FLD_LAUNCH(K_COARSE_SOLVE, (k_vtail<double, kTailSmall>), T.nprob, kTailBlock, s, T,
-                 nu_pre, nu_post, trilinear);
+                 nu_pre, nu_post, trilinear, sweeps);
+    if (routes & 2)
+      FLD_LAUNCH(K_COARSE_SOLVE, (k_vtail<double, kTailBig>), T.nprob, kTailBlock, s, T,
+                 nu_pre, nu_post, trilinear, sweeps);
   }
 }
 

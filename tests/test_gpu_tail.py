@@ -2,7 +2,8 @@
 coarsest solve) at the sizes where it changes its route: a coarsest level of
 at most 64 cells (one wave), up to 1024 and 2048 (operator in registers),
 4096, 8192 and 16384 (operator streamed) and beyond (vectors in memory), and
-no, one, two or more smoothing levels above it, in LDS or in memory.  One
+no, one, two or more smoothing levels above it, in LDS (one cell a thread, the
+largest in pairs of cells) or in memory.  One
 cycle through fld_precondition against the textbook cycle on the oracle's
 operator, within the bounds of the cycle tests (the coarsest solve there:
 sparse CG to 1e-14)."""
@@ -48,7 +49,12 @@ CASES = [  # (shape, levels, tail_cells): coarsest cells, smoothing levels of th
     ((16, 16, 20), 3, 700),    # 80 under one of 640
     ((32, 16, 16), 4, 1024),   # 16 under levels of 1024 and 128 in LDS
     ((16, 16, 32), 4, 2048),   # 16 under 128 and 1024
-    ((32, 32, 32), 4, 8192),   # 64 under levels of 4096 and 512 in memory
+    ((32, 32, 32), 4, 8192),   # 64 under levels of 4096 (in pairs) and 512 in LDS
+    ((32, 32, 32), 3, 512),    # 512 right under one of 4096
+    ((24, 20, 32), 3, 512),    # 240 under one of 1920, rows of 6 pairs
+    ((24, 24, 48), 3, 512),    # 432 under one of 3456
+    ((32, 32, 32), 5, 512),    # 8 under levels of 4096, 512 and 64
+    ((32, 32, 64), 4, 8192),   # 128 under levels of 8192 and 1024 in memory
 ]
 
 
