@@ -763,15 +763,15 @@ void Engine::enqueue_prologue(const ListSet &ls) {
   if (!lazy || !need_pro) return;
   launch_vdown(T, ls.fdn[0], 0, mixed, VD_FRESH, stream);
   launch_bdown(T, ls.bdn[0], 0, mixed, VD_FRESH, stream);
-  launch_fin(T, FIN_FRESH, mixed, stream);
   need_pro = false;
 }
 
 // x += alpha p for problems that stopped iterating with that update pending
-// (fused form); keeps the host mirror in step
-void Engine::finish_x(const ListSet &ls) {
+// (fused form); keeps the host mirror in step.  marked: a FIN_TRUE with alt
+// follows and marks it done
+void Engine::finish_x(const ListSet &ls, bool marked) {
   launch_xfix(T, ls.fine, kmode(), stream);
-  launch_fin(T, FIN_XFIX, mixed, stream);
+  if (!marked) launch_fin(T, FIN_XFIX, mixed, stream);
   for (Scal &sc : h_sc)
     if (sc.xlag && sc.phase != PH_ITER) sc.xlag = 0;
 }
@@ -810,10 +810,10 @@ int Engine::run_solve(bool predicted, bool commit) {
       else if (sc.phase == PH_VERIFY) ++nver;
       if (sc.xlag && sc.phase != PH_ITER) fix = true;
     }
-    if (fix) finish_x(all);
+    if (fix) finish_x(all, nver > 0);
     if (nver) {
       launch_true_resid(T, all.fine, stream);
-      launch_fin(T, FIN_TRUE, mixed, stream);
+      launch_fin(T, FIN_TRUE, mixed, stream, fix);
       need_pro = true;
       if (commit) {
         launch_update_E(T, all.fine, prm.e_floor, 0, stream, 1);
@@ -1067,19 +1067,14 @@ void Engine::enqueue_unit(const ListSet &ls, const CtlParams &cp) {
     launch_fin(T, FIN_WARM, mixed, stream);
   }
   launch_warm_revert(T, ls.fine, stream);
-  launch_fin(T, FIN_STAGE, mixed, stream);
   if (lazy) {
     launch_vdown(T, ls.fdn[0], 0, mixed, VD_FRESH, stream);
     launch_bdown(T, ls.bdn[0], 0, mixed, VD_FRESH, stream);
-    launch_fin(T, FIN_FRESH, mixed, stream);
   }
   enqueue_iteration(ls);
-  if (fused) {
-    launch_xfix(T, ls.fine, kmode(), stream);
-    launch_fin(T, FIN_XFIX, mixed, stream);
-  }
+  if (fused) launch_xfix(T, ls.fine, kmode(), stream);
   launch_true_resid(T, ls.fine, stream);
-  launch_fin(T, FIN_TRUE, mixed, stream);
+  launch_fin(T, FIN_TRUE, mixed, stream, fused);
   launch_update_E(T, ls.fine, prm.e_floor, 0, stream, 1);
   launch_fin(T, FIN_STEP, mixed, stream, 1);
   launch_control(T, cp, stream);

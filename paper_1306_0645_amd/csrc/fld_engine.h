@@ -184,7 +184,7 @@ class Engine {
   void enqueue_fused_rest(const ListSet &ls);
   void enqueue_iteration(const ListSet &ls);
   void enqueue_prologue(const ListSet &ls);
-  void finish_x(const ListSet &ls);
+  void finish_x(const ListSet &ls, bool marked = false);
   int run_solve(bool predicted = false, bool commit = false);
   int run_steps(std::vector<Job> &jobs);
   void enqueue_unit(const ListSet &ls, const CtlParams &cp);

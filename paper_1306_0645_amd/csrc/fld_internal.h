@@ -249,7 +249,8 @@ void launch_assemble(const Tables &T, TileList L0, double c, double theta,
 void launch_coarsen(const Tables &T, TileList coarse, int lc, double scale,
                     int mixed, int op, hipStream_t s);
 // alt: FIN_RZ and FIN_RR2 read the partials of the fused finest tiles; FIN_PQ
-// with alt marks the fused iteration's deferred updates
+// with alt marks the fused iteration's deferred updates; FIN_TRUE with alt
+// also does FIN_XFIX's part
 void launch_fin(const Tables &T, int which, int mixed, hipStream_t s,
                 int alt = 0);
 void launch_pre0(const Tables &T, TileList L, int l, int prec, hipStream_t s);
@@ -341,11 +342,8 @@ enum : int {
   FIN_RR2 = 8,    // fused iteration, after the down pass formed r - alpha q:
                   // ||r||^2, convergence, switch the residual buffer
   FIN_XFIX = 9,   // after k_xfix: the deferred x update is done
-  FIN_FRESH = 10, // after the prologue's down pass: the problems iterate on
-  FIN_WARM = 11,  // after k_warm_x: keep the projected guess if it reduces
+  FIN_WARM = 11   // after k_warm_x: keep the projected guess if it reduces
                   // the residual
-  FIN_STAGE = 12  // device-controlled stepping: the substep's warm start is
-                  // done, its PCG runs on
   // (FIN_RZ with alt = 2: the fused cycle's partials plus the local sweeps')
 };
 

@@ -1421,7 +1421,13 @@ __global__ __launch_bounds__(kFinBlock) void k_fin(Tables T, int which, int mixe
   const bool fz = (alt && which == FIN_RZ) || (alt && which == FIN_PQ && P.spf) ||
                   which == FIN_RR2;
   const int t0 = fz ? P.f0 : P.t0;
-  const int t1 = (which == FIN_XFIX || which == FIN_FRESH) ? t0 : (fz ? P.f1 : P.t1);
+  const int t1 = (which == FIN_XFIX) ? t0 : (fz ? P.f1 : P.t1);
+  // state changes that need no sums ride along (a launch each would cost as
+  // much as the sums): in a device-controlled unit the warm start is behind
+  // the first cycle, and x is up to date once the true residual is formed
+  if (which == FIN_RZ && threadIdx.x == 0 && sc.ctl && sc.stage == 2) sc.stage = 0;
+  if (which == FIN_TRUE && alt && threadIdx.x == 0 && sc.xlag && sc.phase != PH_ITER)
+    sc.xlag = sc.lag = sc.hasb = 0;
   bool part;
   switch (which) {
     case FIN_STEP: part = alt ? commit_now(sc) : sc.live != 0; break;
@@ -1429,13 +1435,9 @@ __global__ __launch_bounds__(kFinBlock) void k_fin(Tables T, int which, int mixe
     case FIN_SETR: part = true; break;
     case FIN_RR2: part = sc.active && sc.has_dir; break;
     case FIN_XFIX: part = sc.xlag && sc.phase != PH_ITER; break;
-    case FIN_FRESH: part = sc.active && sc.fresh; break;
     case FIN_WARM:
       part = warm_due(sc) && T.sd[p].warm > 1.0 && sc.phase == PH_ITER && !sc.cold;
       break;
-    case FIN_STAGE:
-      if (threadIdx.x == 0 && sc.ctl && sc.stage == 2) sc.stage = 0;
-      return;
     default: part = sc.active != 0; break;
   }
   if (!part) return;
@@ -1482,6 +1484,7 @@ __global__ __launch_bounds__(kFinBlock) void k_fin(Tables T, int which, int mixe
     case FIN_RZ: {
       sc.rho = a0;
       sc.rzo = a1;
+      sc.fresh = 0;  // (the finest down pass is done)
       // (a failed solve keeps the z and the scale that its pending update of
       // x is formed from)
       if (!finite(a0) || !finite(a1)) { fail(sc, ST_ENONFINITE); break; }
@@ -1548,9 +1551,6 @@ __global__ __launch_bounds__(kFinBlock) void k_fin(Tables T, int which, int mixe
       break;
     case FIN_XFIX:
       sc.xlag = sc.lag = sc.hasb = 0;
-      break;
-    case FIN_FRESH:
-      sc.fresh = 0;
       break;
     case FIN_WARM:
       // keep the projected guess only if it reduces the residual (else
