@@ -97,6 +97,8 @@ def bpc(name, prec_idx, dir64=False):
 # reads 4 FP64 arrays of level l-1 and writes 4 of level l (plus 4 FP32 copies
 # in mixed mode).
 COARSE_CYCLE_BYTES = (48.0 + 49.0 + 57.0 + 56.0, 28.0 + 28.5 + 32.5 + 32.0)
+# the same under V(1,1): the two fused passes
+COARSE_CYCLE_BYTES_FUSED = (41.0 + 49.0, 20.5 + 24.5)
 # the same under the weighted-Jacobi smoother: first sweep, residual and
 # restriction, x + P e, one sweep
 COARSE_CYCLE_BYTES_JACOBI = (24.0 + 49.0 + 17.0 + 56.0, 12.0 + 28.5 + 8.5 + 28.0)
@@ -125,8 +127,8 @@ def step_bytes(counts, cells, prec_idx, levels, dir64=False):
             else:
                 it += v
     cf = coarse_fraction(levels)
-    cycles = counts.get("vdown_fine", 0) or counts.get("pre0_fine", 0)
-    it += cycles * cf * COARSE_CYCLE_BYTES[prec_idx] * cells
+    it += counts.get("vdown_fine", 0) * cf * COARSE_CYCLE_BYTES_FUSED[prec_idx] * cells
+    it += counts.get("pre0_fine", 0) * cf * COARSE_CYCLE_BYTES[prec_idx] * cells
     it += counts.get("jacobi0_fine", 0) * cf * COARSE_CYCLE_BYTES_JACOBI[prec_idx] * cells
     coarsen = 32.0 * (1.0 + cf - 8.0 ** -(levels - 1)) + (48.0 if prec_idx else 32.0) * cf
     fixed += counts.get("assemble", 0) * coarsen * cells
@@ -147,7 +149,7 @@ def model_step_bytes(cells, iters, nu, prec_idx, levels, steps=1, warm=False,
     nu = 1), the SpMV and the vector update."""
     B = {k: bpc(k, prec_idx, dir64) for k in BYTES_PER_CELL}
     cf = coarse_fraction(levels)
-    coarse = (COARSE_CYCLE_BYTES[prec_idx]
+    coarse = (COARSE_CYCLE_BYTES_FUSED[prec_idx] if nu == 1 else COARSE_CYCLE_BYTES[prec_idx]
               + (4 * (nu - 1)) * (56.0, 32.0)[prec_idx])
     if nu == 1 and prec_idx == 1:
         # fused mixed iteration: the residual update rides in the down pass
