@@ -114,16 +114,35 @@ __device__ __forceinline__ R box_red(const Cell7<R> &a, const R *x, int ex, int 
          a.zm * x[row - hxy + h];
 }
 
+// u / d for a uniform u (m = 2^32 / d + 1, or 0 for d = 1): scalar operations,
+// where the division of two 32-bit numbers takes some 20 dependent ones
+__device__ __forceinline__ unsigned box_div(unsigned u, unsigned m) {
+  return m ? __umulhi(u, m) : u;
+}
+
+// the block's box of level L (unsigned extents of at most 8 bits: the divisions
+// by them stay short)
+__device__ __forceinline__ Tile get_box(const LevelDev &L, const Range &g) {
+  const BoxRec &r = L.box;
+  const unsigned u = g.block;
+  const unsigned row = box_div(u, r.mx), pl = box_div(row, r.my);
+  const unsigned tx = r.ext & 255, ty = r.ext >> 8 & 255, tz = r.ext >> 16 & 255;
+  const int x0 = (u - row * r.nbx) * tx, y0 = (row - pl * r.nby) * ty, z0 = pl * tz;
+  const int ex = min(tx, (unsigned)(L.nx - x0)), ey = min(ty, (unsigned)(L.ny - y0)),
+            ez = min(tz, (unsigned)(L.nz - z0));
+  return {g.prob, x0, y0, z0, ex, ey, ez};
+}
+
 template <typename R, bool L0>
 __global__ __launch_bounds__(kBlock) void k_bdown(Tables T, TileList TL, int l, int sel) {
   using FT = typename FSrc<R, L0>::FT;
-  int tid;
-  const Tile t = get_tile(TL, tid);
-  const Scal &sc = T.sc[t.prob];
+  const Range g0 = get_range(TL);
+  const Scal &sc = T.sc[g0.prob];
   if (!sc.active) return;
   if ((sel == VD_FRESH && !sc.fresh) || (sel == VD_CONT && sc.fresh)) return;
-  const LevelDev L = T.lv[l * T.nprob + t.prob];
-  const ProbDev &P = T.pd[t.prob];
+  const LevelDev L = T.lv[l * T.nprob + g0.prob];
+  const ProbDev &P = T.pd[g0.prob];
+  const Tile t = get_box(L, g0);
   const bool has_coarse = l + 1 < P.levels;
   const LevelDev &Cv = T.lv[min(l + 1, kMaxLevels - 1) * T.nprob + t.prob];
   const Coef<R> C = coefs<R>(L);
@@ -228,18 +247,18 @@ __global__ __launch_bounds__(kBlock) void k_bdown(Tables T, TileList TL, int l, 
     if (s < nred && (s & 3) == 0)
       fc[(((t.z0 >> 1) + K) * Cv.ny + (t.y0 >> 1) + J) * Cv.nx + (t.x0 >> 1) + I] = v;
   }
-  if constexpr (kUpd) write_partials(T, tid, rr, 0.0);
+  if constexpr (kUpd) write_partials(T, P.f0 + g0.block, rr, 0.0);
 }
 
 template <typename R, bool L0, bool TRI>
 __global__ __launch_bounds__(kBlock) void k_bup(Tables T, TileList TL, int l, int flexible) {
   using FT = typename FSrc<R, L0>::FT;
-  int tid;
-  const Tile t = get_tile(TL, tid);
-  const Scal &sc = T.sc[t.prob];
+  const Range g0 = get_range(TL);
+  const Scal &sc = T.sc[g0.prob];
   if (!sc.active) return;
-  const LevelDev L = T.lv[l * T.nprob + t.prob];
-  const ProbDev &P = T.pd[t.prob];
+  const LevelDev L = T.lv[l * T.nprob + g0.prob];
+  const ProbDev &P = T.pd[g0.prob];
+  const Tile t = get_box(L, g0);
   const bool has_coarse = l + 1 < P.levels;
   const LevelDev Cl = T.lv[min(l + 1, kMaxLevels - 1) * T.nprob + t.prob];
   const Coef<R> C = coefs<R>(L);
@@ -404,7 +423,7 @@ __global__ __launch_bounds__(kBlock) void k_bup(Tables T, TileList TL, int l, in
       }
     }
   }
-  if constexpr (L0) write_partials(T, tid, rz, rzo);
+  if constexpr (L0) write_partials(T, P.f0 + g0.block, rz, rzo);
 }
 
 // launchers ------------------------------------------------------------------

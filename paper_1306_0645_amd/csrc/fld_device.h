@@ -25,12 +25,16 @@ __device__ __forceinline__ int xcd_block(int nb) {
   return x * q + (x < rem ? x : rem) + (b >> 3);
 }
 
-// The block's tile: idx is its index inside the full table (for per-tile
-// partial sums).  The problem comes with the range, so that the kernel's
+// The block's range of the list: its problem, its first table entry and the
+// block's index in it.  The problem comes with the range, so that the kernel's
 // loads of the problem's descriptors do not wait for the tile's.  A list of
 // one range (a plain handle) carries it in the kernel arguments; up to 64
 // ranges are searched by one load, a range per lane, and a ballot.
-__device__ __forceinline__ Tile get_tile(const TileList &L, int &idx) {
+struct Range {
+  int prob, first, block;
+};
+
+__device__ __forceinline__ Range get_range(const TileList &L) {
   const int b = xcd_block(L.nblocks);
   int p = L.prob, first = L.first, start = 0;
   if (L.nranges > 1) {
@@ -54,10 +58,17 @@ __device__ __forceinline__ Tile get_tile(const TileList &L, int &idx) {
       p = L.ranges[3 * lo + 2];
     }
   }
-  idx = first + (b - start);
-  Tile t = L.base[idx];
-  t.prob = p;
-  return t;
+  return {p, first, b - start};
+}
+
+// The block's tile: idx is its index inside the full table (for per-tile
+// partial sums).
+__device__ __forceinline__ Tile get_tile(const TileList &L, int &idx) {
+  const Range g = get_range(L);
+  idx = g.first + g.block;
+  const TileRec r = L.base[idx];
+  return {g.prob, r.x0, r.y0, r.z0, (int)(r.ext & 255), (int)(r.ext >> 8 & 255),
+          (int)(r.ext >> 16)};
 }
 
 __device__ __forceinline__ Tile get_tile(const TileList &L) {

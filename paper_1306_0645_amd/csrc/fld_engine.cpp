@@ -69,20 +69,41 @@ static bool box_level(const fld_params &p, int l, long long cells) {
   return cells < kBoxCells;
 }
 
-// Box of a box pass: up to 16 x 8 x 4 cells, halved while that leaves fewer
-// than 256 boxes (one per CU), down to 8 x 4 x 4.
+// Box of a box pass: 16 x 8 x 4 cells; in a level of at most 8 cells along x
+// or 4 along y, which would cut it, as many cells deeper along y or z (8 x 16 x
+// 4, 16 x 4 x 8 and the others fit the same buffers).  Halved while that leaves
+// fewer than 256 boxes (one per CU), down to 8 x 4 x 4.
 void box_shape(int nx, int ny, int nz, int &tx, int &ty, int &tz) {
-  tx = kBoxX;
-  ty = kBoxY;
-  tz = kBoxZ;
-  auto count = [&] {
-    return (long long)((nx + tx - 1) / tx) * ((ny + ty - 1) / ty) * ((nz + tz - 1) / tz);
+  constexpr int cells = kBoxX * kBoxY * kBoxZ;
+  tx = nx > kBoxX / 2 ? kBoxX : kBoxX / 2;
+  ty = cells / kBoxZ / tx;
+  while (ty > 4 && ny <= ty / 2) ty >>= 1;
+  tz = cells / (tx * ty);
+  auto few = [&] {
+    return (long long)((nx + tx - 1) / tx) * ((ny + ty - 1) / ty) * ((nz + tz - 1) / tz) < 256;
   };
-  if (count() < 256) tx = 8;
-  if (count() < 256) ty = 4;
+  if (few()) tx = kBoxX / 2;
+  while (ty > 4 && few()) ty >>= 1;
+  while (tz > 4 && few()) tz >>= 1;
   tx = std::min(tx, nx);
   ty = std::min(ty, ny);
   tz = std::min(tz, nz);
+}
+
+// The boxes of a level; false if a box's index cannot be divided by
+// multiplication: u m / 2^32 = u / d + u e / (d 2^32) with e = m d - 2^32 <= d,
+// exact for u < n while n d <= 2^32 (a level below kBoxCells has at most 2^15
+// boxes).
+bool box_rec(int nx, int ny, int nz, BoxRec &r) {
+  int tx, ty, tz;
+  box_shape(nx, ny, nz, tx, ty, tz);
+  r.nbx = (nx + tx - 1) / tx;
+  r.nby = (ny + ty - 1) / ty;
+  r.mx = r.nbx > 1 ? (unsigned)((1ULL << 32) / r.nbx) + 1 : 0;
+  r.my = r.nby > 1 ? (unsigned)((1ULL << 32) / r.nby) + 1 : 0;
+  r.ext = tx | ty << 8 | tz << 16;
+  const unsigned long long rows = (unsigned long long)r.nby * ((nz + tz - 1) / tz);
+  return rows * r.nbx * r.nbx <= 1ULL << 32 && rows * r.nby <= 1ULL << 32;
 }
 
 // Full 2x coarsening while every extent stays even.  Automatic depth stops
@@ -121,8 +142,9 @@ Hier make_hier(const fld_grid &g, const fld_params &p) {
     --h.tail_sweeps;
   for (int l = 0; l < h.levels; ++l) {
     h.tiles[l] = count_tiles(p, h.n[l][0], h.n[l][1], h.n[l][2]);
-    h.box[l] = box_level(p, l, h.cells(l));
     if (l >= h.tail) continue;  // (no pass of its own)
+    BoxRec r;
+    h.box[l] = box_level(p, l, h.cells(l)) && box_rec(h.n[l][0], h.n[l][1], h.n[l][2], r);
     int tx, ty, tz;
     if (h.box[l]) box_shape(h.n[l][0], h.n[l][1], h.n[l][2], tx, ty, tz);
     else fused_shape(p, l, h.n[l][0], h.n[l][1], h.n[l][2], tx, ty, tz);
@@ -218,6 +240,15 @@ int count_tiles(const fld_params &p, int nx, int ny, int nz) {
   return ((nx + tx - 1) / tx) * ((ny + ty - 1) / ty) * ((nz + tz - 1) / tz);
 }
 
+// Doubles of memory that the coarsest solve works in (k_vtail): none where
+// it keeps its vectors in registers and LDS (and where a single level has no
+// solve), the solution where it streams the operator, four vectors beyond.
+static size_t coarse_scratch(const Hier &h) {
+  const size_t n = (size_t)h.cells(h.levels - 1);
+  if (h.levels == 1 || n <= kTailSmall) return 0;
+  return n <= kTailBig ? n : 4 * n;
+}
+
 void carve_problem(Carver &cv, const Hier &h, const fld_params &p, ProbMem &m) {
   const bool mixed = p.precision == FLD_PREC_MIXED;
   const bool jacobi = p.smoother == FLD_SMOOTH_JACOBI;
@@ -285,7 +316,7 @@ void carve_problem(Carver &cv, const Hier &h, const fld_params &p, ProbMem &m) {
   m.pd.levels = h.levels;
   m.pd.tail = h.tail;
   m.pd.tail_sweeps = h.tail_sweeps;
-  m.pd.cs = cv.take<double>(4 * (size_t)h.cells(h.levels - 1));
+  m.pd.cs = cv.take<double>(coarse_scratch(h));
   m.E_work = cv.take<double>((size_t)h.cells(0));
   for (int k = 0; k < 3; ++k) m.pd.xb[k] = m.xb[k];
   m.pd.Ework = m.E_work;
@@ -298,20 +329,25 @@ size_t problem_bytes(const Hier &h, const fld_params &p) {
   return align_up(cv.off);
 }
 
-static size_t tables_layout(Carver &cv, const std::vector<Hier> &hs,
+// slots: independent range regions (kListSlots for a server, whose phases
+// have lists of their own, else 1)
+static size_t tables_layout(Carver &cv, const std::vector<Hier> &hs, int slots,
                             Engine *e) {
   const int np = (int)hs.size();
   size_t ntiles = 0, nfine = 0, nstd = 0, nranges = 0;
   bool local = false;
+  int lmax = 0;
   for (const Hier &h : hs) {
-    for (int l = 0; l < h.levels; ++l) ntiles += h.tiles[l] + h.ftiles[l];
+    for (int l = 0; l < h.levels; ++l)
+      ntiles += h.tiles[l] + (h.box[l] ? 0 : h.ftiles[l]);
     nfine += h.tiles[0] + h.ftiles[0];  // partial slots: both finest tilings
     nstd += h.tiles[0];                 // (the standard tiles come first)
     local = local || h.local;
+    lmax = std::max(lmax, h.levels);
   }
   // fine, the two SpMV lists and kListsPerLevel lists per level: at most
-  // one range per problem and list, 3 ints each, kListSlots sets
-  nranges = (size_t)(kListsPerLevel * kMaxLevels + 3) * np * 3 * kListSlots;
+  // one range per problem and list, 3 ints each
+  nranges = (size_t)(kListsPerLevel * lmax + 3) * np * 3 * slots;
   LevelDev *lv = cv.take<LevelDev>((size_t)kMaxLevels * np);
   ProbDev *pd = cv.take<ProbDev>(np);
   StepDev *sd = cv.take<StepDev>(np);
@@ -320,7 +356,7 @@ static size_t tables_layout(Carver &cv, const std::vector<Hier> &hs,
   double *lpart = cv.take<double>(local ? 2 * std::max<size_t>(nstd, 1) : 0);
   CtlDev *ctl = cv.take<CtlDev>(std::max(np, 1));
   double *gpart = cv.take<double>(kAsmSums * std::max<size_t>(nstd, 1));
-  Tile *tiles = cv.take<Tile>(std::max<size_t>(ntiles, 1));
+  TileRec *tiles = cv.take<TileRec>(std::max<size_t>(ntiles, 1));
   int *ranges = cv.take<int>(nranges);
   if (e) {
     e->T.lv = lv;
@@ -334,14 +370,14 @@ static size_t tables_layout(Carver &cv, const std::vector<Hier> &hs,
     e->T.nprob = np;
     e->d_tiles = tiles;
     e->d_ranges = ranges;
-    e->ranges_cap = nranges;
+    e->slot_cap = nranges / slots;
   }
   return align_up(cv.off);
 }
 
-size_t tables_bytes(const std::vector<Hier> &hs) {
+size_t tables_bytes(const std::vector<Hier> &hs, int slots) {
   Carver cv;
-  return tables_layout(cv, hs, nullptr);
+  return tables_layout(cv, hs, slots, nullptr);
 }
 
 Engine::~Engine() { release_graph(); }
@@ -364,7 +400,7 @@ int Engine::release_graph() {
 
 int Engine::setup(const fld_params &p, hipStream_t s,
                   const std::vector<fld_grid> &g, Carver &tbl,
-                  std::vector<Carver> &pm) {
+                  std::vector<Carver> &pm, int slots) {
   prm = p;
   stream = s;
   mixed = p.precision == FLD_PREC_MIXED;
@@ -378,9 +414,9 @@ int Engine::setup(const fld_params &p, hipStream_t s,
     hier[i] = make_hier(g[i], p);
     Lmax = std::max(Lmax, hier[i].levels);
     if (hier[i].levels > 1)
-      tail_routes |= hier[i].cells(hier[i].levels - 1) > 2 * kTailBlock ? 2 : 1;
+      tail_routes |= hier[i].cells(hier[i].levels - 1) > kTailSmall ? 2 : 1;
   }
-  tables_layout(tbl, hier, this);
+  tables_layout(tbl, hier, slots, this);
   for (int i = 0; i < np; ++i) {
     // the caller sized each problem's block with the dry run (problem_bytes):
     // a carve that takes more would write past the block, so refuse it
@@ -391,27 +427,23 @@ int Engine::setup(const fld_params &p, hipStream_t s,
 
   // full tile table, level-major; within a level the standard tiles of every
   // problem, then the fused-cycle tiles, so both finest tilings come first
-  // (their indices are the partial-sum slots)
+  // (their indices are the partial-sum slots).  A level run box by box has
+  // none; the partial-sum slots of finest boxes follow those of the tiles
   fused = fused_cycle(p);
   lazy = lazy_iteration(p);
   h_tiles.clear();
   tbeg.assign((size_t)np * kMaxLevels, 0);
   fbeg.assign((size_t)np * kMaxLevels, 0);
-  auto emit = [&](int i, int nx, int ny, int nz, int tx, int ty, int tz) {
+  auto emit = [&](int nx, int ny, int nz, int tx, int ty, int tz) {
     for (int z0 = 0; z0 < nz; z0 += tz)
       for (int y0 = 0; y0 < ny; y0 += ty)
         for (int x0 = 0; x0 < nx; x0 += tx) {
-          Tile t;
-          t.prob = i;
-          t.x0 = x0;
-          t.y0 = y0;
-          t.z0 = z0;
-          t.tx = std::min(tx, nx - x0);
-          t.ty = std::min(ty, ny - y0);
-          t.tz = std::min(tz, nz - z0);
-          h_tiles.push_back(t);
+          const unsigned ex = std::min(tx, nx - x0), ey = std::min(ty, ny - y0),
+                         ez = std::min(tz, nz - z0);
+          h_tiles.push_back({x0, y0, z0, ex | ey << 8 | ez << 16});
         }
   };
+  int box0 = 0;  // partial-sum slot of the next problem's boxes
   for (int l = 0; l < Lmax; ++l) {
     for (int i = 0; i < np; ++i) {
       if (l >= hier[i].levels) continue;
@@ -419,18 +451,18 @@ int Engine::setup(const fld_params &p, hipStream_t s,
       const int nx = hier[i].n[l][0], ny = hier[i].n[l][1], nz = hier[i].n[l][2];
       int tx, ty, tz;
       tile_shape(prm, nx, ny, nz, tx, ty, tz);
-      emit(i, nx, ny, nz, tx, ty, tz);
+      emit(nx, ny, nz, tx, ty, tz);
     }
     for (int i = 0; i < np; ++i) {
       if (l >= hier[i].levels) continue;
       fbeg[(size_t)i * kMaxLevels + l] = (int)h_tiles.size();
-      if (!hier[i].ftiles[l]) continue;
+      if (!hier[i].ftiles[l] || hier[i].box[l]) continue;
       const int nx = hier[i].n[l][0], ny = hier[i].n[l][1], nz = hier[i].n[l][2];
       int tx, ty, tz;
-      if (hier[i].box[l]) box_shape(nx, ny, nz, tx, ty, tz);
-      else fused_shape(prm, l, nx, ny, nz, tx, ty, tz);
-      emit(i, nx, ny, nz, tx, ty, tz);
+      fused_shape(prm, l, nx, ny, nz, tx, ty, tz);
+      emit(nx, ny, nz, tx, ty, tz);
     }
+    if (l == 0) box0 = (int)h_tiles.size();
   }
   h_lv.assign((size_t)kMaxLevels * np, LevelDev{});
   h_pd.resize(np);
@@ -443,12 +475,17 @@ int Engine::setup(const fld_params &p, hipStream_t s,
   xold.assign(np, -1);
   warm_now.assign(np, 0);
   for (int i = 0; i < np; ++i) {
-    for (int l = 0; l < hier[i].levels; ++l) h_lv[(size_t)l * np + i] = mem[i].lv[l];
+    for (int l = 0; l < hier[i].levels; ++l) {
+      LevelDev &L = h_lv[(size_t)l * np + i];
+      L = mem[i].lv[l];
+      if (hier[i].box[l]) box_rec(L.nx, L.ny, L.nz, L.box);
+    }
     h_pd[i] = mem[i].pd;
     h_pd[i].t0 = tbeg[(size_t)i * kMaxLevels];
     h_pd[i].t1 = h_pd[i].t0 + hier[i].tiles[0];
-    h_pd[i].f0 = fbeg[(size_t)i * kMaxLevels];
+    h_pd[i].f0 = hier[i].box[0] ? box0 : fbeg[(size_t)i * kMaxLevels];
     h_pd[i].f1 = h_pd[i].f0 + hier[i].ftiles[0];
+    if (hier[i].box[0]) box0 = h_pd[i].f1;
     h_pd[i].spf = mixed && spmv_on_fused(hier[i]) ? 1 : 0;
     set_x(i);
     h_sc[i].phase = PH_DONE;
@@ -469,8 +506,7 @@ int Engine::setup(const fld_params &p, hipStream_t s,
 // Range lists of every launch kind for the problems flagged in member.
 int Engine::build_lists(const std::vector<char> &member, int slot, ListSet &out) {
   const int np = (int)hier.size();
-  const size_t per_slot = ranges_cap / kListSlots;
-  int *slot_base = d_ranges + per_slot * slot;
+  int *slot_base = d_ranges + slot_cap * slot;
   h_ranges.clear();
   auto make_any = [&](int level, bool fz, auto pred) {
     TileList L{};
@@ -517,7 +553,7 @@ int Engine::build_lists(const std::vector<char> &member, int slot, ListSet &out)
     out.bsm[l] = make_any(l, true, [&](int i) { return smoothed(i) && hier[i].box[l]; });
     out.bdn[l] = make_any(l, true, [&](int i) { return downs(i) && hier[i].box[l]; });
   }
-  if (h_ranges.size() > per_slot) return ST_EINVAL;
+  if (h_ranges.size() > slot_cap) return ST_EINVAL;
   if (!h_ranges.empty())
     HIP_TRY(hipMemcpyAsync(slot_base, h_ranges.data(), sizeof(int) * h_ranges.size(),
                            hipMemcpyHostToDevice, stream));
@@ -530,7 +566,7 @@ int Engine::upload_all() {
                          hipMemcpyHostToDevice, stream));
   HIP_TRY(hipMemcpyAsync(T.pd, h_pd.data(), sizeof(ProbDev) * np,
                          hipMemcpyHostToDevice, stream));
-  HIP_TRY(hipMemcpyAsync(d_tiles, h_tiles.data(), sizeof(Tile) * h_tiles.size(),
+  HIP_TRY(hipMemcpyAsync(d_tiles, h_tiles.data(), sizeof(TileRec) * h_tiles.size(),
                          hipMemcpyHostToDevice, stream));
   int st = upload_sd_sc();
   if (st) return st;

@@ -35,7 +35,7 @@ struct Hier {
   int tail = 1, tail_sweeps = 1;
   int n[kMaxLevels][3] = {};
   int tiles[kMaxLevels] = {};   // tiles per level
-  int ftiles[kMaxLevels] = {};  // fused-cycle tiles (or boxes) per level
+  int ftiles[kMaxLevels] = {};  // fused-cycle tiles (or boxes) per level, 0 in the tail
   bool box[kMaxLevels] = {};    // the fused cycle runs the level box by box
   bool local = false;           // the cycle may end with local sweeps
   long long cells(int l) const { return (long long)n[l][0] * n[l][1] * n[l][2]; }
@@ -51,11 +51,12 @@ void fused_shape(const fld_params &p, int l, int nx, int ny, int nz, int &tx,
                  int &ty, int &tz);
 int count_fused_tiles(const fld_params &p, int l, int nx, int ny, int nz);
 void box_shape(int nx, int ny, int nz, int &tx, int &ty, int &tz);
+bool box_rec(int nx, int ny, int nz, BoxRec &r);
 bool fused_cycle(const fld_params &p);
 bool lazy_iteration(const fld_params &p);
 bool spmv_on_fused(const Hier &h);
 size_t problem_bytes(const Hier &h, const fld_params &p);
-size_t tables_bytes(const std::vector<Hier> &hs);
+size_t tables_bytes(const std::vector<Hier> &hs, int slots = 1);
 
 // device memory of one problem
 struct ProbMem {
@@ -109,7 +110,7 @@ class Engine {
   std::vector<ProbDev> h_pd;
   std::vector<StepDev> h_sd;
   std::vector<Scal> h_sc;
-  std::vector<Tile> h_tiles;
+  std::vector<TileRec> h_tiles;
   std::vector<int> h_ranges;
   std::vector<int> tbeg;   // [p * kMaxLevels + l] first tile of (p, l)
   std::vector<int> fbeg;   // [p * kMaxLevels + l] first fused tile of (p, l)
@@ -130,9 +131,9 @@ class Engine {
   std::vector<char> warm_now;  // the current substep started from a warm guess
 
   Tables T{};
-  Tile *d_tiles = nullptr;
+  TileRec *d_tiles = nullptr;
   int *d_ranges = nullptr;
-  size_t ranges_cap = 0;   // ints available at d_ranges (all slots)
+  size_t slot_cap = 0;     // ints of one slot at d_ranges
   ListSet all;             // every problem (slot 0)
 
   // captured K-iteration batches, by K
@@ -152,7 +153,7 @@ class Engine {
 
   // lay out tables (in tbl) and problems (in pm[i]) and upload descriptors
   int setup(const fld_params &p, hipStream_t s, const std::vector<fld_grid> &g,
-            Carver &tbl, std::vector<Carver> &pm);
+            Carver &tbl, std::vector<Carver> &pm, int slots = 1);
   int upload_all();
   int upload_sd_sc();
   int download_sc();

@@ -16,6 +16,9 @@ constexpr int kBlock = 256;          // threads per tile block (4 wave64)
 constexpr int kFinBlock = 1024;      // threads of the per-problem finalize
 constexpr int kTailBlock = 1024;     // threads of the V-cycle tail kernel
 constexpr int kTailTop = 4 * kTailBlock;  // cells of the largest level it holds in LDS
+// cells of the largest coarsest level that it solves from registers, and from
+// registers and LDS with the operator streamed
+constexpr int kTailSmall = 2 * kTailBlock, kTailBig = 16 * kTailBlock;
 constexpr int kMaxLevels = 12;
 constexpr int kBoxX = 16, kBoxY = 8, kBoxZ = 4;  // largest box of a box pass
 
@@ -51,9 +54,19 @@ enum : int {
   PH_DONE = 2      // final status decided
 };
 
+// The boxes of a level that runs box by box (fld_box.hip).  A table entry a
+// box, of 128 to 512 cells, would take more memory than the tiles that the
+// boxes replace.  nbx, nby: boxes along x and y; mx, my: 2^32 / nbx + 1 and
+// 2^32 / nby + 1 (0: one), by which a kernel divides a box's index (get_box).
+struct BoxRec {
+  unsigned nbx, nby, mx, my;
+  unsigned ext;  // of a whole box, tx + 2^8 ty + 2^16 tz
+};
+
 // One multigrid level of one problem.
 struct LevelDev {
   int nx, ny, nz, n;
+  BoxRec box;
   gptr<double> Tx, Ty, Tz, diag;     // FP64: -A_{p,p+e_d} on +faces; A_pp
   gptr<float> Tx32, Ty32, Tz32, diag32; // FP32 copies (mixed precision)
   gptr<void> x;                      // V-cycle iterate (level precision);
@@ -179,8 +192,18 @@ struct CtlDev {
 struct Tile {
   int prob;
   int x0, y0, z0;
-  unsigned short tx, ty, tz, unused;
+  int tx, ty, tz;
 };
+
+// A tile as the table holds it, 16 bytes: the problem comes with the range
+// (TileList), and no tile is wider than 64 cells or deeper than 256 planes, so
+// its extents share a word (one word, since narrower members are not read by
+// scalar loads).
+struct alignas(16) TileRec {
+  int x0, y0, z0;
+  unsigned ext;  // tx + 2^8 ty + 2^16 tz
+};
+static_assert(sizeof(TileRec) == 16, "one 16-byte load");
 
 // Launch context: the tables live in device memory.
 // per-tile sums of the assembly: ||b||^2, ||b - A x0||^2 (extrapolated
@@ -203,9 +226,10 @@ struct Tables {
 // A launch covers a subset of the full tile table: ranges[3r] is the first
 // block of range r, ranges[3r+1] the tile it maps to, ranges[3r+2] the problem
 // of its tiles; ranges are sorted by block.  nblocks = total blocks of the
-// launch.  first, prob: the tile and the problem of range 0.
+// launch.  first, prob: the tile and the problem of range 0.  (The boxes of a
+// level have no entries in the table: LevelDev::box.)
 struct TileList {
-  gptr<const Tile> base; // device: full tile table
+  gptr<const TileRec> base; // device: full tile table
   gptr<const int> ranges; // device: 3 * nranges ints
   int nranges;
   int nblocks;

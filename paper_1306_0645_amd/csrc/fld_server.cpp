@@ -165,7 +165,7 @@ int fld_server::rebuild() {
     hs.push_back(q->hier);
   }
   if (!resident.empty()) {
-    new_sz = tables_bytes(hs);
+    new_sz = tables_bytes(hs, kListSlots);
     if (!alloc.alloc(new_sz, new_off)) return ST_ENOMEM;
   }
   if (have_tables) alloc.release(tables_off, tables_sz);
@@ -179,7 +179,7 @@ int fld_server::rebuild() {
   for (size_t i = 0; i < resident.size(); ++i) pm[i].base = arena + resident[i]->off;
   eng = new (std::nothrow) Engine;
   if (!eng) return ST_ENOMEM;
-  int st = eng->setup(prm, stream, gs, tbl, pm);
+  int st = eng->setup(prm, stream, gs, tbl, pm, kListSlots);
   if (st) return st;
   for (size_t i = 0; i < resident.size(); ++i) {
     Req *q = resident[i];
@@ -374,7 +374,7 @@ void fld_server::run() {
         std::vector<Hier> hs2 = hs;
         hs2.push_back(q->hier);
         size_t off = 0;
-        const size_t tb = tables_bytes(hs2);
+        const size_t tb = tables_bytes(hs2, kListSlots);
         bool ok = alloc.alloc(q->bytes, off);
         if (ok) {
           size_t toff = 0;
@@ -467,7 +467,7 @@ fld_status fld_server_submit(fld_server *s, const fld_request *r,
   q->hier = make_hier(r->grid, s->prm);
   q->bytes = problem_bytes(q->hier, s->prm);
   std::vector<Hier> one{q->hier};
-  if (q->bytes + tables_bytes(one) + 1024 > s->arena_bytes) {
+  if (q->bytes + tables_bytes(one, kListSlots) + 1024 > s->arena_bytes) {
     delete q;
     return FLD_ENOMEM;
   }

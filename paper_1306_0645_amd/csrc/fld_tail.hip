@@ -740,9 +740,6 @@ __device__ __forceinline__ void level_cg(const LevelDev &L, double *xm, double *
   }
 }
 
-// cells of a coarsest level solved from registers and LDS, by LDS size
-constexpr int kTailSmall = 2 * kTailBlock, kTailBig = 16 * kTailBlock;
-
 template <typename R, int CAP>
 __global__ __launch_bounds__(kTailBlock) void k_vtail(Tables T, int nu_pre,
                                                      int nu_post, int trilinear, int sweeps) {
