@@ -242,11 +242,12 @@ int count_tiles(const fld_params &p, int nx, int ny, int nz) {
 
 // Doubles of memory that the coarsest solve works in (k_vtail): none where
 // it keeps its vectors in registers and LDS (and where a single level has no
-// solve), the solution where it streams the operator, four vectors beyond.
+// solve), the solution and the reciprocal diagonal where it streams the
+// operator, four vectors beyond.
 static size_t coarse_scratch(const Hier &h) {
   const size_t n = (size_t)h.cells(h.levels - 1);
   if (h.levels == 1 || n <= kTailSmall) return 0;
-  return n <= kTailBig ? n : 4 * n;
+  return n <= kTailBig ? 2 * n : 4 * n;
 }
 
 void carve_problem(Carver &cv, const Hier &h, const fld_params &p, ProbMem &m) {

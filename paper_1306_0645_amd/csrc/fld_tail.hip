@@ -13,8 +13,7 @@
 // row operations, then every wave sums the 16 wave results), and a coarsest
 // level of at most 64 cells is solved by one wave without any barrier.  The
 // CG carries r.z and ||r||^2 through one reduction and scales by the
-// approximate reciprocal of the diagonal (any fixed positive scaling leads to
-// the same solution; an exact division costs 16 times the instructions).
+// reciprocal of the diagonal, divided once a solve.
 // A coarsest level of up to 16 x 1024 cells (extents that stop halving early,
 // such as 25^3 under 200^3) keeps r, x and q in registers and p in LDS, and
 // streams the operator from the L2 in each iteration.  Measured per cycle
@@ -50,10 +49,10 @@ __device__ __forceinline__ void tail_sums(double (&v)[N], double *red, int &slot
 
 // ---- coarsest solve ----------------------------------------------------------
 
-// operator of one cell: its six faces and diagonal, and the neighbours'
-// indices
+// operator of one cell: its six faces, diagonal and its reciprocal, and the
+// neighbours' indices
 struct CgCell {
-  double xp, xm, yp, ym, zp, zm, d;
+  double xp, xm, yp, ym, zp, zm, d, id;
   Nb n;
 };
 
@@ -83,7 +82,8 @@ __device__ __forceinline__ double cg_row(const CgCell &a, const double *p) {
 // calls it.  WAVE: n <= 64, only wave 0 works and no barrier is taken.
 // HOLD: the operator (cell[u], loaded by the caller) and x stay in registers;
 // otherwise the operator is read in each iteration, two cells' loads at a
-// time (all 16 at once would spill), and x accumulates in xm (memory).
+// time (all 16 at once would spill), x accumulates in xm (memory) and the
+// reciprocal diagonal lies behind it.
 template <int CPT, bool WAVE, bool HOLD>
 __device__ __forceinline__ void coarse_cg(const LevelDev &L, CgCell (&cell)[HOLD ? CPT : 1],
                                           const double (&f)[CPT], double (&x)[HOLD ? CPT : 1],
@@ -113,8 +113,14 @@ __device__ __forceinline__ void coarse_cg(const LevelDev &L, CgCell (&cell)[HOLD
     r[u] = 0.0;
     if (c < n) {
       r[u] = f[u];
-      if constexpr (!HOLD) xm[c] = 0.0;
-      const double t = r[u] * __builtin_amdgcn_rcp(HOLD ? cell[HOLD ? u : 0].d : L.diag[c]);
+      double id;
+      if constexpr (HOLD) {
+        id = cell[u].id = 1.0 / cell[u].d;
+      } else {
+        xm[c] = 0.0;
+        xm[n + c] = id = 1.0 / L.diag[c];
+      }
+      const double t = r[u] * id;
       sp[c] = t;
       a2[0] += r[u] * r[u];
       a2[1] += r[u] * t;
@@ -184,7 +190,7 @@ __device__ __forceinline__ void coarse_cg(const LevelDev &L, CgCell (&cell)[HOLD
         if constexpr (HOLD) x[u] += alpha * sp[c];
         else xm[c] += alpha * sp[c];
         r[u] -= alpha * q[u];
-        rd[u] = r[u] * __builtin_amdgcn_rcp(HOLD ? cell[HOLD ? u : 0].d : L.diag[c]);
+        rd[u] = r[u] * (HOLD ? cell[HOLD ? u : 0].id : xm[n + c]);
         a2[0] += r[u] * r[u];
         a2[1] += r[u] * rd[u];
       }
@@ -672,7 +678,7 @@ __device__ void mem_coarse_solve(const LevelDev &L, const ProbDev &P, double *re
   int slot = 0;
   double a2[2] = {0.0, 0.0};
   for (int c = threadIdx.x; c < n; c += kTailBlock) {
-    const double v = (double)f[c], t = v * __builtin_amdgcn_rcp(L.diag[c]);
+    const double v = (double)f[c], t = v / L.diag[c];
     rs[c] = v;
     xs[c] = 0.0;
     ps[c] = t;
@@ -704,14 +710,14 @@ __device__ void mem_coarse_solve(const LevelDev &L, const ProbDev &P, double *re
         const double r = rs[c] - alpha * qs[c];
         rs[c] = r;
         a2[0] += r * r;
-        a2[1] += r * (r * __builtin_amdgcn_rcp(L.diag[c]));
+        a2[1] += r * (r / L.diag[c]);
       }
       tail_sums<2>(a2, red, slot);
       if (!(a2[0] > 1e-24 * bb)) break;  // converged (or NaN: stop)
       const double beta = a2[1] / rz;
       rz = a2[1];
       for (int c = threadIdx.x; c < n; c += kTailBlock)
-        ps[c] = rs[c] * __builtin_amdgcn_rcp(L.diag[c]) + beta * ps[c];
+        ps[c] = rs[c] / L.diag[c] + beta * ps[c];
     }
   }
   for (int c = threadIdx.x; c < n; c += kTailBlock) xo[c] = (R)xs[c];
