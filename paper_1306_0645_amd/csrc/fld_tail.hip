@@ -47,6 +47,15 @@ __device__ __forceinline__ void tail_sums(double (&v)[N], double *red, int &slot
   for (int i = 0; i < N; ++i) v[i] = row_total(s[i * kTW + (lane & (kTW - 1))]);
 }
 
+// Orders a wave's LDS accesses before and after it, for values that pass
+// between its lanes: its LDS operations execute in order, so this holds back
+// the compiler alone and costs no instruction.
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // ---- coarsest solve ----------------------------------------------------------
 
 // operator of one cell: its six faces, diagonal and its reciprocal, and the
@@ -134,7 +143,8 @@ __device__ __forceinline__ void coarse_cg(const LevelDev &L, CgCell (&cell)[HOLD
   double rz = a2[1];
   if (!(bb > 0.0)) return;
   for (int it = 0; it < 1000; ++it) {
-    // (the sums above or below ended with a barrier: p is complete)
+    // p is complete: the sums above ended with a barrier, as does the loop
+    if constexpr (WAVE) wave_sync();
     double q[CPT];
     double a1[2] = {0.0, 0.0};
     int i = i0, j = j0, k = k0;
@@ -171,6 +181,7 @@ __device__ __forceinline__ void coarse_cg(const LevelDev &L, CgCell (&cell)[HOLD
       }
     }
     if constexpr (WAVE) {
+      wave_sync();  // every lane has read p
       a1[0] = wave_total(a1[0]);
     } else {
       double b1[1] = {a1[0]};
