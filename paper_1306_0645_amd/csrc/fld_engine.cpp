@@ -90,6 +90,12 @@ void box_shape(int nx, int ny, int nz, int &tx, int &ty, int &tz) {
   tz = std::min(tz, nz);
 }
 
+int count_boxes(int nx, int ny, int nz) {
+  int tx, ty, tz;
+  box_shape(nx, ny, nz, tx, ty, tz);
+  return ((nx + tx - 1) / tx) * ((ny + ty - 1) / ty) * ((nz + tz - 1) / tz);
+}
+
 // The boxes of a level; false if a box's index cannot be divided by
 // multiplication: u m / 2^32 = u / d + u e / (d 2^32) with e = m d - 2^32 <= d,
 // exact for u < n while n d <= 2^32 (a level below kBoxCells has at most 2^15
@@ -145,11 +151,8 @@ Hier make_hier(const fld_grid &g, const fld_params &p) {
     if (l >= h.tail) continue;  // (no pass of its own)
     BoxRec r;
     h.box[l] = box_level(p, l, h.cells(l)) && box_rec(h.n[l][0], h.n[l][1], h.n[l][2], r);
-    int tx, ty, tz;
-    if (h.box[l]) box_shape(h.n[l][0], h.n[l][1], h.n[l][2], tx, ty, tz);
-    else fused_shape(p, l, h.n[l][0], h.n[l][1], h.n[l][2], tx, ty, tz);
-    h.ftiles[l] = ((h.n[l][0] + tx - 1) / tx) * ((h.n[l][1] + ty - 1) / ty) *
-                  ((h.n[l][2] + tz - 1) / tz);
+    h.ftiles[l] = h.box[l] ? count_boxes(h.n[l][0], h.n[l][1], h.n[l][2])
+                           : count_fused_tiles(p, l, h.n[l][0], h.n[l][1], h.n[l][2]);
   }
   return h;
 }

@@ -51,6 +51,7 @@ void fused_shape(const fld_params &p, int l, int nx, int ny, int nz, int &tx,
                  int &ty, int &tz);
 int count_fused_tiles(const fld_params &p, int l, int nx, int ny, int nz);
 void box_shape(int nx, int ny, int nz, int &tx, int &ty, int &tz);
+int count_boxes(int nx, int ny, int nz);
 bool box_rec(int nx, int ny, int nz, BoxRec &r);
 bool fused_cycle(const fld_params &p);
 bool lazy_iteration(const fld_params &p);

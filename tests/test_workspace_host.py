@@ -1,8 +1,9 @@
 """Workspace sizes on the host (no GPU): no grid needs more than the sizes
 below, which an earlier layout of the tables took, so that a grid that fitted
 a workspace of the caller's, a server's arena or the 64 MiB of
-fld_step_static still fits; among them grids just under that line.  And every
-box of the box passes fits the buffers that the kernels hold it in."""
+fld_step_static still fits; among them grids just under that line.  Every
+box of the box passes fits the buffers that the kernels hold it in, and every
+level takes the route that the rules give it."""
 import pytest
 
 from test_carve_host import _run_host
@@ -47,3 +48,7 @@ def test_no_grid_needs_more(fld, shape, kw, size):
 
 def test_boxes_fit_their_buffers(tmp_path):
     _run_host(tmp_path, "box_shapes")
+
+
+def test_level_routes(tmp_path):
+    _run_host(tmp_path, "level_routes")
