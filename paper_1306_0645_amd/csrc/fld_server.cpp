@@ -196,6 +196,9 @@ int fld_server::rebuild() {
     eng->warm_now[i] = q->warm_now;
     eng->set_x((int)i);
   }
+  // (a request that restarts from its true residual still owes its finest down
+  // pass, which the engine before this one had noted)
+  eng->need_pro = true;
   st = eng->upload_pd();
   if (st) return st;
   return eng->upload_sd_sc();
