@@ -219,18 +219,19 @@ def measured_traffic(kernel, form, workload=None, root=ROOT):
 # rocprofv3 kernel names of the finest-level kernels, by (bench name, form)
 PMC_KERNELS = {
     # the fused iteration's SpMV: on the fused tiles where a grid gives 2048
-    # of them, else on the 64 x 4 tiles (the first name that ran is taken)
-    ("spmv_px", "mixed_dir64"): ("fld::k_spmv_f<2>", "fld::k_spmv_p<true, 2>"),
-    ("spmv_px", "mixed"): ("fld::k_spmv_f<1>", "fld::k_spmv_p<true, 1>"),
-    ("spmv_px", "fp64"): "fld::k_spmv_p<true, 0>",
-    ("vup_fine", "mixed"): "fld::k_vup<float, true, false>",
-    ("vup_fine", "mixed_tri"): "fld::k_vup<float, true, true>",
-    ("vup_fine", "fp64"): "fld::k_vup<double, true, false>",
-    ("vdown_fine", "mixed"): "fld::k_vdown<float, true>",
-    ("vdown_fine", "fp64"): "fld::k_vdown<double, true>",
-    ("update_r", "fp64"): "fld::k_update<0, false>",
-    ("true_resid", "any"): "fld::k_true_resid",
-    ("assemble", "any"): "fld::k_assemble",
+    # of them, else on the 64 x 4 tiles (the first name that ran is taken); the
+    # last parameter of most: streaming access, which the counted sizes take
+    ("spmv_px", "mixed_dir64"): ("fld::k_spmv_f<2>", "fld::k_spmv_p<true, 2, true>"),
+    ("spmv_px", "mixed"): ("fld::k_spmv_f<1>", "fld::k_spmv_p<true, 1, true>"),
+    ("spmv_px", "fp64"): "fld::k_spmv_p<true, 0, true>",
+    ("vup_fine", "mixed"): "fld::k_vup<float, true, false, true>",
+    ("vup_fine", "mixed_tri"): "fld::k_vup<float, true, true, true>",
+    ("vup_fine", "fp64"): "fld::k_vup<double, true, false, true>",
+    ("vdown_fine", "mixed"): "fld::k_vdown<float, true, true>",
+    ("vdown_fine", "fp64"): "fld::k_vdown<double, true, true>",
+    ("update_r", "fp64"): "fld::k_update<0, false, true>",
+    ("true_resid", "any"): "fld::k_true_resid<true>",
+    ("assemble", "any"): "fld::k_assemble<true>",
     ("local", "mixed"): "fld::k_local",
 }
 PMC_SOURCES = {

@@ -112,24 +112,21 @@ __device__ __forceinline__ Nb nbrs(int i, int j, int k, int nx, int ny, int nz) 
 }
 
 // ---------------------------------------------------------------------------
-// streaming access: a value that no other block reads or wrote in this launch
-// and that the caches cannot hold until the next one.  Marked as such it leaves
-// its place in the L2 to the cells that neighbouring tiles share (640^3, mixed:
-// a pass of three steps 577 -> 565 ms; the fused passes' face loads are not
-// marked: their edge cells are shared, and marking them cost 4 %).  The SpMV on
-// 64 x 4 tiles, which serves small grids too, streams from 2^20 cells on: a
-// 64^3 grid, whose arrays stay in the caches from one launch to the next,
-// lost 2 % by it, 128^3 grids gained 2.6 %.
+// streaming access (NT): a value that no other block reads or wrote in this
+// launch.  Marked as such it leaves its place in the caches to the cells that
+// neighbouring tiles share; but a working set that stays in the caches from
+// one launch to the next is then read from memory again.  So the launchers
+// take NT from the size of all the problems together (Tables::stream).  The
+// fused passes' face loads are never marked: their edge cells are shared, and
+// marking them cost 4 %.
 // ---------------------------------------------------------------------------
 
-__device__ __forceinline__ bool beyond_cache(int cells) { return cells >= 1 << 20; }
-
-template <bool NT = true, typename V>
+template <bool NT, typename V>
 __device__ __forceinline__ auto stream_in(const V *p) {
   if constexpr (NT) return __builtin_nontemporal_load(p);
   else return *p;
 }
-template <bool NT = true, typename V, typename W>
+template <bool NT, typename V, typename W>
 __device__ __forceinline__ void stream_out(V *p, W v) {
   if constexpr (NT) __builtin_nontemporal_store(v, p);
   else *p = v;

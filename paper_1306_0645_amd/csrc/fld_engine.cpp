@@ -402,6 +402,16 @@ int Engine::release_graph() {
   return ST_OK;
 }
 
+// Workspace of all problems together above which the launches stream (NT
+// access): the Infinity Cache holds 256 MB, and an iteration touches some 60 %
+// of the workspace.  Measured (three steps, us, never / always streaming): FP64
+// 104^3 (134 MB) 4314 / 4692, 128^3 (250 MB) 4988 / 5266, 144^3 (355 MB) 7817 /
+// 8098, 160^3 (487 MB) 10552 / 10432, 192^3 16218 / 15839; mixed 112^3 (208 MB)
+// 4292 / 4650, 128^3 (310 MB) 4517 / 4780, 144^3 (442 MB) 7733 / 7665, 192^3
+// 13459 / 13256; batches of 4 and 8 mixed problems of 32^3 to 96^3 434 / 455 and
+// 836 / 858, of 40 2657 / 2601 (streaming in the SpMV too).
+constexpr size_t kStreamBytes = size_t(400) << 20;
+
 int Engine::setup(const fld_params &p, hipStream_t s,
                   const std::vector<fld_grid> &g, Carver &tbl,
                   std::vector<Carver> &pm, int slots) {
@@ -428,6 +438,10 @@ int Engine::setup(const fld_params &p, hipStream_t s,
     carve_problem(pm[i], hier[i], p, mem[i]);
     if (align_up(pm[i].off) - start > problem_bytes(hier[i], p)) return ST_ENOMEM;
   }
+
+  size_t bytes = 0;
+  for (const Hier &h : hier) bytes += problem_bytes(h, p);
+  T.stream = bytes > kStreamBytes;
 
   // full tile table, level-major; within a level the standard tiles of every
   // problem, then the fused-cycle tiles, so both finest tilings come first

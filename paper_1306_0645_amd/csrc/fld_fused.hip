@@ -62,12 +62,12 @@ __device__ __forceinline__ void ld2(const R *p, R &u, R &v) {
   v = w.y;
 }
 
-template <typename R>
+template <bool NT, typename R>
 __device__ __forceinline__ void st2(R *p, R u, R v) {
   Vec2<R> w;
   w.x = u;
   w.y = v;
-  stream_out(reinterpret_cast<Vec2<R> *>(p), w);
+  stream_out<NT>(reinterpret_cast<Vec2<R> *>(p), w);
 }
 
 // in-plane faces of one quad: Tx, Ty at (a, b) (the + faces of each cell),
@@ -453,7 +453,7 @@ __device__ __forceinline__ Q4<R> q_store_plane(const QPlane<R, L0, UP> &pl,
   return id;
 }
 
-template <typename R, bool L0>
+template <typename R, bool L0, bool NT>
 __global__ __launch_bounds__(kBlock) void k_vdown(Tables T, TileList TL, int l,
                                                   int sel) {
   int tid;
@@ -522,8 +522,8 @@ __global__ __launch_bounds__(kBlock) void k_vdown(Tables T, TileList TL, int l,
         for (int u = 0; u < kHalo; ++u) pl.hf[u] = __builtin_fma(-alpha, hq[u], pl.hf[u]);
         if (qon && pz >= t.z0 && pz < t.z0 + t.tz) {
           const int r0 = (pz * ny + qy) * nx + qx;
-          st2(rn + r0, pl.f00, pl.f10);
-          st2(rn + r0 + nx, pl.f01, pl.f11);
+          st2<NT>(rn + r0, pl.f00, pl.f10);
+          st2<NT>(rn + r0 + nx, pl.f01, pl.f11);
           rr += pl.f00 * pl.f00;
           rr += pl.f10 * pl.f10;
           rr += pl.f01 * pl.f01;
@@ -582,7 +582,7 @@ __global__ __launch_bounds__(kBlock) void k_vdown(Tables T, TileList TL, int l,
 // take more registers than that leaves (measured at 640^3: 2.35 ms a launch
 // with three blocks and a few spilled registers, 2.64 ms with two).  The FP64
 // instances need more registers than three blocks allow whatever the bound.
-template <typename R, bool L0, bool TRI>
+template <typename R, bool L0, bool TRI, bool NT>
 __global__ __launch_bounds__(kBlock, 3) void k_vup(Tables T, TileList TL, int l,
                                                 int flexible) {
   using FT = typename QPlane<R, L0, true>::FT;
@@ -745,15 +745,15 @@ __global__ __launch_bounds__(kBlock, 3) void k_vup(Tables T, TileList TL, int l,
         if (rd_old) rzo += H.v11 * ((double)zo11 * zs_old);
         rz += H.v11 * z11;
         if constexpr (sizeof(R) == 4) {
-          st2(znew + o0, v00, v10);
-          st2(znew + o0 + nx, v01, v11);
+          st2<NT>(znew + o0, v00, v10);
+          st2<NT>(znew + o0 + nx, v01, v11);
         } else {
-          st2(znew + o0, z00, z10);
-          st2(znew + o0 + nx, z01, z11);
+          st2<NT>(znew + o0, z00, z10);
+          st2<NT>(znew + o0 + nx, z01, z11);
         }
       } else {
-        st2(xout + o0, v00, v10);
-        st2(xout + o0 + nx, v01, v11);
+        st2<NT>(xout + o0, v00, v10);
+        st2<NT>(xout + o0 + nx, v01, v11);
       }
     }
   }
@@ -762,26 +762,35 @@ __global__ __launch_bounds__(kBlock, 3) void k_vup(Tables T, TileList TL, int l,
 
 // launchers ------------------------------------------------------------------
 
+template <typename R, bool L0>
+static void launch_vdown_t(const Tables &T, TileList L, int l, int id, int sel, hipStream_t s) {
+  with_stream(T, [&](auto nt) {
+    FLD_LAUNCH(id, (k_vdown<R, L0, L0 && nt()>), L.nblocks, kBlock, s, T, L, l, sel);
+  });
+}
+
 void launch_vdown(const Tables &T, TileList L, int l, int prec, int sel,
                   hipStream_t s) {
   if (!L.nblocks) return;
   const int id = l == 0 ? K_VDOWN_F : K_VDOWN_C;
   if (prec) {
-    if (l == 0) FLD_LAUNCH(id, (k_vdown<float, true>), L.nblocks, kBlock, s, T, L, l, sel);
-    else FLD_LAUNCH(id, (k_vdown<float, false>), L.nblocks, kBlock, s, T, L, l, sel);
+    if (l == 0) launch_vdown_t<float, true>(T, L, l, id, sel, s);
+    else launch_vdown_t<float, false>(T, L, l, id, sel, s);
   } else {
-    if (l == 0) FLD_LAUNCH(id, (k_vdown<double, true>), L.nblocks, kBlock, s, T, L, l, sel);
-    else FLD_LAUNCH(id, (k_vdown<double, false>), L.nblocks, kBlock, s, T, L, l, sel);
+    if (l == 0) launch_vdown_t<double, true>(T, L, l, id, sel, s);
+    else launch_vdown_t<double, false>(T, L, l, id, sel, s);
   }
 }
 
 template <typename R, bool L0>
 static void launch_vup_t(const Tables &T, TileList L, int l, int id, int flexible,
                          int trilinear, hipStream_t s) {
-  if (trilinear)
-    FLD_LAUNCH(id, (k_vup<R, L0, true>), L.nblocks, kBlock, s, T, L, l, flexible);
-  else
-    FLD_LAUNCH(id, (k_vup<R, L0, false>), L.nblocks, kBlock, s, T, L, l, flexible);
+  with_stream(T, [&](auto nt) {
+    if (trilinear)
+      FLD_LAUNCH(id, (k_vup<R, L0, true, nt()>), L.nblocks, kBlock, s, T, L, l, flexible);
+    else
+      FLD_LAUNCH(id, (k_vup<R, L0, false, nt()>), L.nblocks, kBlock, s, T, L, l, flexible);
+  });
 }
 
 void launch_vup(const Tables &T, TileList L, int l, int prec, int flexible,

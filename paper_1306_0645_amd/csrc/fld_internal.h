@@ -10,6 +10,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 namespace fld {
 
 constexpr int kBlock = 256;          // threads per tile block (4 wave64)
@@ -221,6 +223,7 @@ struct Tables {
   gptr<CtlDev> ctl; // [nprob] device-side step control
   gptr<double> gpart; // [n finest standard tiles][kAsmSums] sums of the assembly
   int nprob;
+  int stream;       // the problems together exceed the caches (NT access)
 };
 
 // A launch covers a subset of the full tile table: ranges[3r] is the first
@@ -261,6 +264,14 @@ struct ProfScope {
     ::fld::ProfScope _ps((id), (s));                                      \
     hipLaunchKernelGGL(kern, dim3(grid), dim3(block), 0, s, __VA_ARGS__); \
   } while (0)
+
+// f(std::true_type) where the launches over T stream, else f(std::false_type):
+// the launcher's choice of a kernel's NT parameter
+template <typename F>
+inline void with_stream(const Tables &T, F f) {
+  if (T.stream) f(std::true_type{});
+  else f(std::false_type{});
+}
 
 // ---- launchers (fld_kernels.hip, fld_fused.hip) ---------------------------
 // prec: 0 = FP64 V-cycle, 1 = FP32 V-cycle.

@@ -125,6 +125,7 @@ constexpr int kEdgeZ = 8, kEdge = kEdgeZ * 64;
 // here too (local; see k_local), where their faces are at hand.  Measured at
 // 256^3, mixed, warm: 545 + 116 us with five limiters a cell and the lists in a
 // pass of their own, 494 us together.
+template <bool NT>
 __global__ __launch_bounds__(kBlock) void k_assemble(Tables T, TileList L0,
                                                      double c_light, double theta,
                                                      double dmax, double rmin,
@@ -239,7 +240,7 @@ __global__ __launch_bounds__(kBlock) void k_assemble(Tables T, TileList L0,
       const double LE = (Dxp * (Exp - Ec) - Dxm * (Ec - Exm)) * ix2 +
                         (Dyp * (Eyp - Ec) - Dym * (Ec - Eym)) * iy2 +
                         (Dzp * (Ep - Ec) - Dzm * (Ec - Em)) * iz2 - mu * Ec;
-      const double b = S.dt * (LE + stream_in(&eta[cc]));
+      const double b = S.dt * (LE + stream_in<NT>(&eta[cc]));
       const double tx = tdt * Dxp * ix2, ty = tdt * Dyp * iy2, tz = tdt * Dzp * iz2;
       const double txm = tdt * Dxm * ix2, tym = tdt * Dym * iy2, tzm = tdt * Dzm * iz2;
       if (local && tx + txm + ty + tym + tz + tzm > coupling * diag) {
@@ -247,17 +248,17 @@ __global__ __launch_bounds__(kBlock) void k_assemble(Tables T, TileList L0,
         if ((i + j + k) & 1) ++m1;
         else ++m0;
       }
-      stream_out(&Tx[cc], tx);
-      stream_out(&Ty[cc], ty);
-      stream_out(&Tz[cc], tz);
-      stream_out(&Dg[cc], diag);
+      stream_out<NT>(&Tx[cc], tx);
+      stream_out<NT>(&Ty[cc], ty);
+      stream_out<NT>(&Tz[cc], tz);
+      stream_out<NT>(&Dg[cc], diag);
       if (mixed) {
-        stream_out(&L.Tx32[cc], (float)tx);
-        stream_out(&L.Ty32[cc], (float)ty);
-        stream_out(&L.Tz32[cc], (float)tz);
-        stream_out(&L.diag32[cc], (float)diag);
+        stream_out<NT>(&L.Tx32[cc], (float)tx);
+        stream_out<NT>(&L.Ty32[cc], (float)ty);
+        stream_out<NT>(&L.Tz32[cc], (float)tz);
+        stream_out<NT>(&L.diag32[cc], (float)diag);
       }
-      stream_out(&bv[cc], b);
+      stream_out<NT>(&bv[cc], b);
       bb += b * b;
       if (gal) {
         // A h at the cell for h = dE(n) and dE(n-1); x and r are k_warm_x's
@@ -286,14 +287,14 @@ __global__ __launch_bounds__(kBlock) void k_assemble(Tables T, TileList L0,
                            ty * guess(cc + dyp) + tym * guess(cc + dym) +
                            tz * gp + tzm * gm;
         const double r = b - (diag * gc - off);
-        stream_out(&xv[cc], gc);
-        stream_out(&rv[cc], r);
+        stream_out<NT>(&xv[cc], gc);
+        stream_out<NT>(&rv[cc], r);
         rr += r * r;
         gm = gc;
         gc = gp;
       } else {
-        stream_out(&xv[cc], 0.0);
-        stream_out(&rv[cc], b);
+        stream_out<NT>(&xv[cc], 0.0);
+        stream_out<NT>(&rv[cc], b);
       }
       Em = Ec;
       Km = Kc;
@@ -828,7 +829,7 @@ __device__ __forceinline__ double spmv_column(
   return acc;
 }
 
-template <bool LAZY, int KM>
+template <bool LAZY, int KM, bool NT>
 __global__ __launch_bounds__(kBlock) void k_spmv_p(Tables T, TileList TL) {
   int tid;
   const Tile t = get_tile(TL, tid);
@@ -840,11 +841,8 @@ __global__ __launch_bounds__(kBlock) void k_spmv_p(Tables T, TileList TL) {
   double pq = 0.0;
   if (col.on) {
     auto run = [&](auto S) {
-      if (beyond_cache(L.n))
-        return spmv_column<true>(t, col, L.nx, L.ny, L.nz, S, dir_next<KM>(P, sc), P.q, L.Tx,
-                                 L.Ty, L.Tz, L.diag, P.x);
-      return spmv_column<false>(t, col, L.nx, L.ny, L.nz, S, dir_next<KM>(P, sc), P.q, L.Tx,
-                                L.Ty, L.Tz, L.diag, P.x);
+      return spmv_column<NT>(t, col, L.nx, L.ny, L.nz, S, dir_next<KM>(P, sc), P.q, L.Tx, L.Ty,
+                             L.Tz, L.diag, P.x);
     };
     if constexpr (LAZY) {
       if (sc.lag) {
@@ -873,6 +871,7 @@ __global__ __launch_bounds__(kBlock) void k_spmv_p(Tables T, TileList TL) {
 // are held, where reading them again a plane later would miss the L2, which
 // holds less than one plane of all the resident tiles.  Per cell the
 // arithmetic is spmv_column's, term by term, so q and p are the same.
+// (Always streaming: 2048 such tiles are beyond the caches.)
 constexpr int kSpRows = 4;
 
 template <int F, bool BASE, int KM>
@@ -930,10 +929,10 @@ __device__ __forceinline__ double spmv_rows(
         const double sm = Tx[c] * S.val(xr) + Tx[c + dxm] * S.val(xl) + tyc * S.val(up) +
                           tyd * S.val(dn) + Tz[c] * S.val(pp[r]) + tzm[r] * S.val(pm[r]);
         const double p_c = S.val(pc[r]);
-        const double qq = stream_in(&Dg[c]) * p_c - sm;
-        if constexpr (F == F_STORE) stream_out(&x[c], S.advance(stream_in(&x[c]), oc[r], mc[r]));
-        if constexpr (F != F_SKIP) stream_out(&pn[c], pc[r]);
-        stream_out(&q[c], qq);
+        const double qq = stream_in<true>(&Dg[c]) * p_c - sm;
+        if constexpr (F == F_STORE) stream_out<true>(&x[c], S.advance(stream_in<true>(&x[c]), oc[r], mc[r]));
+        if constexpr (F != F_SKIP) stream_out<true>(&pn[c], pc[r]);
+        stream_out<true>(&q[c], qq);
         acc += p_c * qq;
         tzm[r] = Tz[c];
         tyd = tyc;
@@ -1036,7 +1035,7 @@ __global__ __launch_bounds__(kBlock) void k_xfix(Tables T, TileList TL) {
 }
 
 // r -= alpha q, partial ||r||^2, and (X) x += alpha p
-template <int KM, bool X>
+template <int KM, bool X, bool NT>
 __global__ __launch_bounds__(kBlock) void k_update(Tables T, TileList TL) {
   int tid;
   const Tile t = get_tile(TL, tid);
@@ -1054,9 +1053,9 @@ __global__ __launch_bounds__(kBlock) void k_update(Tables T, TileList TL) {
     const int plane = L.nx * L.ny;
     int c = t.z0 * plane + col.j * L.nx + col.i;
     for (int k = 0; k < t.tz; ++k, c += plane) {
-      if constexpr (X) stream_out(&x[c], stream_in(&x[c]) + alpha * newest_p<KM>(P, sc, c));
-      const double rn = r[c] - alpha * stream_in(&q[c]);
-      stream_out(&r[c], rn);
+      if constexpr (X) stream_out<NT>(&x[c], stream_in<NT>(&x[c]) + alpha * newest_p<KM>(P, sc, c));
+      const double rn = r[c] - alpha * stream_in<NT>(&q[c]);
+      stream_out<NT>(&r[c], rn);
       rr += rn * rn;
     }
   }
@@ -1069,6 +1068,7 @@ __global__ __launch_bounds__(kBlock) void k_update(Tables T, TileList TL) {
 // carried to the next one, and the stores cannot alias the loads.  256^3
 // mixed, a pass of three steps: 15.71 -> 15.65 ms; 4 groups of 128^3 7.77 ->
 // 7.72)
+template <bool NT>
 __global__ __launch_bounds__(kBlock) void k_true_resid(Tables T, TileList TL) {
   int tid;
   const Tile t = get_tile(TL, tid);
@@ -1097,8 +1097,8 @@ __global__ __launch_bounds__(kBlock) void k_true_resid(Tables T, TileList TL) {
       const double x_p = x[cp], tz_c = Tz[c];
       const double off = Tx[c] * x[c + dxp] + Tx[c + dxm] * x[c + dxm] + Ty[c] * x[c + dyp] +
                          Ty[c + dym] * x[c + dym] + tz_c * x_p + tz_m * x_m;
-      const double r = stream_in(&P.b[c]) - (stream_in(&L.diag[c]) * x_c - off);
-      stream_out(&rv[c], r);
+      const double r = stream_in<NT>(&P.b[c]) - (stream_in<NT>(&L.diag[c]) * x_c - off);
+      stream_out<NT>(&rv[c], r);
       rr += r * r;
       tz_m = tz_c;
       x_m = x_c;
@@ -1112,6 +1112,7 @@ __global__ __launch_bounds__(kBlock) void k_true_resid(Tables T, TileList TL) {
 // Galerkin warm guess, once FIN_BB has solved for c: x0 = c1 dE(n) + c2
 // dE(n-1), formed at the cell and its neighbours on the fly, and r = b - A x0
 // with the assembled FP64 operator; partial ||r||^2 for FIN_WARM.
+template <bool NT>
 __global__ __launch_bounds__(kBlock) void k_warm_x(Tables T, TileList TL) {
   int tid;
   const Tile t = get_tile(TL, tid);
@@ -1145,9 +1146,9 @@ __global__ __launch_bounds__(kBlock) void k_warm_x(Tables T, TileList TL) {
       const double off = Tx[c] * g(c + dxp) + Tx[c + dxm] * g(c + dxm) +
                          Ty[c] * g(c + dyp) + Ty[c + dym] * g(c + dym) +
                          Tz[c] * x_p + tz_m * x_m;
-      const double r = stream_in(&P.b[c]) - (stream_in(&L.diag[c]) * x_c - off);
-      stream_out(&P.x[c], x_c);
-      stream_out(&rv[c], r);
+      const double r = stream_in<NT>(&P.b[c]) - (stream_in<NT>(&L.diag[c]) * x_c - off);
+      stream_out<NT>(&P.x[c], x_c);
+      stream_out<NT>(&rv[c], r);
       rr += r * r;
       tz_m = Tz[c];
       x_m = x_c;
@@ -1295,6 +1296,7 @@ __device__ __forceinline__ bool commit_now(const Scal &sc) {
   return sc.live && sc.phase == PH_DONE && sc.status == ST_OK && !sc.committed;
 }
 
+template <bool NT>
 __global__ __launch_bounds__(kBlock) void k_update_E(Tables T, TileList TL,
                                                      double floor,
                                                      int copy_only, int in_solve) {
@@ -1314,10 +1316,10 @@ __global__ __launch_bounds__(kBlock) void k_update_E(Tables T, TileList TL,
       const double d = P.x[c];
       dd += d * d;
       if (copy_only) {
-        stream_out(&S.Eout[c], d);
+        stream_out<NT>(&S.Eout[c], d);
       } else {
-        const double en = stream_in(&S.E[c]) + d;
-        stream_out(&S.Eout[c], en);
+        const double en = stream_in<NT>(&S.E[c]) + d;
+        stream_out<NT>(&S.Eout[c], en);
         double w = fabs(en);
         w = (w < floor) ? floor : w;
         if (w > 0.0) {
@@ -1701,7 +1703,10 @@ ProfScope::~ProfScope() {
 void launch_assemble(const Tables &T, TileList L0, double c, double theta,
                      double dmax, double rmin, int mixed, int local,
                      double coupling, hipStream_t s) {
-  if (L0.nblocks) LAUNCH(K_ASSEMBLE, k_assemble, L0.nblocks, kBlock, s, T, L0, c, theta, dmax, rmin, mixed, local, coupling);
+  if (!L0.nblocks) return;
+  with_stream(T, [&](auto nt) {
+    LAUNCH(K_ASSEMBLE, k_assemble<nt()>, L0.nblocks, kBlock, s, T, L0, c, theta, dmax, rmin, mixed, local, coupling);
+  });
 }
 
 void launch_coarsen(const Tables &T, TileList LC, int lc, double scale,
@@ -1781,12 +1786,14 @@ void launch_spmv_f(const Tables &T, TileList F0, int km, hipStream_t s) {
 
 void launch_spmv_p(const Tables &T, TileList L0, int lazy, int km, hipStream_t s) {
   if (!L0.nblocks) return;
-  if (lazy && km == KM_FP64) LAUNCH(K_SPMV_PX, (k_spmv_p<true, KM_FP64>), L0.nblocks, kBlock, s, T, L0);
-  else if (lazy && km == KM_MIX64) LAUNCH(K_SPMV_PX, (k_spmv_p<true, KM_MIX64>), L0.nblocks, kBlock, s, T, L0);
-  else if (lazy) LAUNCH(K_SPMV_PX, (k_spmv_p<true, KM_MIX32>), L0.nblocks, kBlock, s, T, L0);
-  else if (km == KM_MIX64) LAUNCH(K_SPMV_P, (k_spmv_p<false, KM_MIX64>), L0.nblocks, kBlock, s, T, L0);
-  else if (km == KM_MIX32) LAUNCH(K_SPMV_P, (k_spmv_p<false, KM_MIX32>), L0.nblocks, kBlock, s, T, L0);
-  else LAUNCH(K_SPMV_P, (k_spmv_p<false, KM_FP64>), L0.nblocks, kBlock, s, T, L0);
+  with_stream(T, [&](auto nt) {
+    if (lazy && km == KM_FP64) LAUNCH(K_SPMV_PX, (k_spmv_p<true, KM_FP64, nt()>), L0.nblocks, kBlock, s, T, L0);
+    else if (lazy && km == KM_MIX64) LAUNCH(K_SPMV_PX, (k_spmv_p<true, KM_MIX64, nt()>), L0.nblocks, kBlock, s, T, L0);
+    else if (lazy) LAUNCH(K_SPMV_PX, (k_spmv_p<true, KM_MIX32, nt()>), L0.nblocks, kBlock, s, T, L0);
+    else if (km == KM_MIX64) LAUNCH(K_SPMV_P, (k_spmv_p<false, KM_MIX64, nt()>), L0.nblocks, kBlock, s, T, L0);
+    else if (km == KM_MIX32) LAUNCH(K_SPMV_P, (k_spmv_p<false, KM_MIX32, nt()>), L0.nblocks, kBlock, s, T, L0);
+    else LAUNCH(K_SPMV_P, (k_spmv_p<false, KM_FP64, nt()>), L0.nblocks, kBlock, s, T, L0);
+  });
 }
 
 void launch_z_out(const Tables &T, TileList L0, int fused, double *out, hipStream_t s) {
@@ -1802,14 +1809,19 @@ void launch_xfix(const Tables &T, TileList L0, int km, hipStream_t s) {
 
 void launch_update(const Tables &T, TileList L0, int km, int r_only, hipStream_t s) {
   if (!L0.nblocks) return;
-  if (r_only) LAUNCH(K_UPDATE_R, (k_update<KM_FP64, false>), L0.nblocks, kBlock, s, T, L0);
-  else if (km == KM_MIX32) LAUNCH(K_UPDATE, (k_update<KM_MIX32, true>), L0.nblocks, kBlock, s, T, L0);
-  else if (km == KM_MIX64) LAUNCH(K_UPDATE, (k_update<KM_MIX64, true>), L0.nblocks, kBlock, s, T, L0);
-  else LAUNCH(K_UPDATE, (k_update<KM_FP64, true>), L0.nblocks, kBlock, s, T, L0);
+  with_stream(T, [&](auto nt) {
+    if (r_only) LAUNCH(K_UPDATE_R, (k_update<KM_FP64, false, nt()>), L0.nblocks, kBlock, s, T, L0);
+    else if (km == KM_MIX32) LAUNCH(K_UPDATE, (k_update<KM_MIX32, true, nt()>), L0.nblocks, kBlock, s, T, L0);
+    else if (km == KM_MIX64) LAUNCH(K_UPDATE, (k_update<KM_MIX64, true, nt()>), L0.nblocks, kBlock, s, T, L0);
+    else LAUNCH(K_UPDATE, (k_update<KM_FP64, true, nt()>), L0.nblocks, kBlock, s, T, L0);
+  });
 }
 
 void launch_true_resid(const Tables &T, TileList L0, hipStream_t s) {
-  if (L0.nblocks) LAUNCH(K_TRUE_RESID, k_true_resid, L0.nblocks, kBlock, s, T, L0);
+  if (!L0.nblocks) return;
+  with_stream(T, [&](auto nt) {
+    LAUNCH(K_TRUE_RESID, k_true_resid<nt()>, L0.nblocks, kBlock, s, T, L0);
+  });
 }
 
 
@@ -1818,7 +1830,10 @@ void launch_local(const Tables &T, TileList L0, int colour, hipStream_t s) {
 }
 
 void launch_warm_x(const Tables &T, TileList L0, hipStream_t s) {
-  if (L0.nblocks) LAUNCH(K_WARM_X, k_warm_x, L0.nblocks, kBlock, s, T, L0);
+  if (!L0.nblocks) return;
+  with_stream(T, [&](auto nt) {
+    LAUNCH(K_WARM_X, k_warm_x<nt()>, L0.nblocks, kBlock, s, T, L0);
+  });
 }
 
 void launch_apply(const Tables &T, TileList L0, const double *u, double *out,
@@ -1860,9 +1875,11 @@ void launch_warm_revert(const Tables &T, TileList L0, hipStream_t s) {
 
 void launch_update_E(const Tables &T, TileList L0, double floor, int copy_only,
                      hipStream_t s, int in_solve) {
-  if (L0.nblocks)
-    LAUNCH(K_UPDATE_E, k_update_E, L0.nblocks, kBlock, s, T, L0, floor, copy_only,
+  if (!L0.nblocks) return;
+  with_stream(T, [&](auto nt) {
+    LAUNCH(K_UPDATE_E, k_update_E<nt()>, L0.nblocks, kBlock, s, T, L0, floor, copy_only,
            in_solve);
+  });
 }
 
 }  // namespace fld
