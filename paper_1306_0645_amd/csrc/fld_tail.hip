@@ -91,12 +91,13 @@ __device__ __forceinline__ double cg_row(const CgCell &a, const double *p) {
 // calls it.  WAVE: n <= 64, only wave 0 works and no barrier is taken.
 // HOLD: the operator (cell[u], loaded by the caller) and x stay in registers;
 // otherwise the operator is read in each iteration, two cells' loads at a
-// time (all 16 at once would spill), x accumulates in xm (memory) and the
-// reciprocal diagonal lies behind it.
+// time (all 16 at once would spill), x accumulates in xm and the reciprocal
+// diagonal lies in im (memory).
 template <int CPT, bool WAVE, bool HOLD>
 __device__ __forceinline__ void coarse_cg(const LevelDev &L, CgCell (&cell)[HOLD ? CPT : 1],
                                           const double (&f)[CPT], double (&x)[HOLD ? CPT : 1],
-                                          double *xm, double *sp, double *red) {
+                                          double *__restrict__ xm, double *__restrict__ im,
+                                          double *sp, double *red) {
   const int n = L.n;
   int slot = 0;
   auto sums = [&](double (&v)[2]) {
@@ -127,7 +128,7 @@ __device__ __forceinline__ void coarse_cg(const LevelDev &L, CgCell (&cell)[HOLD
         id = cell[u].id = 1.0 / cell[u].d;
       } else {
         xm[c] = 0.0;
-        xm[n + c] = id = 1.0 / L.diag[c];
+        im[c] = id = 1.0 / L.diag[c];
       }
       const double t = r[u] * id;
       sp[c] = t;
@@ -201,7 +202,7 @@ __device__ __forceinline__ void coarse_cg(const LevelDev &L, CgCell (&cell)[HOLD
         if constexpr (HOLD) x[u] += alpha * sp[c];
         else xm[c] += alpha * sp[c];
         r[u] -= alpha * q[u];
-        rd[u] = r[u] * (HOLD ? cell[HOLD ? u : 0].id : xm[n + c]);
+        rd[u] = r[u] * (HOLD ? cell[HOLD ? u : 0].id : im[c]);
         a2[0] += r[u] * r[u];
         a2[1] += r[u] * rd[u];
       }
@@ -549,9 +550,9 @@ __device__ __forceinline__ void tail_lds(const Tables &T, int p, int lt, int lc,
   const double f[1] = {c < L2.n ? (double)fcg : 0.0};
   double x[1] = {0.0};
   if (L2.n <= 64) {
-    if (c < 64) coarse_cg<1, true, true>(L2, cell, f, x, nullptr, sp, red);
+    if (c < 64) coarse_cg<1, true, true>(L2, cell, f, x, nullptr, nullptr, sp, red);
   } else {
-    coarse_cg<1, false, true>(L2, cell, f, x, nullptr, sp, red);
+    coarse_cg<1, false, true>(L2, cell, f, x, nullptr, nullptr, sp, red);
   }
   R *xl = ns == 2 ? xc : (!TOP || ns == 1) ? xb : xa;
   if (c < L2.n) xl[c] = (R)x[0];
@@ -749,7 +750,7 @@ __device__ __forceinline__ void level_cg(const LevelDev &L, double *xm, double *
       if constexpr (HOLD) cg_load(cell[u], L, c);
     }
   }
-  coarse_cg<CPT, false, HOLD>(L, cell, f, x, xm, sp, red);
+  coarse_cg<CPT, false, HOLD>(L, cell, f, x, xm, xm + L.n, sp, red);
 #pragma unroll
   for (int u = 0; u < CPT; ++u) {
     const int c = threadIdx.x + u * kTailBlock;
@@ -810,7 +811,7 @@ __global__ __launch_bounds__(kTailBlock) void k_vtail(Tables T, int nu_pre,
           f[0] = (double)((const R *)LC.f)[c];
           cg_load(cell[0], LC, c);
         }
-        coarse_cg<1, true, true>(LC, cell, f, x, nullptr, sp, red);
+        coarse_cg<1, true, true>(LC, cell, f, x, nullptr, nullptr, sp, red);
         if (c < LC.n) ((R *)LC.x)[c] = (R)x[0];
       }
     } else if (LC.n <= kTailBlock) {
