@@ -158,7 +158,7 @@ typedef struct fld_params {
                           Mcell-updates/s with 0 and 2658 with 4096).  From
                           512 on, red/black cycles other than V(1,1) send
                           levels of up to 4096 cells there too (32^3, V(2,2):
-                          281 -> 226 us a step) */
+                          277 -> 230 us a step) */
   int32_t smoother;    /* fld_smoother; default FLD_SMOOTH_RBGS */
   int32_t fused_levels;/* under V(1,1) red/black every level above the tail runs
                           two fused passes: the finest fused_levels levels on

@@ -1,6 +1,6 @@
 // One-sweep V-cycle passes for levels that do not fill the GPU: a block does
-// a small box of the level (up to 16 x 8 x 4 cells) at once instead of
-// marching through planes.
+// a small box of the level (up to 512 cells, 16 x 8 x 4 where the level is not
+// thin) at once instead of marching through planes.
 //
 // The algebra is that of the marching passes (x = 0 on entry, one red/black
 // sweep before and one black/red sweep after the coarse-grid correction):
@@ -25,7 +25,8 @@
 
 namespace fld {
 
-constexpr int kBX = kBoxX, kBY = kBoxY, kBZ = kBoxZ;               // largest box
+constexpr int kBX = kBoxX, kBY = kBoxY, kBZ = kBoxZ;               // the widest box (box_shape:
+                                                                  // the others fit its buffers)
 constexpr int kYN = (kBX + 4) * (kBY + 4) * (kBZ + 4);             // its + 2 frame
 constexpr int kHN = (kBX + 2) / 2 * (kBY + 2) * (kBZ + 2);         // black half of the + 1 frame
 constexpr int kYS = (kYN + kBlock - 1) / kBlock, kHS = (kHN + kBlock - 1) / kBlock;

@@ -139,7 +139,7 @@ Hier make_hier(const fld_grid &g, const fld_params &p) {
   while (h.tail > 1 && h.cells(h.tail - 1) <= tc) --h.tail;
   // A cycle of per-sweep passes pays a launch per half-sweep, so from 512 on
   // it takes the level above as well, as far as the tail kernel holds it in
-  // LDS (32^3 step, FP64 V(2,2): 281 -> 226 us; batch of 24, mixed V(2,2):
+  // LDS (32^3 step, FP64 V(2,2): 277 -> 230 us; batch of 24, mixed V(2,2):
   // 2.90 -> 2.82 ms).  The fused cycle's two box passes cost what the level
   // costs the one workgroup (64^3 mixed 3500 -> 3470 us, 96 x 64 x 40 FP64
   // 1285 -> 1310, 256^3 mixed 15.75 -> 15.82 ms): it keeps them

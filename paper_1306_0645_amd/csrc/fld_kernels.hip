@@ -14,7 +14,7 @@
 // (x, y) column of the tile and walks its tz planes, so x-consecutive lanes
 // read x-consecutive cells (coalesced).  Blocks are remapped so that each of
 // the 8 XCDs gets a contiguous run of tiles and neighbouring tiles share an L2.
-// Reductions are deterministic: a fixed wave64 butterfly, a fixed LDS order,
+// Reductions are deterministic: wave sums by DPP row scans, a fixed LDS order,
 // one partial per tile, then a per-problem finalize kernel that sums the
 // partials in tile order.
 

@@ -14,9 +14,10 @@
 // level of at most 64 cells is solved by one wave without any barrier.  The
 // CG carries r.z and ||r||^2 through one reduction and scales by the
 // reciprocal of the diagonal, divided once a solve.
-// A coarsest level of up to 16 x 1024 cells (extents that stop halving early,
-// such as 25^3 under 200^3) keeps r, x and q in registers and p in LDS, and
-// streams the operator from the L2 in each iteration.  Measured per cycle
+// A coarsest level of up to 2 x 1024 cells keeps its operator in registers; one
+// of up to 16 x 1024 (extents that stop halving early, such as 25^3 under
+// 200^3) keeps r and q in registers, p in LDS and x in memory, and streams the
+// operator and its reciprocal diagonal from the L2 in each iteration.  Measured per cycle
 // (before: every phase through memory, three reductions of two barriers each
 // per CG iteration, exact divisions): 8^3 and 4^3 levels of 64^3 and 256^3
 // 21.3 -> 8.0 us, of 256^3 in FP64 24.8 -> 10.0 us; one 4^3 level 8.1 ->
