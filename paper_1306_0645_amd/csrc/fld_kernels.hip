@@ -332,6 +332,10 @@ __global__ __launch_bounds__(kBlock) void k_coarsen(Tables T, TileList LC,
   if (!asm_due(sc)) return;
   const LevelDev F = T.lv[(lc - 1) * T.nprob + t.prob];
   const LevelDev C = T.lv[lc * T.nprob + t.prob];
+  const ProbDev &P = T.pd[t.prob];
+  // the coarsest level, where its solve streams the operator: the reciprocal
+  // diagonal too, behind that solve's x
+  const bool inv = lc == P.levels - 1 && C.n > kTailSmall && C.n <= kTailBig;
   const Col col = tile_col(t);
   if (!col.on) return;
   const int fx = F.nx, fy = F.ny, fz = F.nz;
@@ -386,6 +390,7 @@ __global__ __launch_bounds__(kBlock) void k_coarsen(Tables T, TileList LC,
     C.Ty[o] = typ;
     C.Tz[o] = tzp;
     C.diag[o] = diag;
+    if (inv) P.cs[C.n + o] = 1.0 / diag;
     if (mixed) {
       C.Tx32[o] = (float)txp;
       C.Ty32[o] = (float)typ;

@@ -13,7 +13,8 @@
 // row operations, then every wave sums the 16 wave results), and a coarsest
 // level of at most 64 cells is solved by one wave without any barrier.  The
 // CG carries r.z and ||r||^2 through one reduction and scales by the
-// reciprocal of the diagonal, divided once a solve.
+// reciprocal of the diagonal, divided once a solve (once an assembly where the
+// operator is streamed).
 // A coarsest level of up to 2 x 1024 cells keeps its operator in registers; one
 // of up to 16 x 1024 (extents that stop halving early, such as 25^3 under
 // 200^3) keeps r and q in registers, p in LDS and x in memory, and streams the
@@ -92,12 +93,12 @@ __device__ __forceinline__ double cg_row(const CgCell &a, const double *p) {
 // calls it.  WAVE: n <= 64, only wave 0 works and no barrier is taken.
 // HOLD: the operator (cell[u], loaded by the caller) and x stay in registers;
 // otherwise the operator is read in each iteration, two cells' loads at a
-// time (all 16 at once would spill), x accumulates in xm and the reciprocal
-// diagonal lies in im (memory).
+// time (all 16 at once would spill), x accumulates in xm (memory) and im holds
+// the reciprocal diagonal, from k_coarsen.
 template <int CPT, bool WAVE, bool HOLD>
 __device__ __forceinline__ void coarse_cg(const LevelDev &L, CgCell (&cell)[HOLD ? CPT : 1],
                                           const double (&f)[CPT], double (&x)[HOLD ? CPT : 1],
-                                          double *__restrict__ xm, double *__restrict__ im,
+                                          double *__restrict__ xm, const double *__restrict__ im,
                                           double *sp, double *red) {
   const int n = L.n;
   int slot = 0;
@@ -129,7 +130,7 @@ __device__ __forceinline__ void coarse_cg(const LevelDev &L, CgCell (&cell)[HOLD
         id = cell[u].id = 1.0 / cell[u].d;
       } else {
         xm[c] = 0.0;
-        im[c] = id = 1.0 / L.diag[c];
+        id = im[c];
       }
       const double t = r[u] * id;
       sp[c] = t;
